@@ -185,7 +185,8 @@ scat_status scat_plan_reserve(scat_plan *plan, long batch, int with_backward);
  * no kernel timing (scat_plan_timing_* is ignored for it).  A batch whose intermediates exceed
  * the buffer is run in consecutive chunks on `stream`.
  * Errors: as scat_forward, and SCAT_ERR_WORKSPACE if a single plane of this plan needs more
- * than the buffer (scat_plan_workspace_bytes(plan, 1) > SCAT_STATIC_SCRATCH_MB MiB); then
+ * than the buffer (1-D and 2-D: scat_plan_workspace_bytes(plan, 1) > SCAT_STATIC_SCRATCH_MB MiB;
+ * 3-D plans whose workspace exceeds it take fewer nodes at a time where that suffices); then
  * nothing is enqueued.
  * Every call on a GPU shares that GPU's buffer, whatever the plan or stream: calls whose work
  * overlaps in time on one GPU race; the caller orders them (one stream, or events).  The

@@ -35,15 +35,14 @@ __global__ __launch_bounds__(256) void k3_real_to_complex(const float *__restric
     out[i] = make_float2(x[i], 0.f);
 }
 
-// dst[v][e] (+)= src[v][e] * filt[e * fstride]: one real table applied to every volume of the
-// batch (fstride = 2 reads one member of a table pair stored as complex numbers)
+// dst[v][e] (+)= src[v][e] * filt[e]: one real table applied to every volume of the batch
 __global__ __launch_bounds__(256) void k3_mul_table(const float2 *__restrict__ src,
-                                                    const float *__restrict__ filt, int fstride,
+                                                    const float *__restrict__ filt,
                                                     float2 *__restrict__ dst, long total, long n,
                                                     int accumulate) {
   const long stride = static_cast<long>(gridDim.x) * blockDim.x;
   for (long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const float f = filt[(i % n) * fstride];
+    const float f = filt[i % n];
     const float2 v = src[i];
     float2 o = make_float2(v.x * f, v.y * f);
     if (accumulate) {
@@ -78,25 +77,6 @@ __global__ __launch_bounds__(256) void k3_tile_phi(const float2 *__restrict__ Gs
                          (static_cast<size_t>(a & (m0 - 1)) * m1 + (b & (m1 - 1))) * m2 + (c & (m2 - 1))];
     const float f = phi[e];
     float2 o = make_float2(gs.x * f, gs.y * f);
-    if (accumulate) {
-      const float2 d = dst[i];
-      o.x += d.x;
-      o.y += d.y;
-    }
-    dst[i] = o;
-  }
-}
-
-// dst[v][e] (+)= src[v][e] * c[e] (or conj(c[e])): a pair of real tables stored as one complex
-__global__ __launch_bounds__(256) void k3_mul_ctable(const float2 *__restrict__ src,
-                                                     const float2 *__restrict__ ctab,
-                                                     float2 *__restrict__ dst, long total, long n,
-                                                     int conj_table, int accumulate) {
-  const long stride = static_cast<long>(gridDim.x) * blockDim.x;
-  for (long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x; i < total; i += stride) {
-    float2 c = ctab[i % n];
-    if (conj_table) c.y = -c.y;
-    float2 o = c_mul(src[i], c);
     if (accumulate) {
       const float2 d = dst[i];
       o.x += d.x;
@@ -168,9 +148,12 @@ __global__ __launch_bounds__(256) void k3_sample(const float2 *__restrict__ src,
 //
 // A 3-D transform is split into the two slab axes (one workgroup holds whole N1 x N2
 // slabs: rows through registers, a transposition through LDS, columns through registers)
-// and axis 0 (columns of stride N1*N2).  Around them:
+// and axis 0 (columns of stride N1*N2).  Every launch takes a LIST of nodes (j, l)
+// (blockIdx.y): a 32^3 volume has 32 slabs of 64 threads, so one node of a small batch fills
+// a quarter of the chip and runs at the latency of its load - transform - store chain; with
+// the nodes of a whole order side by side the launches are both larger and fewer.
 //   k3_slab_mul_inv   W_p = inverse transform over the slab axes of F^ (g_2p + i g_2p+1), all
-//                     pairs of one (j, l) in one launch (the slab of F^ is read once).  The
+//                     pairs of a (j, l) (the slab of F^ is read once).  The
 //                     signal F is real and the tables g_m are real with the parity of l, so
 //                     F conv g_m is real (l even) or imaginary (l odd) and one complex
 //                     transform carries two of them: |W_p|^2 = |F conv g_2p|^2 +
@@ -182,16 +165,28 @@ __global__ __launch_bounds__(256) void k3_sample(const float2 *__restrict__ src,
 //                     k0 <= n0/2 and, by conjugate symmetry, for n0 - k0), product with the
 //                     lowpass and the sum over the aliases of the slab axes (periodic
 //                     subsampling by 2^J seen from the Fourier side)
-//   k3_fold0          the aliases of axis 0; the small inverse transforms then give S
+//   k3_out            the aliases of axis 0, the small inverse transform, real part and crop
+
+// symmetric extension of an axis of n samples to P (the caller's volume read in place)
+__device__ __forceinline__ int mirror_source(int i, int n, int P) {
+  const int h = (P - n + 1) / 2;
+  int v = i < n + h ? i : i - P;
+  v %= 2 * n;
+  if (v < 0) v += 2 * n;
+  return v < n ? v : 2 * n - 1 - v;
+}
 
 template <int N1, int N2, bool SPLIT>
-__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_mul_inv(const float2 *__restrict__ Fh,
-                                                       const float2 *__restrict__ tab,
-                                                       float2 *__restrict__ W, long slabs, int n0,
-                                                       int M, size_t mstride,
+__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_mul_inv(Nodes3 nodes, long slabs, int n0,
+                                                       size_t mstride,
                                                        const float2 *__restrict__ tw, int tw_n) {
   using S = Slab<N1, N2>;
+  constexpr bool WAVE = S::TS <= 64;  // a slab's threads are lanes of one wavefront
   extern __shared__ float2 lds[];
+  const Node3 &nd = nodes.v[blockIdx.y];
+  const int M = nd.M;
+  // SPLIT: one filter per workgroup (blockIdx.z), no loop state to carry
+  if (SPLIT && static_cast<int>(blockIdx.z) >= M) return;
   const int s = threadIdx.x / S::TS, q = threadIdx.x % S::TS;
   const long slab = static_cast<long>(blockIdx.x) * S::SPW + s;
   const bool live = slab < slabs;
@@ -201,48 +196,49 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_mul_inv(const floa
   const int c = q % N2, t1 = q / N2;
   const int k0 = static_cast<int>(sl % n0);
   const size_t base = static_cast<size_t>(sl) * N1 * N2;
-  const float2 *src = Fh + base + r * N2 + t;
-  // the slab of F^ stays in registers across the filters; the 1024-thread variants (128
-  // registers per thread) instead take one filter per workgroup and read it again
+  const float2 *__restrict__ src = nd.src + base + r * N2 + t;
+  const float2 *__restrict__ tab = nd.tab;
+  float2 *__restrict__ W = nd.W;
+  // the slab of F^ stays in registers across the filters, except in the SPLIT variants
   constexpr bool KEEP = !SPLIT;
   float2 f[KEEP ? 16 : 1];
   if (KEEP) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) f[KEEP ? i : 0] = src[S::T2 * i];
   }
-  // SPLIT: one filter per workgroup (blockIdx.y), no loop state to carry
-  const int m_first = SPLIT ? static_cast<int>(blockIdx.y) : 0, m_last = SPLIT ? m_first + 1 : M;
+  const int m_first = SPLIT ? static_cast<int>(blockIdx.z) : 0, m_last = SPLIT ? m_first + 1 : M;
   for (int m = m_first; m < m_last; ++m) {
     const float2 *tb = tab + (static_cast<size_t>(m) * n0 + k0) * N1 * N2 + r * N2 + t;
     float2 v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       v[i] = c_mul(KEEP ? f[KEEP ? i : 0] : src[S::T2 * i], tb[S::T2 * i]);
-      // two batches of loads, so that the operands in flight fit
-      if (!KEEP && i == 7) __builtin_amdgcn_sched_barrier(0);
+      // (1024 threads, 128 registers each) two batches of loads, so that the operands in flight fit
+      if (!KEEP && S::NT == 1024 && i == 7) __builtin_amdgcn_sched_barrier(0);
     }
-    S::template transform<true>(v, area, r, t, c, t1, tw, tw_n);
+    S::template transform<true, WAVE>(v, area, r, t, c, t1, tw, tw_n);
     if (live) {
       float2 *dst = W + static_cast<size_t>(m) * mstride + base + c;
 #pragma unroll
       for (int i = 0; i < 16; ++i) dst[(t1 + S::T1 * i) * N2] = v[i];
     }
-    if (!SPLIT) __syncthreads();  // the slab area is reused by the next filter
+    if (!SPLIT) group_sync<WAVE>();  // the slab area is reused by the next filter
   }
 }
 
-// Tin holds slabs k0 = 0 .. n0/2 only (the axis-0 spectrum of a real signal); the slab
+// A node's T holds slabs k0 = 0 .. n0/2 only (the axis-0 spectrum of a real signal); the slab
 // n0 - k0 of U^ and of the folded lowpass product is the conjugate of slab k0 with both
-// slab indices negated, and is written from the same registers.
+// slab indices negated, and is written from the same registers.  phi == nullptr: U^ only.
 template <int N1, int N2>
-__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_low(const float2 *__restrict__ Tin,
-                                                       float2 *__restrict__ Uout,
+__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_low(Nodes3 nodes,
                                                        const float *__restrict__ phi,
                                                        float2 *__restrict__ P, long slabs, int n0,
-                                                       int J, size_t p_vol_stride, size_t chan_off,
+                                                       int J, size_t p_vol_stride, size_t p_chan_stride,
                                                        const float2 *__restrict__ tw, int tw_n) {
   using S = Slab<N1, N2>;
+  constexpr bool WAVE = S::TS <= 64;
   extern __shared__ float2 lds[];
+  const Node3 &nd = nodes.v[blockIdx.y];
   const int s = threadIdx.x / S::TS, q = threadIdx.x % S::TS;
   const long slab = static_cast<long>(blockIdx.x) * S::SPW + s;
   const bool live = slab < slabs;
@@ -254,11 +250,12 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_low(const floa
   const int k0 = static_cast<int>(sl % H);
   const long vol = sl / H;
   const bool twin = k0 > 0 && k0 < n0 - k0;  // slab n0 - k0 is a different slab
-  const float2 *src = Tin + static_cast<size_t>(sl) * N1 * N2 + r * N2 + t;
+  const float2 *__restrict__ src = nd.T + static_cast<size_t>(sl) * N1 * N2 + r * N2 + t;
+  float2 *__restrict__ Uout = nd.U;
   float2 v[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) v[i] = src[S::T2 * i];
-  S::template transform<false>(v, area, r, t, c, t1, tw, tw_n);
+  S::template transform<false, WAVE>(v, area, r, t, c, t1, tw, tw_n);
   if (Uout != nullptr && live) {
     float2 *dst = Uout + (static_cast<size_t>(vol) * n0 + k0) * N1 * N2 + c;
 #pragma unroll
@@ -270,18 +267,19 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_low(const floa
         dm[((N1 - (t1 + S::T1 * i)) & (N1 - 1)) * N2] = make_float2(v[i].x, -v[i].y);
     }
   }
+  if (phi == nullptr) return;
   // lowpass product, then the sum over the 4^J aliases of the slab axes
   const float *ph = phi + static_cast<size_t>(k0) * N1 * N2 + c;
-  __syncthreads();
+  group_sync<WAVE>();
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const float g = ph[(t1 + S::T1 * i) * N2];
     area[(t1 + S::T1 * i) * S::RS + c] = make_float2(v[i].x * g, v[i].y * g);
   }
-  __syncthreads();
+  group_sync<WAVE>();
   const int m1 = N1 >> J, m2 = N2 >> J, al = 1 << J;
   if (!live) return;
-  float2 *pv = P + static_cast<size_t>(vol) * p_vol_stride + chan_off;
+  float2 *pv = P + static_cast<size_t>(vol) * p_vol_stride + nd.chan * p_chan_stride;
   float2 *dst = pv + static_cast<size_t>(k0) * m1 * m2;
   float2 *dm = pv + static_cast<size_t>(n0 - k0) * m1 * m2;
   for (int o = q; o < m1 * m2; o += S::TS) {
@@ -299,18 +297,19 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_low(const floa
 }
 
 // Axis 0 of [volumes][E*T][Mc]: a workgroup takes TC columns of one volume, thread (t, c)
-// holds rows t + T i.  xreal != nullptr: forward transform of the real input.  Else: inverse
-// transform of the M signals W_m, root of the sum of their squared moduli, forward transform.
-// The transformed signal is real, so only rows 0 .. N0/2 of its spectrum are stored:
-// dst [volumes][N0/2 + 1][Mc].
+// holds rows t + T i.  xreal != nullptr: forward transform of the real input (of u0 x u1 x u2
+// samples, extended symmetrically to the grid with u0 > 0, else of the grid's own size).
+// Else: inverse transform of the node's M signals W_m, root of the sum of their squared
+// moduli, forward transform.  The transformed signal is real, so only rows 0 .. N0/2 of its
+// spectrum are stored: T [volumes][N0/2 + 1][Mc].
 template <int E, int T>
-__global__ __launch_bounds__(256) void k3_axis0_rho(const float2 *__restrict__ W,
-                                                    const float *__restrict__ xreal,
-                                                    float2 *__restrict__ dst, int Mc, int TC, int M,
+__global__ __launch_bounds__(256) void k3_axis0_rho(Nodes3 nodes, const float *__restrict__ xreal,
+                                                    int u0, int u1, int u2, int n2, int Mc, int TC,
                                                     size_t mstride, const float2 *__restrict__ tw,
                                                     int tw_n) {
   constexpr int N0 = E * T;
   extern __shared__ float2 lds[];
+  const Node3 &nd = nodes.v[blockIdx.y];
   const int KS = T * TC + (E == 32 ? 0 : 1);
   const int c = threadIdx.x % TC, t = threadIdx.x / TC;
   const int tiles = Mc / TC;
@@ -322,13 +321,23 @@ __global__ __launch_bounds__(256) void k3_axis0_rho(const float2 *__restrict__ W
   load_twiddles<E, T>(wt, t, tw, tw_n);
   float2 v[E];
   if (xreal != nullptr) {
+    if (u0 > 0) {
+      const int b = (c0 + c) / n2, e = (c0 + c) % n2;
+      const float *x = xreal + (static_cast<size_t>(vol) * u0 * u1 + mirror_source(b, u1, Mc / n2)) * u2 +
+                       mirror_source(e, u2, n2);
 #pragma unroll
-    for (int i = 0; i < E; ++i) v[i] = make_float2(xreal[off + i * step], 0.f);
+      for (int i = 0; i < E; ++i)
+        v[i] = make_float2(x[static_cast<size_t>(mirror_source(t + T * i, u0, N0)) * u1 * u2], 0.f);
+    } else {
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[i] = make_float2(xreal[off + i * step], 0.f);
+    }
   } else {
+    const float2 *__restrict__ W = nd.W;
     float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.f;
-    for (int m = 0; m < M; ++m) {
+    for (int m = 0; m < nd.M; ++m) {
       const float2 *p = W + static_cast<size_t>(m) * mstride + off;
 #pragma unroll
       for (int i = 0; i < E; ++i) v[i] = p[i * step];
@@ -340,23 +349,33 @@ __global__ __launch_bounds__(256) void k3_axis0_rho(const float2 *__restrict__ W
     for (int i = 0; i < E; ++i) v[i] = make_float2(__builtin_amdgcn_sqrtf(acc[i]), 0.f);
   }
   fft_core<E, T, false, false>(v, t, lds + c, KS, TC, wt);
-  float2 *o = dst + static_cast<size_t>(vol) * (N0 / 2 + 1) * Mc + static_cast<size_t>(t) * Mc + c0 + c;
+  float2 *o = nd.T + static_cast<size_t>(vol) * (N0 / 2 + 1) * Mc + static_cast<size_t>(t) * Mc + c0 + c;
 #pragma unroll
   for (int i = 0; i < E; ++i)
     if (t + T * i <= N0 / 2) o[i * step] = v[i];
 }
 
-// Backward pass, axis 0 of the P signals W_p [volumes][E*T][Mc] (in place).
-// MODE 0: inverse transform of every W_p (the slab axes are already done), written back as
-//         the filtered signals y_p, and acc = sum_p |y_p|^2.
-// MODE 1: y_p <- Re(gu) y_p / sqrt(acc) (0 where acc = 0), then the forward transform.
-template <int E, int T, int MODE>
-__global__ __launch_bounds__(256) void k3_axis0_back(float2 *__restrict__ W, float *__restrict__ acc,
-                                                     const float2 *__restrict__ gu, int Mc, int TC,
-                                                     int P, size_t mstride,
+// ---- backward pass of the fused plans.  For a node with signals y_p = IFFT(F^ c_p), given
+// the gradient g of rho = sqrt(sum_p |y_p|^2) along the slab axes' inverse transform (T):
+//   k3_slab_sum_inv   T = inverse slab transform of phi^ * tile(g_S^) (+ the spectra its
+//                     children contributed)
+//   k3_axis0_back     inverse transform along axis 0 of T and of every W_p, y_p g / rho,
+//                     forward transform along axis 0, in place
+//   k3_slab_fwd_mulacc  forward slab transform, product with conj(c_p), sum over the pairs:
+//                     the node's contribution to its source's gradient spectrum
+
+// W_p <- forward transform along axis 0 of g y_p / rho (0 where rho = 0), y_p = inverse
+// transform of W_p (the slab axes' inverse transforms are done).  The signals are read and
+// inverse-transformed twice, once for rho and once for the product: keeping them would take a
+// write and a read of every signal instead of the second read.  T holds rows 0 .. N0/2 where
+// the gradient is real by symmetry (nd.half) and all rows otherwise (its real part counts).
+template <int E, int T>
+__global__ __launch_bounds__(256) void k3_axis0_back(Nodes3 nodes, int Mc, int TC, size_t mstride,
                                                      const float2 *__restrict__ tw, int tw_n) {
   constexpr int N0 = E * T;
   extern __shared__ float2 lds[];
+  const Node3 &nd = nodes.v[blockIdx.y];
+  const int P = nd.M;
   const int KS = T * TC + (E == 32 ? 0 : 1);
   const int c = threadIdx.x % TC, t = threadIdx.x / TC;
   const int tiles = Mc / TC;
@@ -374,56 +393,70 @@ __global__ __launch_bounds__(256) void k3_axis0_back(float2 *__restrict__ W, flo
       wtab[idx] = tw[(idx / T) * (idx % T) * (tw_n / N0)];
     __syncthreads();
   }
-  float a[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    if (MODE == 0) {
-      a[i] = 0.f;
-    } else {
-      const float s2 = acc[off + i * step];
-      a[i] = over_sqrt(gu[off + i * step].x, s2);
-    }
-  }
   float2 vn[E];
   auto fetch = [&](int p) {
-    const float2 *w = W + static_cast<size_t>(p) * mstride + off;
+    const float2 *w = nd.W + static_cast<size_t>(p) * mstride + off;
 #pragma unroll
     for (int i = 0; i < E; ++i) vn[i] = w[i * step];
   };
+  float a[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) a[i] = 0.f;
   fetch(0);
+  float2 v[E];
   for (int p = 0; p < P; ++p) {
-    float2 *w = W + static_cast<size_t>(p) * mstride + off;
-    float2 v[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) v[i] = vn[i];
     if (p + 1 < P) fetch(p + 1);
-    if (MODE == 0) {
-      fft_core_tab<E, T, true, false>(v, t, lds + c, KS, TC, wtab + t, T);
+    fft_core_tab<E, T, true, false>(v, t, lds + c, KS, TC, wtab + t, T);
 #pragma unroll
-      for (int i = 0; i < E; ++i) a[i] += v[i].x * v[i].x + v[i].y * v[i].y;
-    } else {
+    for (int i = 0; i < E; ++i) a[i] += v[i].x * v[i].x + v[i].y * v[i].y;
+  }
+  // one pair: its signal is still in v; else the first one is requested again
+  float2 g[E];
+  {
+    const float2 *src = nd.T + static_cast<size_t>(vol) * (nd.half ? N0 / 2 + 1 : N0) * Mc + c0 + c;
 #pragma unroll
-      for (int i = 0; i < E; ++i) v[i] = make_float2(v[i].x * a[i], v[i].y * a[i]);
-      fft_core_tab<E, T, false, false>(v, t, lds + c, KS, TC, wtab + t, T);
+    for (int i = 0; i < E; ++i) {
+      const int row = t + T * i;
+      const bool mir = nd.half && row > N0 / 2;
+      g[i] = src[static_cast<size_t>(mir ? N0 - row : row) * Mc];
+      if (mir) g[i].y = -g[i].y;
     }
+  }
+  fft_core_tab<E, T, true, false>(g, t, lds + c, KS, TC, wtab + t, T);
+#pragma unroll
+  for (int i = 0; i < E; ++i) a[i] = over_sqrt(g[i].x, a[i]);
+  if (P > 1) fetch(0);
+  for (int p = 0; p < P; ++p) {
+    float2 *w = nd.W + static_cast<size_t>(p) * mstride + off;
+    if (P > 1) {
+#pragma unroll
+      for (int i = 0; i < E; ++i) v[i] = vn[i];
+      if (p + 1 < P) fetch(p + 1);
+      fft_core_tab<E, T, true, false>(v, t, lds + c, KS, TC, wtab + t, T);
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) v[i] = make_float2(v[i].x * a[i], v[i].y * a[i]);
+    fft_core_tab<E, T, false, false>(v, t, lds + c, KS, TC, wtab + t, T);
 #pragma unroll
     for (int i = 0; i < E; ++i) w[i * step] = v[i];
   }
-  if (MODE == 0) {
-#pragma unroll
-    for (int i = 0; i < E; ++i) acc[off + i * step] = a[i];
-  }
 }
 
-// Backward pass, slab axes: A[slab] += sum_p conj(c_p) * (forward slab transform of W_p), the
-// adjoint of k3_slab_mul_inv (c_p = the pair tables of the node); A's slab is read and
-// written once for all p.
+// Slab axes: A[slab] = sum_p conj(c_p) * (forward slab transform of W_p), the adjoint of
+// k3_slab_mul_inv (c_p = the pair tables of the node), written over W_0 (a slab is read and
+// written by the same workgroup only).
 template <int N1, int N2>
-__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_mulacc(
-    const float2 *__restrict__ W, const float2 *__restrict__ tab, float2 *__restrict__ A, long slabs,
-    int n0, int P, size_t mstride, const float2 *__restrict__ tw, int tw_n) {
+__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_mulacc(Nodes3 nodes, long slabs, int n0,
+                                                                         size_t mstride,
+                                                                         const float2 *__restrict__ tw,
+                                                                         int tw_n) {
   using S = Slab<N1, N2>;
+  constexpr bool WAVE = S::TS <= 64;
   extern __shared__ float2 lds[];
+  const Node3 &nd = nodes.v[blockIdx.y];
+  const int P = nd.M;
   const int s = threadIdx.x / S::TS, q = threadIdx.x % S::TS;
   const long slab = static_cast<long>(blockIdx.x) * S::SPW + s;
   const bool live = slab < slabs;
@@ -441,15 +474,15 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_mulacc(
 #pragma unroll
   for (int i = 0; i < 16; ++i) sum[i] = make_float2(0.f, 0.f);
   for (int p = 0; p < P; ++p) {
-    const float2 *src = W + static_cast<size_t>(p) * mstride + base + r * N2 + t;
+    const float2 *src = nd.W + static_cast<size_t>(p) * mstride + base + r * N2 + t;
     float2 v[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = src[S::T2 * i];
-    const float2 *tb = tab + (static_cast<size_t>(p) * n0 + k0) * N1 * N2 + c;
+    const float2 *tb = nd.tab + (static_cast<size_t>(p) * n0 + k0) * N1 * N2 + c;
     float2 gt[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) gt[i] = tb[(t1 + S::T1 * i) * N2];
-    S::template transform_tab<false>(v, area, r, t, c, t1, wtab);
+    S::template transform_tab<false, WAVE>(v, area, r, t, c, t1, wtab);
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       float2 g = gt[i];
@@ -458,16 +491,196 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_mulacc(
       sum[i].x += o.x;
       sum[i].y += o.y;
     }
-    __syncthreads();  // the slab area is reused by the next signal
+    group_sync<WAVE>();  // the slab area is reused by the next signal
   }
   if (!live) return;
-  float2 *dst = A + base + c;
+  float2 *dst = nd.W + base + c;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) dst[(t1 + S::T1 * i) * N2] = sum[i];
+}
+
+// T = inverse slab transform of phi^ * tile(g_S^) + sum of the item's spectra A: slabs 0 .. n0/2
+// where there are none (the gradient of the lowpass alone is real), else all of them.
+template <int N1, int N2>
+__global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_sum_inv(Sums3 sums, const float *__restrict__ phi,
+                                                       const float2 *__restrict__ Gs, long volumes, int n0,
+                                                       int J, int K, const float2 *__restrict__ tw, int tw_n) {
+  using S = Slab<N1, N2>;
+  constexpr bool WAVE = S::TS <= 64;
+  extern __shared__ float2 lds[];
+  const Sum3 &it = sums.v[blockIdx.y];
+  const int H = it.count == 0 ? n0 / 2 + 1 : n0;
+  const long slabs = volumes * H;
+  if (static_cast<long>(blockIdx.x) * S::SPW >= slabs) return;
+  const int s = threadIdx.x / S::TS, q = threadIdx.x % S::TS;
+  const long slab = static_cast<long>(blockIdx.x) * S::SPW + s;
+  const bool live = slab < slabs;
+  const long sl = live ? slab : slabs - 1;
+  float2 *area = lds + s * N1 * S::RS;
+  const int r = q / S::T2, t = q % S::T2;
+  const int c = q % N2, t1 = q / N2;
+  const int k0 = static_cast<int>(sl % H);
+  const long vol = sl / H;
+  const int m0 = n0 >> J, m1 = N1 >> J, m2 = N2 >> J;
+  const float2 *gs = Gs + ((static_cast<size_t>(vol) * K + it.chan) * m0 + (k0 & (m0 - 1))) * m1 * m2 +
+                     (c & (m2 - 1));
+  const float *ph = phi + static_cast<size_t>(k0) * N1 * N2 + c;
+  const size_t base = (static_cast<size_t>(vol) * n0 + k0) * N1 * N2 + c;
+  float2 v[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    float2 *d = dst + (t1 + S::T1 * i) * N2;
-    const float2 old = *d;
-    *d = make_float2(old.x + sum[i].x, old.y + sum[i].y);
+    const int row = t1 + S::T1 * i;
+    const float f = ph[row * N2];
+    const float2 g = gs[(row & (m1 - 1)) * m2];
+    v[i] = make_float2(g.x * f, g.y * f);
   }
+  for (int a = 0; a < it.count; ++a) {
+    const float2 *p = sums.A[it.first + a] + base;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float2 u = p[(t1 + S::T1 * i) * N2];
+      v[i].x += u.x;
+      v[i].y += u.y;
+    }
+  }
+  S::template transform_back<true, WAVE>(v, area, r, t, c, t1, tw, tw_n);
+  if (!live) return;
+  float2 *dst = it.T + static_cast<size_t>(sl) * N1 * N2 + r * N2 + t;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) dst[S::T2 * i] = v[i];
+}
+
+// dst[i] = sum of the first item's spectra (which may include dst itself)
+__global__ __launch_bounds__(256) void k3_sum_spectra(Sums3 sums, float2 *dst, long total) {
+  const long stride = static_cast<long>(gridDim.x) * blockDim.x;
+  const Sum3 &it = sums.v[0];
+  for (long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x; i < total; i += stride) {
+    float2 acc = make_float2(0.f, 0.f);
+    for (int a = 0; a < it.count; ++a) {
+      const float2 u = sums.A[it.first + a][i];
+      acc.x += u.x;
+      acc.y += u.y;
+    }
+    dst[i] = acc;
+  }
+}
+
+// out [volumes][E*T][Mc] = real part of the inverse transform along axis 0 of T
+template <int E, int T>
+__global__ __launch_bounds__(256) void k3_axis0_real(const float2 *__restrict__ src, float *__restrict__ out,
+                                                     int Mc, int TC, const float2 *__restrict__ tw, int tw_n) {
+  constexpr int N0 = E * T;
+  extern __shared__ float2 lds[];
+  const int KS = T * TC + (E == 32 ? 0 : 1);
+  const int c = threadIdx.x % TC, t = threadIdx.x / TC;
+  const int tiles = Mc / TC;
+  const long vol = blockIdx.x / tiles;
+  const int c0 = static_cast<int>(blockIdx.x % tiles) * TC;
+  const size_t off = static_cast<size_t>(vol) * N0 * Mc + static_cast<size_t>(t) * Mc + c0 + c;
+  const size_t step = static_cast<size_t>(T) * Mc;
+  float2 wt[E];
+  load_twiddles<E, T>(wt, t, tw, tw_n);
+  float2 v[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) v[i] = src[off + i * step];
+  fft_core<E, T, true, false>(v, t, lds + c, KS, TC, wt);
+#pragma unroll
+  for (int i = 0; i < E; ++i) out[off + i * step] = v[i].x;
+}
+
+// ---- output grids held whole by a workgroup: at most 4096 points, at most 32 a side, lines
+// transformed by one thread each
+constexpr int kOutPoints = 4096;
+
+template <int M, bool INV>
+__device__ __forceinline__ void line_fft(float2 *p, int stride) {
+  float2 v[M];
+#pragma unroll
+  for (int i = 0; i < M; ++i) v[i] = p[i * stride];
+  DftRegs<M, INV>::run(v);
+#pragma unroll
+  for (int i = 0; i < M; ++i) p[i * stride] = v[i];
+}
+template <bool INV>
+__device__ __forceinline__ void line_fft_any(float2 *p, int stride, int m) {
+  switch (m) {
+    case 2: line_fft<2, INV>(p, stride); break;
+    case 4: line_fft<4, INV>(p, stride); break;
+    case 8: line_fft<8, INV>(p, stride); break;
+    case 16: line_fft<16, INV>(p, stride); break;
+    case 32: line_fft<32, INV>(p, stride); break;
+    default: break;
+  }
+}
+// transform along the three axes of buf [m0][m1][m2 + 1]
+template <bool INV>
+__device__ __forceinline__ void cube_fft(float2 *buf, int m0, int m1, int m2) {
+  const int rs = m2 + 1;
+  for (int l = threadIdx.x; l < m0 * m1; l += blockDim.x) line_fft_any<INV>(buf + l * rs, 1, m2);
+  __syncthreads();
+  for (int l = threadIdx.x; l < m0 * m2; l += blockDim.x)
+    line_fft_any<INV>(buf + (l / m2) * m1 * rs + l % m2, rs, m1);
+  __syncthreads();
+  for (int l = threadIdx.x; l < m1 * m2; l += blockDim.x)
+    line_fft_any<INV>(buf + (l / m2) * rs + l % m2, m1 * rs, m0);
+  __syncthreads();
+}
+
+// One workgroup per (volume, channel): the sum over the aliases of axis 0 of P [n0][m1 m2], the
+// inverse transform on the output grid and its real part, restricted to o0 x o1 x o2 samples.
+// One launch for what took a fold, three passes of plain transforms, a real part and a crop
+// (six launches of 2 to 8 us each on grids of 512 to 4096 points).
+__global__ __launch_bounds__(256) void k3_out(const float2 *__restrict__ P, float *__restrict__ out, int n0,
+                                              int m0, int m1, int m2, int o0, int o1, int o2) {
+  extern __shared__ float2 lds[];
+  const int slab = m1 * m2, pts = m0 * slab, rs = m2 + 1;
+  const float2 *src = P + static_cast<size_t>(blockIdx.x) * n0 * slab;
+  // four points per thread at a time: their loads are in flight together
+  for (int e0 = threadIdx.x; e0 < pts; e0 += 4 * blockDim.x) {
+    float2 acc[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] = make_float2(0.f, 0.f);
+#pragma unroll 2
+    for (int a = 0; a < n0 / m0; ++a) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = e0 + u * blockDim.x;
+        const float2 w = src[static_cast<size_t>(a) * pts + (e < pts ? e : 0)];
+        acc[u].x += w.x;
+        acc[u].y += w.y;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int e = e0 + u * blockDim.x;
+      if (e < pts) lds[(e / m2) * rs + e % m2] = acc[u];
+    }
+  }
+  __syncthreads();
+  cube_fft<true>(lds, m0, m1, m2);
+  float *dst = out + static_cast<size_t>(blockIdx.x) * o0 * o1 * o2;
+  for (int e = threadIdx.x; e < o0 * o1 * o2; e += blockDim.x) {
+    const int c = e % o2, ab = e / o2;
+    dst[e] = lds[((ab / o1) * m1 + ab % o1) * rs + c].x;
+  }
+}
+
+// The adjoint's first step: Gs [m0][m1][m2] = forward transform of the output gradient of one
+// (volume, channel), given on o0 x o1 x o2 samples and zero elsewhere.
+__global__ __launch_bounds__(256) void k3_out_adj(const float *__restrict__ gout, float2 *__restrict__ Gs, int m0,
+                                                  int m1, int m2, int o0, int o1, int o2) {
+  extern __shared__ float2 lds[];
+  const int pts = m0 * m1 * m2, rs = m2 + 1;
+  const float *src = gout + static_cast<size_t>(blockIdx.x) * o0 * o1 * o2;
+  for (int e = threadIdx.x; e < pts; e += blockDim.x) {
+    const int c = e % m2, ab = e / m2, a = ab / m1, b = ab % m1;
+    const bool in = a < o0 && b < o1 && c < o2;
+    lds[ab * rs + c] = make_float2(in ? src[(a * o1 + b) * o2 + c] : 0.f, 0.f);
+  }
+  __syncthreads();
+  cube_fft<false>(lds, m0, m1, m2);
+  float2 *dst = Gs + static_cast<size_t>(blockIdx.x) * pts;
+  for (int e = threadIdx.x; e < pts; e += blockDim.x) dst[e] = lds[(e / m2) * rs + e % m2];
 }
 
 // Q[g][a0][e] = sum_p P[g][a0 + m0 p][e]: g over volumes x channels, e over the m1*m2
@@ -499,37 +712,56 @@ __global__ __launch_bounds__(256) void k3_real_part(const float2 *__restrict__ s
     out[i] = src[i].x;
 }
 
+// Slab transforms of every node of the list.  SPLIT (one filter per workgroup instead of a loop
+// over the node's filters) always for the 1024-thread slabs (no registers for the loop state),
+// else below 700 workgroups, where the loop's serial chain of transforms is the launch's time: a
+// whole forward call with the loop / split takes 104 / 98 us for one volume of 64^3 (512
+// workgroups), 131 / 132 us for two (1024), 200 / 220 us for four and 690 / 777 us for sixteen.
 template <int N1, int N2>
-hipError_t slab_mul_inv_t(const float2 *Fh, const float2 *tab, float2 *W, long volumes, int n0, int M,
-                          const float2 *tw, int tw_n, hipStream_t st) {
+hipError_t slab_mul_inv_t(const Nodes3 &nodes, long volumes, int n0, const float2 *tw, int tw_n,
+                          hipStream_t st) {
   using S = Slab<N1, N2>;
   const long slabs = volumes * n0;
   const long blocks = (slabs + S::SPW - 1) / S::SPW;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  const std::string name = "k3_slab_mul_inv<" + std::to_string(N1) + ", " + std::to_string(N2) +
-                           (S::NT == 1024 ? ", true>" : ", false>");
-  const double pts = static_cast<double>(slabs) * N1 * N2;
-  LaunchScope obs(name.c_str(), pts * 8.0 * (1 + M) + 8.0 * M * n0 * N1 * N2,
-                  pts * M * (5.0 * (ilog2h(N1) + ilog2h(N2)) + 6.0), st);
-  constexpr bool SPLIT = S::NT == 1024;  // (measured: slower for the smaller slabs)
-  if (SPLIT && M > 65535) return hipErrorInvalidValue;
-  if (S::lds_bytes > 65536) {
-    static unsigned long long lds_ok = 0;
-    hipError_t e =
-        allow_large_lds(reinterpret_cast<const void *>(k3_slab_mul_inv<N1, N2, SPLIT>), lds_ok);
-    if (e != hipSuccess) return e;
+  int most = 0, all = 0;
+  for (int i = 0; i < nodes.n; ++i) {
+    most = nodes.v[i].M > most ? nodes.v[i].M : most;
+    all += nodes.v[i].M;
   }
-  hipLaunchKernelGGL((k3_slab_mul_inv<N1, N2, SPLIT>),
-                     dim3(static_cast<unsigned>(blocks), SPLIT ? M : 1), dim3(S::NT),
-                     S::lds_bytes, st, Fh, tab, W, slabs, n0, M,
-                     static_cast<size_t>(slabs) * N1 * N2, tw, tw_n);
+  const bool split = S::NT == 1024 || blocks * nodes.n < 700;
+  const std::string name = "k3_slab_mul_inv<" + std::to_string(N1) + ", " + std::to_string(N2) +
+                           (split ? ", true>" : ", false>");
+  const double pts = static_cast<double>(slabs) * N1 * N2;
+  LaunchScope obs(name.c_str(), pts * 8.0 * (nodes.n + all) + 8.0 * all * n0 * N1 * N2,
+                  pts * all * (5.0 * (ilog2h(N1) + ilog2h(N2)) + 6.0), st);
+  const size_t mstride = static_cast<size_t>(slabs) * N1 * N2;
+  if (split) {
+    if (most > 65535) return hipErrorInvalidValue;
+    if (S::lds_bytes > 65536) {
+      static unsigned long long lds_ok = 0;
+      hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k3_slab_mul_inv<N1, N2, true>), lds_ok);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k3_slab_mul_inv<N1, N2, true>), dim3(static_cast<unsigned>(blocks), nodes.n, most),
+                       dim3(S::NT), S::lds_bytes, st, nodes, slabs, n0, mstride, tw, tw_n);
+    return hipGetLastError();
+  }
+  if constexpr (S::NT != 1024) {
+    if (S::lds_bytes > 65536) {
+      static unsigned long long lds_ok = 0;
+      hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k3_slab_mul_inv<N1, N2, false>), lds_ok);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k3_slab_mul_inv<N1, N2, false>), dim3(static_cast<unsigned>(blocks), nodes.n),
+                       dim3(S::NT), S::lds_bytes, st, nodes, slabs, n0, mstride, tw, tw_n);
+  }
   return hipGetLastError();
 }
 
 template <int N1, int N2>
-hipError_t slab_fwd_low_t(const float2 *Tin, float2 *Uout, const float *phi, float2 *P,
-                          long volumes, int n0, int J, int K, int chan, const float2 *tw, int tw_n,
-                          hipStream_t st) {
+hipError_t slab_fwd_low_t(const Nodes3 &nodes, const float *phi, float2 *P, long volumes, int n0, int J,
+                          int K, const float2 *tw, int tw_n, hipStream_t st) {
   using S = Slab<N1, N2>;
   const long slabs = volumes * (n0 / 2 + 1);
   const long blocks = (slabs + S::SPW - 1) / S::SPW;
@@ -539,23 +771,24 @@ hipError_t slab_fwd_low_t(const float2 *Tin, float2 *Uout, const float *phi, flo
       "k3_slab_fwd_low<" + std::to_string(N1) + ", " + std::to_string(N2) + ">";
   const double pts = static_cast<double>(slabs) * N1 * N2;
   const double full = static_cast<double>(volumes) * n0 * N1 * N2;
+  int stored = 0;
+  for (int i = 0; i < nodes.n; ++i) stored += nodes.v[i].U != nullptr;
   LaunchScope obs(name.c_str(),
-                  pts * 8.0 + (Uout ? full * 8.0 : 0.0) + 4.0 * (n0 / 2 + 1) * N1 * N2 +
-                      8.0 * volumes * folded,
-                  pts * (5.0 * (ilog2h(N1) + ilog2h(N2)) + 4.0), st);
+                  nodes.n * pts * 8.0 + stored * full * 8.0 +
+                      (phi ? 4.0 * (n0 / 2 + 1) * N1 * N2 + nodes.n * 8.0 * volumes * folded : 0.0),
+                  nodes.n * pts * (5.0 * (ilog2h(N1) + ilog2h(N2)) + (phi ? 4.0 : 0.0)), st);
   if (S::lds_bytes > 65536) {
     static unsigned long long lds_ok = 0;
     hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k3_slab_fwd_low<N1, N2>), lds_ok);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k3_slab_fwd_low<N1, N2>), dim3(static_cast<unsigned>(blocks)), dim3(S::NT),
-                     S::lds_bytes, st, Tin, Uout, phi, P, slabs, n0, J, folded * K, folded * chan,
-                     tw, tw_n);
+  hipLaunchKernelGGL((k3_slab_fwd_low<N1, N2>), dim3(static_cast<unsigned>(blocks), nodes.n), dim3(S::NT),
+                     S::lds_bytes, st, nodes, phi, P, slabs, n0, J, folded * K, folded, tw, tw_n);
   return hipGetLastError();
 }
 
 template <int E, int T>
-hipError_t axis0_t(const float2 *W, const float *xreal, float2 *dst, long volumes, int Mc, int M,
+hipError_t axis0_t(const Nodes3 &nodes, const float *xreal, const int *user, long volumes, int n2, int Mc,
                    const float2 *tw, int tw_n, hipStream_t st) {
   int TC = 256 / T;
   if (TC > Mc) TC = Mc;
@@ -565,17 +798,19 @@ hipError_t axis0_t(const float2 *W, const float *xreal, float2 *dst, long volume
       T == 1 ? 0 : static_cast<size_t>(E) * (T * TC + (E == 32 ? 0 : 1)) * sizeof(float2);
   const std::string name = "k3_axis0_rho<" + std::to_string(E) + ", " + std::to_string(T) + ">";
   const double pts = static_cast<double>(volumes) * E * T * Mc;
-  const int passes = xreal ? 1 : M + 1;
-  LaunchScope obs(name.c_str(), pts * (xreal ? 4.0 : 8.0 * M) + pts * 8.0 * (E * T / 2 + 1) / (E * T),
-                  pts * (passes * 5.0 * ilog2h(E * T) + (xreal ? 0.0 : 4.0 * M)), st);
-  hipLaunchKernelGGL((k3_axis0_rho<E, T>), dim3(static_cast<unsigned>(blocks)), dim3(T * TC), lds, st,
-                     W, xreal, dst, Mc, TC, M, static_cast<size_t>(volumes) * E * T * Mc, tw, tw_n);
+  int all = 0;
+  for (int i = 0; i < nodes.n; ++i) all += nodes.v[i].M;
+  LaunchScope obs(name.c_str(),
+                  pts * (xreal ? 4.0 : 8.0 * all) + nodes.n * pts * 8.0 * (E * T / 2 + 1) / (E * T),
+                  pts * ((xreal ? 1 : all + nodes.n) * 5.0 * ilog2h(E * T) + (xreal ? 0.0 : 4.0 * all)), st);
+  hipLaunchKernelGGL((k3_axis0_rho<E, T>), dim3(static_cast<unsigned>(blocks), nodes.n), dim3(T * TC), lds, st,
+                     nodes, xreal, user ? user[0] : 0, user ? user[1] : 0, user ? user[2] : 0, n2, Mc, TC,
+                     static_cast<size_t>(volumes) * E * T * Mc, tw, tw_n);
   return hipGetLastError();
 }
 
 template <int E, int T>
-hipError_t axis0_back_t(int mode, float2 *W, float *acc, const float2 *gu, long volumes, int Mc, int P,
-                        const float2 *tw, int tw_n, hipStream_t st) {
+hipError_t axis0_back_t(const Nodes3 &nodes, long volumes, int Mc, const float2 *tw, int tw_n, hipStream_t st) {
   int TC = 256 / T;
   if (TC > Mc) TC = Mc;
   const long blocks = volumes * (Mc / TC);
@@ -583,24 +818,37 @@ hipError_t axis0_back_t(int mode, float2 *W, float *acc, const float2 *gu, long 
   // exchange area of the transforms, then their twiddle table
   const size_t lds =
       T == 1 ? 0 : (static_cast<size_t>(E) * (T * TC + (E == 32 ? 0 : 1)) + E * T) * sizeof(float2);
-  const std::string name = "k3_axis0_back<" + std::to_string(E) + ", " + std::to_string(T) + ", " +
-                           (mode ? "1>" : "0>");
+  const std::string name = "k3_axis0_back<" + std::to_string(E) + ", " + std::to_string(T) + ">";
   const double pts = static_cast<double>(volumes) * E * T * Mc;
-  LaunchScope obs(name.c_str(), pts * (16.0 * P + (mode ? 12.0 : 4.0)),
-                  pts * P * (5.0 * ilog2h(E * T) + 4.0), st);
-  const size_t mstride = static_cast<size_t>(volumes) * E * T * Mc;
-  if (mode == 0)
-    hipLaunchKernelGGL((k3_axis0_back<E, T, 0>), dim3(static_cast<unsigned>(blocks)), dim3(T * TC), lds,
-                       st, W, acc, gu, Mc, TC, P, mstride, tw, tw_n);
-  else
-    hipLaunchKernelGGL((k3_axis0_back<E, T, 1>), dim3(static_cast<unsigned>(blocks)), dim3(T * TC), lds,
-                       st, W, acc, gu, Mc, TC, P, mstride, tw, tw_n);
+  int all = 0;
+  for (int i = 0; i < nodes.n; ++i) all += nodes.v[i].M;
+  LaunchScope obs(name.c_str(), pts * (16.0 * all + 8.0 * nodes.n),
+                  pts * ((2 * all + nodes.n) * 5.0 * ilog2h(E * T) + 6.0 * all), st);
+  hipLaunchKernelGGL((k3_axis0_back<E, T>), dim3(static_cast<unsigned>(blocks), nodes.n), dim3(T * TC), lds, st,
+                     nodes, Mc, TC, static_cast<size_t>(volumes) * E * T * Mc, tw, tw_n);
+  return hipGetLastError();
+}
+
+template <int E, int T>
+hipError_t axis0_real_t(const float2 *src, float *out, long volumes, int Mc, const float2 *tw, int tw_n,
+                        hipStream_t st) {
+  int TC = 256 / T;
+  if (TC > Mc) TC = Mc;
+  const long blocks = volumes * (Mc / TC);
+  if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  const size_t lds =
+      T == 1 ? 0 : static_cast<size_t>(E) * (T * TC + (E == 32 ? 0 : 1)) * sizeof(float2);
+  const std::string name = "k3_axis0_real<" + std::to_string(E) + ", " + std::to_string(T) + ">";
+  const double pts = static_cast<double>(volumes) * E * T * Mc;
+  LaunchScope obs(name.c_str(), pts * 12.0, pts * 5.0 * ilog2h(E * T), st);
+  hipLaunchKernelGGL((k3_axis0_real<E, T>), dim3(static_cast<unsigned>(blocks)), dim3(T * TC), lds, st, src, out,
+                     Mc, TC, tw, tw_n);
   return hipGetLastError();
 }
 
 template <int N1, int N2>
-hipError_t slab_fwd_mulacc_t(const float2 *W, const float2 *tab, float2 *A, long volumes, int n0, int P,
-                             const float2 *tw, int tw_n, hipStream_t st) {
+hipError_t slab_fwd_mulacc_t(const Nodes3 &nodes, long volumes, int n0, const float2 *tw, int tw_n,
+                             hipStream_t st) {
   using S = Slab<N1, N2>;
   const long slabs = volumes * n0;
   const long blocks = (slabs + S::SPW - 1) / S::SPW;
@@ -608,8 +856,10 @@ hipError_t slab_fwd_mulacc_t(const float2 *W, const float2 *tab, float2 *A, long
   const std::string name =
       "k3_slab_fwd_mulacc<" + std::to_string(N1) + ", " + std::to_string(N2) + ">";
   const double pts = static_cast<double>(slabs) * N1 * N2;
-  LaunchScope obs(name.c_str(), pts * 8.0 * (P + 2) + 8.0 * P * n0 * N1 * N2,
-                  pts * P * (5.0 * (ilog2h(N1) + ilog2h(N2)) + 8.0), st);
+  int all = 0;
+  for (int i = 0; i < nodes.n; ++i) all += nodes.v[i].M;
+  LaunchScope obs(name.c_str(), pts * 8.0 * (all + nodes.n) + 8.0 * all * n0 * N1 * N2,
+                  pts * all * (5.0 * (ilog2h(N1) + ilog2h(N2)) + 8.0), st);
   const size_t lds = S::lds_bytes + S::tab_elems * sizeof(float2);
   if (lds > 65536) {
     static unsigned long long lds_ok = 0;
@@ -617,9 +867,33 @@ hipError_t slab_fwd_mulacc_t(const float2 *W, const float2 *tab, float2 *A, long
         allow_large_lds(reinterpret_cast<const void *>(k3_slab_fwd_mulacc<N1, N2>), lds_ok);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k3_slab_fwd_mulacc<N1, N2>), dim3(static_cast<unsigned>(blocks)), dim3(S::NT),
-                     lds, st, W, tab, A, slabs, n0, P, static_cast<size_t>(slabs) * N1 * N2,
-                     tw, tw_n);
+  hipLaunchKernelGGL((k3_slab_fwd_mulacc<N1, N2>), dim3(static_cast<unsigned>(blocks), nodes.n), dim3(S::NT),
+                     lds, st, nodes, slabs, n0, static_cast<size_t>(slabs) * N1 * N2, tw, tw_n);
+  return hipGetLastError();
+}
+
+template <int N1, int N2>
+hipError_t slab_sum_inv_t(const Sums3 &sums, const float *phi, const float2 *Gs, long volumes, int n0, int J,
+                          int K, const float2 *tw, int tw_n, hipStream_t st) {
+  using S = Slab<N1, N2>;
+  const long blocks = (volumes * n0 + S::SPW - 1) / S::SPW;
+  if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  const std::string name = "k3_slab_sum_inv<" + std::to_string(N1) + ", " + std::to_string(N2) + ">";
+  const double pts = static_cast<double>(volumes) * n0 * N1 * N2;
+  double moved = 0, done = 0;
+  for (int i = 0; i < sums.n; ++i) {
+    moved += sums.v[i].count == 0 ? 0.5 : 1.0 + sums.v[i].count;
+    done += sums.v[i].count == 0 ? 0.5 : 1.0;
+  }
+  LaunchScope obs(name.c_str(), pts * 8.0 * moved + 4.0 * n0 * N1 * N2,
+                  pts * done * (5.0 * (ilog2h(N1) + ilog2h(N2)) + 4.0), st);
+  if (S::lds_bytes > 65536) {
+    static unsigned long long lds_ok = 0;
+    hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k3_slab_sum_inv<N1, N2>), lds_ok);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k3_slab_sum_inv<N1, N2>), dim3(static_cast<unsigned>(blocks), sums.n), dim3(S::NT),
+                     S::lds_bytes, st, sums, phi, Gs, volumes, n0, J, K, tw, tw_n);
   return hipGetLastError();
 }
 
@@ -659,74 +933,134 @@ bool fused3_supported(int n0, int n1, int n2, int J) {
     default: return hipErrorInvalidValue;          \
   }
 
-hipError_t launch3_slab_mul_inv(const float2 *Fh, const float2 *tab, float2 *W, long volumes, int n0,
-                                int n1, int n2, int M, const float2 *tw, int tw_n, hipStream_t st) {
-  if (volumes <= 0 || M <= 0) return hipSuccess;
-  if (tw_n % n1 != 0 || tw_n % n2 != 0) return hipErrorInvalidValue;
-#define SCAT3_A(A_, B_) return slab_mul_inv_t<A_, B_>(Fh, tab, W, volumes, n0, M, tw, tw_n, st)
+hipError_t launch3_slab_mul_inv(const Nodes3 &nodes, long volumes, int n0, int n1, int n2, const float2 *tw,
+                                int tw_n, hipStream_t st) {
+  if (volumes <= 0 || nodes.n <= 0) return hipSuccess;
+  if (tw_n % n1 != 0 || tw_n % n2 != 0 || nodes.n > kMaxNodes3) return hipErrorInvalidValue;
+#define SCAT3_A(A_, B_) return slab_mul_inv_t<A_, B_>(nodes, volumes, n0, tw, tw_n, st)
   SCAT3_SLAB_DISPATCH(SCAT3_A)
 #undef SCAT3_A
 }
 
-hipError_t launch3_slab_fwd_low(const float2 *Tin, float2 *Uout, const float *phi, float2 *P,
-                                long volumes, int n0, int n1, int n2, int J, int K, int chan,
-                                const float2 *tw, int tw_n, hipStream_t st) {
-  if (volumes <= 0) return hipSuccess;
-  if (tw_n % n1 != 0 || tw_n % n2 != 0 || J < 0 || J > 4 || (n1 >> J) < 1 || (n2 >> J) < 1)
+hipError_t launch3_slab_fwd_low(const Nodes3 &nodes, const float *phi, float2 *P, long volumes, int n0, int n1,
+                                int n2, int J, int K, const float2 *tw, int tw_n, hipStream_t st) {
+  if (volumes <= 0 || nodes.n <= 0) return hipSuccess;
+  if (tw_n % n1 != 0 || tw_n % n2 != 0 || J < 0 || J > 4 || (n1 >> J) < 1 || (n2 >> J) < 1 ||
+      nodes.n > kMaxNodes3)
     return hipErrorInvalidValue;
-#define SCAT3_C(A_, B_) \
-  return slab_fwd_low_t<A_, B_>(Tin, Uout, phi, P, volumes, n0, J, K, chan, tw, tw_n, st)
+#define SCAT3_C(A_, B_) return slab_fwd_low_t<A_, B_>(nodes, phi, P, volumes, n0, J, K, tw, tw_n, st)
   SCAT3_SLAB_DISPATCH(SCAT3_C)
 #undef SCAT3_C
 }
 
-hipError_t launch3_axis0_rho(const float2 *W, const float *xreal, float2 *dst, long volumes, int n0,
-                             int Mc, int M, const float2 *tw, int tw_n, hipStream_t st) {
-  if (volumes <= 0) return hipSuccess;
-  if (tw_n % n0 != 0 || Mc < 256 || (Mc & (Mc - 1)) != 0 || (xreal == nullptr && M <= 0))
-    return hipErrorInvalidValue;
-#define SCAT3_B(E_, T_) return axis0_t<E_, T_>(W, xreal, dst, volumes, Mc, M, tw, tw_n, st)
-  switch (n0) {
-    case 4: SCAT3_B(4, 1);
-    case 8: SCAT3_B(8, 1);
-    case 16: SCAT3_B(16, 1);
-    case 32: SCAT3_B(16, 2);
-    case 64: SCAT3_B(16, 4);
-    case 128: SCAT3_B(16, 8);
-    case 256: SCAT3_B(16, 16);
-    default: return hipErrorInvalidValue;
+#define SCAT3_AXIS0_DISPATCH(CALL)        \
+  switch (n0) {                           \
+    case 4: CALL(4, 1);                   \
+    case 8: CALL(8, 1);                   \
+    case 16: CALL(16, 1);                 \
+    case 32: CALL(16, 2);                 \
+    case 64: CALL(16, 4);                 \
+    case 128: CALL(16, 8);                \
+    case 256: CALL(16, 16);               \
+    default: return hipErrorInvalidValue; \
   }
+
+hipError_t launch3_axis0_rho(const Nodes3 &nodes, const float *xreal, const int *user, long volumes, int n0,
+                             int n2, int Mc, const float2 *tw, int tw_n, hipStream_t st) {
+  if (volumes <= 0 || nodes.n <= 0) return hipSuccess;
+  if (tw_n % n0 != 0 || Mc < 256 || (Mc & (Mc - 1)) != 0 || nodes.n > kMaxNodes3 ||
+      (xreal != nullptr && nodes.n != 1))
+    return hipErrorInvalidValue;
+  for (int i = 0; xreal == nullptr && i < nodes.n; ++i)
+    if (nodes.v[i].M <= 0) return hipErrorInvalidValue;
+#define SCAT3_B(E_, T_) return axis0_t<E_, T_>(nodes, xreal, user, volumes, n2, Mc, tw, tw_n, st)
+  SCAT3_AXIS0_DISPATCH(SCAT3_B)
 #undef SCAT3_B
 }
 
-hipError_t launch3_axis0_back(int mode, float2 *W, float *acc, const float2 *gu, long volumes, int n0,
-                              int Mc, int P, const float2 *tw, int tw_n, hipStream_t st) {
-  if (volumes <= 0 || P <= 0) return hipSuccess;
-  if (tw_n % n0 != 0 || Mc < 256 || (Mc & (Mc - 1)) != 0 || acc == nullptr ||
-      (mode != 0 && gu == nullptr))
-    return hipErrorInvalidValue;
-#define SCAT3_AB(E_, T_) return axis0_back_t<E_, T_>(mode, W, acc, gu, volumes, Mc, P, tw, tw_n, st)
-  switch (n0) {
-    case 4: SCAT3_AB(4, 1);
-    case 8: SCAT3_AB(8, 1);
-    case 16: SCAT3_AB(16, 1);
-    case 32: SCAT3_AB(16, 2);
-    case 64: SCAT3_AB(16, 4);
-    case 128: SCAT3_AB(16, 8);
-    case 256: SCAT3_AB(16, 16);
-    default: return hipErrorInvalidValue;
-  }
+hipError_t launch3_axis0_back(const Nodes3 &nodes, long volumes, int n0, int Mc, const float2 *tw, int tw_n,
+                              hipStream_t st) {
+  if (volumes <= 0 || nodes.n <= 0) return hipSuccess;
+  if (tw_n % n0 != 0 || Mc < 256 || (Mc & (Mc - 1)) != 0 || nodes.n > kMaxNodes3) return hipErrorInvalidValue;
+  for (int i = 0; i < nodes.n; ++i)
+    if (nodes.v[i].M <= 0 || nodes.v[i].T == nullptr) return hipErrorInvalidValue;
+#define SCAT3_AB(E_, T_) return axis0_back_t<E_, T_>(nodes, volumes, Mc, tw, tw_n, st)
+  SCAT3_AXIS0_DISPATCH(SCAT3_AB)
 #undef SCAT3_AB
 }
 
-hipError_t launch3_slab_fwd_mulacc(const float2 *W, const float2 *tab, float2 *A, long volumes, int n0,
-                                   int n1, int n2, int P, const float2 *tw, int tw_n,
-                                   hipStream_t st) {
-  if (volumes <= 0 || P <= 0) return hipSuccess;
-  if (tw_n % n1 != 0 || tw_n % n2 != 0) return hipErrorInvalidValue;
-#define SCAT3_D(A_, B_) return slab_fwd_mulacc_t<A_, B_>(W, tab, A, volumes, n0, P, tw, tw_n, st)
+hipError_t launch3_axis0_real(const float2 *src, float *out, long volumes, int n0, int Mc, const float2 *tw,
+                              int tw_n, hipStream_t st) {
+  if (volumes <= 0) return hipSuccess;
+  if (tw_n % n0 != 0 || Mc < 256 || (Mc & (Mc - 1)) != 0) return hipErrorInvalidValue;
+#define SCAT3_AR(E_, T_) return axis0_real_t<E_, T_>(src, out, volumes, Mc, tw, tw_n, st)
+  SCAT3_AXIS0_DISPATCH(SCAT3_AR)
+#undef SCAT3_AR
+}
+
+hipError_t launch3_slab_fwd_mulacc(const Nodes3 &nodes, long volumes, int n0, int n1, int n2, const float2 *tw,
+                                   int tw_n, hipStream_t st) {
+  if (volumes <= 0 || nodes.n <= 0) return hipSuccess;
+  if (tw_n % n1 != 0 || tw_n % n2 != 0 || nodes.n > kMaxNodes3) return hipErrorInvalidValue;
+#define SCAT3_D(A_, B_) return slab_fwd_mulacc_t<A_, B_>(nodes, volumes, n0, tw, tw_n, st)
   SCAT3_SLAB_DISPATCH(SCAT3_D)
 #undef SCAT3_D
+}
+
+hipError_t launch3_slab_sum_inv(const Sums3 &sums, const float *phi, const float2 *Gs, long volumes, int n0,
+                                int n1, int n2, int J, int K, const float2 *tw, int tw_n, hipStream_t st) {
+  if (volumes <= 0 || sums.n <= 0) return hipSuccess;
+  if (tw_n % n1 != 0 || tw_n % n2 != 0 || J < 0 || (n0 >> J) < 1 || (n1 >> J) < 1 || (n2 >> J) < 1 ||
+      sums.n > kMaxNodes3)
+    return hipErrorInvalidValue;
+  for (int i = 0; i < sums.n; ++i)
+    if (sums.v[i].first < 0 || sums.v[i].count < 0 || sums.v[i].first + sums.v[i].count > kMaxSpectra3)
+      return hipErrorInvalidValue;
+#define SCAT3_S(A_, B_) return slab_sum_inv_t<A_, B_>(sums, phi, Gs, volumes, n0, J, K, tw, tw_n, st)
+  SCAT3_SLAB_DISPATCH(SCAT3_S)
+#undef SCAT3_S
+}
+
+hipError_t launch3_sum_spectra(const Sums3 &sums, float2 *dst, long total, hipStream_t st) {
+  if (total <= 0) return hipSuccess;
+  if (sums.n != 1 || sums.v[0].first < 0 || sums.v[0].count < 1 ||
+      sums.v[0].first + sums.v[0].count > kMaxSpectra3)
+    return hipErrorInvalidValue;
+  LaunchScope obs("k3_sum_spectra", total * 8.0 * (1 + sums.v[0].count), total * 2.0 * sums.v[0].count, st);
+  hipLaunchKernelGGL(k3_sum_spectra, dim3(blocks_for(total)), dim3(256), 0, st, sums, dst, total);
+  return hipGetLastError();
+}
+
+bool out3_supported(int m0, int m1, int m2) {
+  return m0 <= 32 && m1 <= 32 && m2 <= 32 && m0 * m1 * m2 <= kOutPoints;
+}
+
+hipError_t launch3_out(const float2 *P, float *out, long maps, int n0, int m0, int m1, int m2, const int *o,
+                       hipStream_t st) {
+  if (maps <= 0) return hipSuccess;
+  if (!out3_supported(m0, m1, m2) || n0 % m0 != 0 || o[0] > m0 || o[1] > m1 || o[2] > m2 || maps > 0x7fffffffL)
+    return hipErrorInvalidValue;
+  const double pts = static_cast<double>(maps) * m0 * m1 * m2;
+  LaunchScope obs("k3_out", pts * 8.0 * (n0 / m0) + 4.0 * maps * o[0] * o[1] * o[2],
+                  pts * 5.0 * (ilog2h(m0) + ilog2h(m1) + ilog2h(m2)), st);
+  hipLaunchKernelGGL(k3_out, dim3(static_cast<unsigned>(maps)), dim3(256),
+                     static_cast<size_t>(m0) * m1 * (m2 + 1) * sizeof(float2), st, P, out, n0, m0, m1, m2, o[0],
+                     o[1], o[2]);
+  return hipGetLastError();
+}
+
+hipError_t launch3_out_adj(const float *gout, float2 *Gs, long maps, int m0, int m1, int m2, const int *o,
+                           hipStream_t st) {
+  if (maps <= 0) return hipSuccess;
+  if (!out3_supported(m0, m1, m2) || o[0] > m0 || o[1] > m1 || o[2] > m2 || maps > 0x7fffffffL)
+    return hipErrorInvalidValue;
+  const double pts = static_cast<double>(maps) * m0 * m1 * m2;
+  LaunchScope obs("k3_out_adj", pts * 8.0 + 4.0 * maps * o[0] * o[1] * o[2],
+                  pts * 5.0 * (ilog2h(m0) + ilog2h(m1) + ilog2h(m2)), st);
+  hipLaunchKernelGGL(k3_out_adj, dim3(static_cast<unsigned>(maps)), dim3(256),
+                     static_cast<size_t>(m0) * m1 * (m2 + 1) * sizeof(float2), st, gout, Gs, m0, m1, m2, o[0],
+                     o[1], o[2]);
+  return hipGetLastError();
 }
 
 hipError_t launch3_fold0(const float2 *P, float2 *Q, long groups, int n0, int m0, int slab,
@@ -762,13 +1096,11 @@ hipError_t launch3_real_to_complex(const float *x, float2 *out, long total, hipS
 }
 
 hipError_t launch3_mul_table(const float2 *src, const float *filt, float2 *dst, long volumes, long n,
-                             hipStream_t st, int fstride, bool accumulate) {
+                             hipStream_t st, bool accumulate) {
   const long total = volumes * n;
   if (total <= 0) return hipSuccess;
-  if (fstride < 1) return hipErrorInvalidValue;
   LaunchScope obs("k3_mul_table", total * (accumulate ? 24.0 : 16.0) + n * 4.0, total * 2.0, st);
-  hipLaunchKernelGGL(k3_mul_table, dim3(blocks_for(total)), dim3(256), 0, st, src, filt, fstride, dst,
-                     total, n, accumulate ? 1 : 0);
+  hipLaunchKernelGGL(k3_mul_table, dim3(blocks_for(total)), dim3(256), 0, st, src, filt, dst, total, n, accumulate ? 1 : 0);
   return hipGetLastError();
 }
 
@@ -780,16 +1112,6 @@ hipError_t launch3_tile_phi(const float2 *Gs, const float *phi, float2 *dst, lon
                   st);
   hipLaunchKernelGGL(k3_tile_phi, dim3(blocks_for(total)), dim3(256), 0, st, Gs, phi, dst, volumes, K,
                      chan, n0, n1, n2, J, accumulate ? 1 : 0);
-  return hipGetLastError();
-}
-
-hipError_t launch3_mul_ctable(const float2 *src, const float2 *ctab, float2 *dst, long volumes, long n,
-                              bool conj_table, bool accumulate, hipStream_t st) {
-  const long total = volumes * n;
-  if (total <= 0) return hipSuccess;
-  LaunchScope obs("k3_mul_ctable", total * (accumulate ? 24.0 : 16.0) + n * 8.0, total * 6.0, st);
-  hipLaunchKernelGGL(k3_mul_ctable, dim3(blocks_for(total)), dim3(256), 0, st, src, ctab, dst, total, n,
-                     conj_table ? 1 : 0, accumulate ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -210,7 +210,13 @@ struct Layout {
   size_t pad_in = 0, pad_out = 0;             // padded plans: extended input, uncropped output
 };
 
-size_t bytes_per_volume_3d(const scat_plan &p);
+struct Layout3 {
+  long chunk = 0;
+  size_t core = 0, area = 0;  // bytes of a chunk without the padded plan's arrays; of the nodes in flight
+  size_t pad_in = 0, pad_out = 0;  // bytes per volume of those arrays (0 where not needed)
+  size_t total() const { return core + (pad_in + pad_out) * static_cast<size_t>(chunk); }
+};
+Layout3 layout_3d(const scat_plan &p, long batch, size_t budget, bool backward);
 
 // 1-D: elements per signal of the row-pass output buffer T.  It first holds one octave's Q
 // first-order signals (consumed by the column pass) and then, at once, that octave's
@@ -240,20 +246,6 @@ Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
   Layout L;
   if (budget == 0) budget = scratch_budget();
   const scat::HostPlan &h = p.host;
-  if (h.dims == 3) {
-    L.per_plane = bytes_per_volume_3d(p);
-    if (p.padded) {
-      // extended input and uncropped output behind the transform's buffers
-      L.pad_in = p.h3.points() * sizeof(float);
-      L.pad_out = static_cast<size_t>(h.K) * (p.h3.points() >> (3 * p.h3.out_shift())) * sizeof(float);
-      L.xh = L.per_plane;  // offset of those two per volume
-      L.per_plane += L.pad_in + L.pad_out;
-    }
-    long c = static_cast<long>(budget / L.per_plane);
-    if (c < 1) c = 1;
-    L.chunk = c > batch ? batch : c;
-    return L;
-  }
   const size_t n = static_cast<size_t>(p.n1) * p.n2;
   const bool second = h.max_order == 2 && h.J >= 2;
   const size_t c8 = sizeof(float2);
@@ -1907,68 +1899,329 @@ scat_status upload_3d(scat_plan *p) {
   return note_static_scratch(p);
 }
 
-// scratch per volume.  General path: X^, U^ (and V^ at order 2), work buffer, all complex;
-// |.|^2 sums, real.  Fused path: X^, U^, the axis-0 stage T, the 2L+1 filtered signals W_m,
-// the slab-folded lowpass spectra P of all K channels and their fully folded form Q.
-size_t bytes_per_volume_3d(const scat_plan &p) {
+// ---- Scratch of the fused 3-D passes, in complex elements per volume: what a call keeps from
+// beginning to end (fixed), and an area for the nodes in flight, which go through the passes in
+// batches: as many nodes at a time as the area holds.  `least` holds the largest node there is
+// (with, in the backward pass, all its children), `most` every node of a layer at once.
+struct Work3 {
+  size_t fixed = 0, least = 0, most = 0;
+};
+
+struct Sizes3 {
+  size_t n, half, folded12, mout;  // grid points, rows 0 .. n0/2 of it, slab-folded and folded lowpass
+  bool small_out;                  // one workgroup holds an output grid
+};
+
+Sizes3 sizes_3d(const scat_plan &p) {
   const scat::HostPlan3D &h = p.h3;
-  const size_t n = h.points();
-  if (!p.fused3)
-    return n * sizeof(float2) * (p.host.max_order == 2 && p.host.J >= 2 ? 4 : 3) + n * sizeof(float);
   const int Jo = h.out_shift();
-  const size_t folded12 = static_cast<size_t>(h.shape[0]) * (h.shape[1] >> Jo) * (h.shape[2] >> Jo);
-  return (n * (3 + h.L + 1) + static_cast<size_t>(h.K) * (folded12 + (n >> (3 * Jo)))) *
-         sizeof(float2);
+  Sizes3 s;
+  s.n = h.points();
+  s.half = static_cast<size_t>(h.shape[0] / 2 + 1) * h.shape[1] * h.shape[2];
+  s.folded12 = static_cast<size_t>(h.shape[0]) * (h.shape[1] >> Jo) * (h.shape[2] >> Jo);
+  s.mout = s.n >> (3 * Jo);
+  s.small_out = scat::out3_supported(h.shape[0] >> Jo, h.shape[1] >> Jo, h.shape[2] >> Jo);
+  return s;
 }
 
-scat_status forward_3d_fused(scat_plan *p, const float *in, float *out, long p0, long pc,
-                             hipStream_t st) {
+Work3 work_3d(const scat_plan &p, bool backward) {
+  const scat::HostPlan3D &h = p.h3;
+  const Sizes3 s = sizes_3d(p);
+  const bool second = h.max_order == 2 && h.J >= 2;
+  const size_t L = h.L, J = h.J, pairs = (L + 1) * (L + 2) / 2, K = h.K;
+  Work3 w;
+  if (!backward) {
+    w.fixed = s.n + K * (s.folded12 + (s.small_out ? 0 : s.mout));
+    const size_t node = (L + 1) * s.n + s.half;
+    const size_t layer = pairs * s.n + (L + 1) * s.half;  // one scale, all degrees
+    w.least = (second ? s.n : 0) + node;
+    w.most = second ? (J - 1) * (L + 1) * s.n + std::max(J, J * (J - 1) / 2) * layer : J * layer;
+  } else {
+    w.fixed = 2 * s.n + K * s.mout;
+    const size_t node = (L + 2) * s.n, child = (L + 1) * s.n + s.half;
+    w.least = node + (second ? s.n + (J - 1) * child : 0);
+    w.most = J * (pairs + L + 1) * s.n;
+    if (second) w.most += (J - 1) * (L + 1) * s.n + J * (J - 1) / 2 * (pairs * s.n + (L + 1) * s.half);
+  }
+  return w;
+}
+
+// Bytes for the nodes in flight of a chunk of `pc` volumes: all of a layer's where that is below
+// kArea3, else as many as that holds.  (Smaller areas, whose contents the last-level cache would
+// hold from one launch to the next, measured slower: 16 volumes of 64^3, forward, 766 us with
+// 64 to 192 MB, 720 us from 384 MB up; forward and backward 2.52 ms, 2.41 ms with 384 MB, 2.30 ms
+// with 1 GB.)  Never less than one node needs; never decreasing in pc (scat_plan_reserve).
+constexpr size_t kArea3 = size_t(1) << 30;
+size_t area_bytes_3d(const Work3 &w, long pc, size_t budget) {
+  const size_t c8 = sizeof(float2), n = static_cast<size_t>(pc);
+  const size_t least = w.least * n * c8, most = w.most * n * c8, fixed = w.fixed * n * c8;
+  const size_t room = budget > fixed ? std::min(kArea3, budget - fixed) : 0;
+  return std::min(most, std::max(least, room));
+}
+
+// Hands out the area of the nodes in flight, in complex elements.
+struct Arena3 {
+  float2 *base;
+  size_t size, used = 0;
+  bool full = false;  // more was asked for than there is: nothing may be launched
+  float2 *take(size_t count) {
+    float2 *r = base + used;
+    used += count;
+    full = full || used > size;
+    return r;
+  }
+};
+
+size_t bytes_per_volume_3d_bwd(const scat_plan &p);
+
+// How a call of `batch` volumes uses `budget` bytes of scratch (0: scratch_budget()).
+Layout3 layout_3d(const scat_plan &p, long batch, size_t budget, bool backward) {
+  const scat::HostPlan3D &h = p.h3;
+  const Sizes3 s = sizes_3d(p);
+  if (budget == 0) budget = scratch_budget();
+  Layout3 lay;
+  if (p.padded) {
+    // extended input (fused plans extend it while they read it), in the backward pass the
+    // gradient on the periodic grid, and the output (gradient) on the periodic output grid
+    // (fused plans with small output grids crop and extend it in place)
+    lay.pad_in = ((p.fused3 ? 0 : s.n) + (backward ? s.n : 0)) * sizeof(float);
+    lay.pad_out = p.fused3 && s.small_out ? 0 : h.K * s.mout * sizeof(float);
+  }
+  const size_t pads = lay.pad_in + lay.pad_out;
+  Work3 w;
+  size_t per;
+  if (p.fused3) {
+    w = work_3d(p, backward);
+    per = (w.fixed + w.least) * sizeof(float2);
+  } else {
+    per = backward ? bytes_per_volume_3d_bwd(p)
+                   : s.n * sizeof(float2) * (h.max_order == 2 && h.J >= 2 ? 4 : 3) + s.n * sizeof(float);
+  }
+  long c = static_cast<long>(budget / (per + pads));
+  if (c < 1) c = 1;
+  if (c > batch) c = batch;
+  lay.chunk = c;
+  if (!p.fused3) {
+    lay.core = per * static_cast<size_t>(c);
+    return lay;
+  }
+  const size_t padding = pads * static_cast<size_t>(c);
+  lay.area = area_bytes_3d(w, c, budget > padding ? budget - padding : 0);
+  lay.core = w.fixed * sizeof(float2) * static_cast<size_t>(c) + lay.area;
+  return lay;
+}
+
+// first-order node c (channel 1 + c) is scale c / (L+1), degree c % (L+1); its children's
+// channels follow those of the nodes before it
+int second_channel_3d(const scat::HostPlan3D &h, int j1, int l) {
+  int c = 1 + h.J * (h.L + 1);
+  for (int j = 0; j < j1; ++j) c += (h.L + 1) * (h.J - 1 - j);
+  return c + l * (h.J - 1 - j1);
+}
+
+// x: the chunk's first volume (the caller's volume of a padded plan: it is extended while it is
+// read); o: its first output volume (padded plans with a small output grid: cropped, else the
+// periodic grid's).
+scat_status forward_3d_fused(scat_plan *p, const float *x, float *o, long pc, size_t area, hipStream_t st) {
   const scat::HostPlan3D &h = p->h3;
   const int n0 = h.shape[0], n1 = h.shape[1], n2 = h.shape[2];
   const int J = h.J, L = h.L, K = h.K;
   const int Jo = h.out_shift();  // the outputs are read at the samples 2^Jo n
-  const size_t n = h.points();
-  const size_t tot = static_cast<size_t>(pc) * n;
+  const Sizes3 sz = sizes_3d(*p);
+  const size_t tot = static_cast<size_t>(pc) * sz.n, half = static_cast<size_t>(pc) * sz.half;
   const bool second = h.max_order == 2 && J >= 2;
   const int m0 = n0 >> Jo, m1 = n1 >> Jo, m2 = n2 >> Jo;
   float2 *XH = static_cast<float2 *>(p->work);
-  float2 *UH = XH + tot;
-  float2 *T = UH + tot;
-  float2 *W = T + tot;
-  float2 *P = W + tot * (L + 1);
-  float2 *Q = P + static_cast<size_t>(pc) * K * n0 * m1 * m2;
+  float2 *P = XH + tot;
+  float2 *Q = P + static_cast<size_t>(pc) * K * sz.folded12;
+  Arena3 arena{Q + (sz.small_out ? 0 : static_cast<size_t>(pc) * K * sz.mout), area / sizeof(float2)};
   const float *tab = p->d_tables;
   const float2 *tw = p->d_tw;
   const int tw_n = p->tw_n;
-  const float *x = in + static_cast<size_t>(p0) * n;
-  const size_t mout = static_cast<size_t>(m0) * m1 * m2;
-  float *o = out + static_cast<size_t>(p0) * K * mout;
   const float *phi = tab + p->phi3_off;
-  // dst^ (may be null) and channel c from the real signal with spectrum Fh; its 2l+1
-  // filtered versions travel as l+1 complex signals
-  auto node = [&](const float2 *Fh, int j, int l, float2 *dst, int c) -> hipError_t {
-    const float2 *ps = reinterpret_cast<const float2 *>(
-        tab + p->psi3_off[static_cast<size_t>(j) * (L + 1) + l]);
-    hipError_t e = scat::launch3_slab_mul_inv(Fh, ps, W, pc, n0, n1, n2, l + 1, tw, tw_n, st);
-    if (e != hipSuccess) return e;
-    e = scat::launch3_axis0_rho(W, nullptr, T, pc, n0, n1 * n2, l + 1, tw, tw_n, st);
-    if (e != hipSuccess) return e;
-    return scat::launch3_slab_fwd_low(T, dst, phi, P, pc, n0, n1, n2, Jo, K, c, tw, tw_n, st);
+  auto pairs = [&](int j, int l) {
+    return reinterpret_cast<const float2 *>(tab + p->psi3_off[static_cast<size_t>(j) * (L + 1) + l]);
   };
-  SCAT_TRY(scat::launch3_axis0_rho(nullptr, x, T, pc, n0, n1 * n2, 0, tw, tw_n, st));
-  SCAT_TRY(scat::launch3_slab_fwd_low(T, XH, phi, P, pc, n0, n1, n2, Jo, K, 0, tw, tw_n, st));
-  int c1 = 1, c2 = 1 + J * (L + 1);
-  for (int j1 = 0; j1 < J; ++j1)
-    for (int l = 0; l <= L; ++l) {
-      const bool kids = second && j1 < J - 1;
-      SCAT_TRY(node(XH, j1, l, kids ? UH : nullptr, c1++));
-      if (!kids) continue;
-      for (int j2 = j1 + 1; j2 < J; ++j2) SCAT_TRY(node(UH, j2, l, nullptr, c2++));
+  auto passes = [&](scat::Nodes3 &nd) -> hipError_t {
+    hipError_t e = scat::launch3_slab_mul_inv(nd, pc, n0, n1, n2, tw, tw_n, st);
+    if (e != hipSuccess) return e;
+    e = scat::launch3_axis0_rho(nd, nullptr, nullptr, pc, n0, n2, n1 * n2, tw, tw_n, st);
+    if (e != hipSuccess) return e;
+    return scat::launch3_slab_fwd_low(nd, phi, P, pc, n0, n1, n2, Jo, K, tw, tw_n, st);
+  };
+  scat::Nodes3 nd{};
+  {
+    nd.n = 1;
+    nd.v[0] = scat::Node3{nullptr, nullptr, nullptr, arena.base, XH, 0, 0, 0};
+    SCAT_TRY(scat::launch3_axis0_rho(nd, x, p->padded ? p->user_shape3 : nullptr, pc, n0, n2, n1 * n2, tw, tw_n,
+                                     st));
+    SCAT_TRY(scat::launch3_slab_fwd_low(nd, phi, P, pc, n0, n1, n2, Jo, K, tw, tw_n, st));
+  }
+  // signals and axis-0 spectrum of a node of degree l
+  auto cost = [&](int l) { return static_cast<size_t>(l + 1) * tot + half; };
+  const int first = J * (L + 1);
+  for (int b = 0; b < first;) {
+    // first-order nodes b .. e: their spectra (where they have children) at the front of the
+    // area, the rest of it for the passes of the nodes and then of their children
+    size_t u = 0, w = 0;
+    int e = b;
+    for (; e < first && e - b < scat::kMaxNodes3; ++e) {
+      const bool kids = second && e / (L + 1) < J - 1;
+      const size_t u1 = u + (kids ? tot : 0), w1 = w + cost(e % (L + 1));
+      // (the children of one node need what a node of the largest degree does)
+      if (e > b && u1 + std::max(w1, kids || u > 0 ? cost(L) : 0) > arena.size) break;
+      u = u1;
+      w = w1;
     }
+    arena.used = 0;
+    std::vector<float2 *> spec(e - b, nullptr);
+    for (int c = b; c < e; ++c)
+      if (second && c / (L + 1) < J - 1) spec[c - b] = arena.take(tot);
+    nd.n = 0;
+    for (int c = b; c < e; ++c) {
+      const int j = c / (L + 1), l = c % (L + 1);
+      float2 *W = arena.take(static_cast<size_t>(l + 1) * tot);
+      nd.v[nd.n++] = scat::Node3{XH, pairs(j, l), W, arena.take(half), spec[c - b], l + 1, 1 + c, 0};
+    }
+    if (arena.full) return SCAT_ERR_ALLOC;
+    SCAT_TRY(passes(nd));
+    nd.n = 0;
+    arena.used = u;
+    for (int c = b; c < e; ++c) {
+      const int j1 = c / (L + 1), l = c % (L + 1);
+      for (int j2 = j1 + 1; second && j2 < J; ++j2) {
+        if (nd.n == scat::kMaxNodes3 || (nd.n > 0 && arena.used + cost(l) > arena.size)) {
+          SCAT_TRY(passes(nd));
+          nd.n = 0;
+          arena.used = u;
+        }
+        float2 *W = arena.take(static_cast<size_t>(l + 1) * tot);
+        nd.v[nd.n++] = scat::Node3{spec[c - b], pairs(j2, l), W, arena.take(half), nullptr, l + 1,
+                                   second_channel_3d(h, j1, l) + j2 - j1 - 1, 0};
+        if (arena.full) return SCAT_ERR_ALLOC;
+      }
+    }
+    if (nd.n > 0) SCAT_TRY(passes(nd));
+    b = e;
+  }
   // aliases of axis 0, small inverse transforms, real parts: all channels at once
+  if (sz.small_out) {
+    const int whole[3] = {m0, m1, m2};
+    SCAT_TRY(scat::launch3_out(P, o, pc * K, n0, m0, m1, m2, p->padded ? p->user_out3 : whole, st));
+    return SCAT_OK;
+  }
   SCAT_TRY(scat::launch3_fold0(P, Q, pc * K, n0, m0, m1 * m2, st));
   SCAT_TRY(scat::launch3_fft(Q, pc * K, m0, m1, m2, true, tw, tw_n, st));
-  SCAT_TRY(scat::launch3_real_part(Q, o, pc * K * static_cast<long>(mout), st));
+  SCAT_TRY(scat::launch3_real_part(Q, o, pc * K * static_cast<long>(sz.mout), st));
+  return SCAT_OK;
+}
+
+// ---- Backward pass of a fused 3-D plan.  Batches of first-order nodes with all their children:
+// the forward passes again up to the nodes' spectra, the gradients of every rho from the output
+// gradients (and, for nodes with children, from the children's contributions), and back through
+// the same passes; the contributions to x's gradient spectrum are summed over the batches in AX.
+// x as in forward_3d_fused; go: the output gradient (of a padded plan with a small output grid:
+// the caller's, else on the periodic grid's); gi: gradient on the periodic grid.
+scat_status backward_3d_fused(scat_plan *p, const float *x, const float *go, float *gi, long pc, size_t area,
+                              hipStream_t st) {
+  const scat::HostPlan3D &h = p->h3;
+  const int n0 = h.shape[0], n1 = h.shape[1], n2 = h.shape[2];
+  const int J = h.J, L = h.L, K = h.K;
+  const int Jo = h.out_shift();
+  const Sizes3 sz = sizes_3d(*p);
+  const size_t tot = static_cast<size_t>(pc) * sz.n, half = static_cast<size_t>(pc) * sz.half;
+  const bool second = h.max_order == 2 && J >= 2;
+  const int m0 = n0 >> Jo, m1 = n1 >> Jo, m2 = n2 >> Jo;
+  float2 *XH = static_cast<float2 *>(p->work);
+  float2 *AX = XH + tot;
+  float2 *Gs = AX + tot;
+  Arena3 arena{Gs + static_cast<size_t>(pc) * K * sz.mout, area / sizeof(float2)};
+  const float *tab = p->d_tables;
+  const float2 *tw = p->d_tw;
+  const int tw_n = p->tw_n;
+  const float *phi = tab + p->phi3_off;
+  auto pairs = [&](int j, int l) {
+    return reinterpret_cast<const float2 *>(tab + p->psi3_off[static_cast<size_t>(j) * (L + 1) + l]);
+  };
+  // small spectra of the output gradient, all channels of the chunk at once
+  if (sz.small_out) {
+    const int whole[3] = {m0, m1, m2};
+    SCAT_TRY(scat::launch3_out_adj(go, Gs, pc * K, m0, m1, m2, p->padded ? p->user_out3 : whole, st));
+  } else {
+    SCAT_TRY(scat::launch3_real_to_complex(go, Gs, pc * K * static_cast<long>(sz.mout), st));
+    SCAT_TRY(scat::launch3_fft(Gs, pc * K, m0, m1, m2, false, tw, tw_n, st));
+  }
+  scat::Nodes3 one{};
+  one.n = 1;
+  one.v[0] = scat::Node3{nullptr, nullptr, nullptr, AX, XH, 0, 0, 0};
+  SCAT_TRY(scat::launch3_axis0_rho(one, x, p->padded ? p->user_shape3 : nullptr, pc, n0, n2, n1 * n2, tw, tw_n,
+                                   st));
+  SCAT_TRY(scat::launch3_slab_fwd_low(one, nullptr, nullptr, pc, n0, n1, n2, Jo, K, tw, tw_n, st));
+  auto size = [&](int l) { return static_cast<size_t>(l + 1) * tot; };
+  const int first = J * (L + 1);
+  bool have_ax = false;
+  for (int b = 0; b < first;) {
+    size_t used = 0;
+    int e = b, kids_n = 0;
+    for (; e < first && e - b < scat::kMaxNodes3; ++e) {
+      const int j = e / (L + 1), l = e % (L + 1), kids = second ? J - 1 - j : 0;
+      const size_t more = size(l) + tot + (kids > 0 ? tot : 0) + kids * (size(l) + half);
+      if (e > b && (used + more > arena.size || kids_n + kids > scat::kMaxNodes3)) break;
+      used += more;
+      kids_n += kids;
+    }
+    arena.used = 0;
+    scat::Nodes3 all{}, parents{}, kids{};
+    for (int c = b; c < e; ++c) {
+      const int j = c / (L + 1), l = c % (L + 1);
+      const bool has = second && j < J - 1;
+      float2 *W = arena.take(size(l)), *T = arena.take(tot), *U = has ? arena.take(tot) : nullptr;
+      all.v[all.n++] = scat::Node3{XH, pairs(j, l), W, T, U, l + 1, 1 + c, has ? 0 : 1};
+      if (!has) continue;
+      parents.v[parents.n++] = all.v[all.n - 1];
+      for (int j2 = j + 1; j2 < J; ++j2) {
+        float2 *W2 = arena.take(size(l));
+        kids.v[kids.n++] = scat::Node3{U, pairs(j2, l), W2, arena.take(half), nullptr, l + 1,
+                                       second_channel_3d(h, j, l) + j2 - j - 1, 1};
+      }
+    }
+    if (arena.full) return SCAT_ERR_ALLOC;
+    SCAT_TRY(scat::launch3_slab_mul_inv(all, pc, n0, n1, n2, tw, tw_n, st));
+    // gradients of the signals that only the lowpass reads
+    scat::Sums3 leaves{};
+    if (kids.n > 0) {
+      SCAT_TRY(scat::launch3_axis0_rho(parents, nullptr, nullptr, pc, n0, n2, n1 * n2, tw, tw_n, st));
+      SCAT_TRY(scat::launch3_slab_fwd_low(parents, nullptr, nullptr, pc, n0, n1, n2, Jo, K, tw, tw_n, st));
+      SCAT_TRY(scat::launch3_slab_mul_inv(kids, pc, n0, n1, n2, tw, tw_n, st));
+      for (int i = 0; i < kids.n; ++i) leaves.v[leaves.n++] = scat::Sum3{kids.v[i].T, 0, 0, kids.v[i].chan};
+      SCAT_TRY(scat::launch3_slab_sum_inv(leaves, phi, Gs, pc, n0, n1, n2, Jo, K, tw, tw_n, st));
+      SCAT_TRY(scat::launch3_axis0_back(kids, pc, n0, n1 * n2, tw, tw_n, st));
+      SCAT_TRY(scat::launch3_slab_fwd_mulacc(kids, pc, n0, n1, n2, tw, tw_n, st));
+    }
+    scat::Sums3 own{};
+    int k = 0;
+    for (int i = 0; i < all.n; ++i) {
+      const int j = (all.v[i].chan - 1) / (L + 1), count = all.v[i].half ? 0 : J - 1 - j;
+      own.v[own.n++] = scat::Sum3{all.v[i].T, k, count, all.v[i].chan};
+      for (int q = 0; q < count; ++q, ++k) own.A[k] = kids.v[k].W;
+    }
+    SCAT_TRY(scat::launch3_slab_sum_inv(own, phi, Gs, pc, n0, n1, n2, Jo, K, tw, tw_n, st));
+    SCAT_TRY(scat::launch3_axis0_back(all, pc, n0, n1 * n2, tw, tw_n, st));
+    SCAT_TRY(scat::launch3_slab_fwd_mulacc(all, pc, n0, n1, n2, tw, tw_n, st));
+    scat::Sums3 top{};
+    top.n = 1;
+    top.v[0] = scat::Sum3{AX, 0, 0, 0};
+    int &count = top.v[0].count;
+    for (int i = 0; i < all.n; ++i) top.A[count++] = all.v[i].W;
+    if (have_ax) top.A[count++] = AX;
+    if (e < first)
+      SCAT_TRY(scat::launch3_sum_spectra(top, AX, static_cast<long>(tot), st));
+    else  // (in place: a slab of AX is read and written by one workgroup)
+      SCAT_TRY(scat::launch3_slab_sum_inv(top, phi, Gs, pc, n0, n1, n2, Jo, K, tw, tw_n, st));
+    have_ax = true;
+    b = e;
+  }
+  SCAT_TRY(scat::launch3_axis0_real(AX, gi, pc, n0, n1 * n2, tw, tw_n, st));
   return SCAT_OK;
 }
 
@@ -2032,8 +2285,9 @@ scat_status forward_3d(scat_plan *p, const float *in, float *out, long p0, long 
   return SCAT_OK;
 }
 
-// ---- backward pass of a 3-D plan (every shape: the full-grid schedule, transforms by the
-// plain passes).  With spectra A accumulated in the Fourier domain, S = sample(F conv phi)
+// ---- backward pass of a 3-D plan whose slabs do not fit a workgroup (full-grid schedule,
+// transforms by the plain passes).  With spectra A accumulated in the
+// Fourier domain, S = sample(F conv phi)
 // gives A_F += phi^ FFT(upsample(g_S)); rho = sqrt(sum_m |y_m|^2), y_m = IFFT(F^ g_m) gives
 // A_F += sum_m g_m FFT(g_rho y_m / rho); g_F = Re IFFT(A_F).  The filtered signals y_m of the
 // node at hand (and of its child) are recomputed and kept while their gradients are formed.
@@ -2067,12 +2321,8 @@ scat_status backward_3d(scat_plan *p, const float *in, const float *gout, float 
   const float *go = gout + static_cast<size_t>(p0) * K * mout;
   float *gi = gin + static_cast<size_t>(p0) * n;
   const float *phi = tab + p->phi3_off;
-  // table m of (j, l): fused plans keep them as interleaved pairs
-  auto table = [&](int j, int l, int m, int *stride) -> const float * {
-    const float *base = tab + p->psi3_off[static_cast<size_t>(j) * (L + 1) + l];
-    *stride = p->fused3 ? 2 : 1;
-    return p->fused3 ? base + static_cast<size_t>(m / 2) * 2 * n + (m & 1)
-                     : base + static_cast<size_t>(m) * n;
+  auto table = [&](int j, int l, int m) -> const float * {
+    return tab + p->psi3_off[static_cast<size_t>(j) * (L + 1) + l] + static_cast<size_t>(m) * n;
   };
   auto fft3 = [&](float2 *d, bool inv) {
     return scat::launch3_fft(d, pc, n0, n1, n2, inv, tw, tw_n, st);
@@ -2082,33 +2332,11 @@ scat_status backward_3d(scat_plan *p, const float *in, const float *gout, float 
   auto lowpass_adj = [&](int chan, float2 *dst, bool accumulate) -> hipError_t {
     return scat::launch3_tile_phi(Gs, phi, dst, pc, K, chan, n0, n1, n2, Jo, accumulate, st);
   };
-  // member p of the pair tables of (j, l) (fused plans)
-  auto pair_table = [&](int j, int l, int pr) -> const float2 * {
-    return reinterpret_cast<const float2 *>(tab + p->psi3_off[static_cast<size_t>(j) * (L + 1) + l]) +
-           static_cast<size_t>(pr) * n;
-  };
-  // W[m] = IFFT(Fh g_{j,l,m}), acc = sum_m |W[m]|^2.  Fused plans: the tables come in pairs
-  // c = g_2p + i g_2p+1 and W[p] = IFFT(Fh c) carries both members (|W[p]|^2 is the sum of
-  // their squares, and the adjoint of the product is the product with conj(c)).
+  // W[m] = IFFT(Fh g_{j,l,m}), acc = sum_m |W[m]|^2
   auto filtered = [&](const float2 *Fh, int j, int l, float2 *W, float *acc) -> hipError_t {
-    if (p->fused3) {
-      // every pair of the node at once: product + inverse slab transform, then axis 0
-      hipError_t e = scat::launch3_slab_mul_inv(Fh, pair_table(j, l, 0), W, pc, n0, n1, n2, l + 1, tw,
-                                                tw_n, st);
-      if (e != hipSuccess) return e;
-      return scat::launch3_axis0_back(0, W, acc, nullptr, pc, n0, n1 * n2, l + 1, tw, tw_n, st);
-    }
-    const int cnt = p->fused3 ? l + 1 : 2 * l + 1;
-    for (int m = 0; m < cnt; ++m) {
+    for (int m = 0; m < 2 * l + 1; ++m) {
       float2 *w = W + static_cast<size_t>(m) * tot;
-      hipError_t e;
-      if (p->fused3) {
-        e = scat::launch3_mul_ctable(Fh, pair_table(j, l, m), w, pc, static_cast<long>(n), false, false, st);
-      } else {
-        int fs;
-        const float *t = table(j, l, m, &fs);
-        e = scat::launch3_mul_table(Fh, t, w, pc, static_cast<long>(n), st, fs, false);
-      }
+      hipError_t e = scat::launch3_mul_table(Fh, table(j, l, m), w, pc, static_cast<long>(n), st, false);
       if (e != hipSuccess) return e;
       e = fft3(w, true);
       if (e != hipSuccess) return e;
@@ -2120,27 +2348,13 @@ scat_status backward_3d(scat_plan *p, const float *in, const float *gout, float 
   // A += sum_m g_m FFT(Re(gu) W[m] / sqrt(acc)); W is overwritten
   auto rho_adj = [&](const float2 *gu, int j, int l, float2 *W, const float *acc,
                      float2 *A) -> hipError_t {
-    if (p->fused3) {
-      hipError_t e = scat::launch3_axis0_back(1, W, const_cast<float *>(acc), gu, pc, n0, n1 * n2,
-                                              l + 1, tw, tw_n, st);
-      if (e != hipSuccess) return e;
-      return scat::launch3_slab_fwd_mulacc(W, pair_table(j, l, 0), A, pc, n0, n1, n2, l + 1, tw, tw_n,
-                                           st);
-    }
-    const int cnt = p->fused3 ? l + 1 : 2 * l + 1;
-    for (int m = 0; m < cnt; ++m) {
+    for (int m = 0; m < 2 * l + 1; ++m) {
       float2 *w = W + static_cast<size_t>(m) * tot;
       hipError_t e = scat::launch3_rho_back(gu, acc, w, tot, st);
       if (e != hipSuccess) return e;
       e = fft3(w, false);
       if (e != hipSuccess) return e;
-      if (p->fused3) {
-        e = scat::launch3_mul_ctable(w, pair_table(j, l, m), A, pc, static_cast<long>(n), true, true, st);
-      } else {
-        int fs;
-        const float *t = table(j, l, m, &fs);
-        e = scat::launch3_mul_table(w, t, A, pc, static_cast<long>(n), st, fs, true);
-      }
+      e = scat::launch3_mul_table(w, table(j, l, m), A, pc, static_cast<long>(n), st, true);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -2382,27 +2596,106 @@ scat_status ensure_scratch(scat_plan *plan, size_t need) {
   return SCAT_OK;
 }
 
-// Routes the launches of one call to the plan's timer while it records.
-struct ObserverScope {
-  explicit ObserverScope(scat_plan *plan) {
-    scat::set_launch_observer(plan->timer.enabled ? &plan->timer : nullptr);
+// Routes a call's launches to the plan's timer, unless the call may not create HIP events
+// (scat_forward_static).
+struct CallScope {
+  scat_plan *p;
+  bool was;
+  CallScope(scat_plan *q, bool observe) : p(q), was(q->timer.enabled) {
+    if (!observe) p->timer.enabled = false;
+    scat::set_launch_observer(p->timer.enabled ? &p->timer : nullptr);
   }
-  ~ObserverScope() { scat::set_launch_observer(nullptr); }
+  ~CallScope() {
+    scat::set_launch_observer(nullptr);
+    p->timer.enabled = was;
+  }
 };
+
+// The chunk loop of a forward call of a 3-D plan.
+scat_status forward_chunks_3d(scat_plan *plan, const float *in, float *out, long batch, const Layout3 &lay,
+                              hipStream_t st, bool observe = true) {
+  CallScope scope(plan, observe);
+  const Sizes3 sz = sizes_3d(*plan);
+  const int *u = plan->padded ? plan->user_shape3 : plan->h3.shape, *g = plan->h3.shape;
+  const int Jo = plan->h3.out_shift(), K = plan->h3.K;
+  const int whole[3] = {g[0] >> Jo, g[1] >> Jo, g[2] >> Jo};
+  const int *o = plan->padded ? plan->user_out3 : whole;
+  const size_t un = static_cast<size_t>(u[0]) * u[1] * u[2], on = static_cast<size_t>(o[0]) * o[1] * o[2];
+  for (long p0 = 0; p0 < batch; p0 += lay.chunk) {
+    const long pc = batch - p0 < lay.chunk ? batch - p0 : lay.chunk;
+    const float *x = in + static_cast<size_t>(p0) * un;
+    float *y = out + static_cast<size_t>(p0) * K * on;
+    char *tail = static_cast<char *>(plan->work) + lay.core;
+    if (lay.pad_in > 0) {
+      float *xp = reinterpret_cast<float *>(tail);
+      hipLaunchKernelGGL(k_pad_symmetric3, dim3(stream_blocks(pc * static_cast<long>(sz.n))), dim3(256), 0, st, x,
+                         xp, pc, u[0], u[1], u[2], g[0], g[1], g[2]);
+      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
+      x = xp;
+    }
+    float *op = lay.pad_out > 0 ? reinterpret_cast<float *>(tail + lay.pad_in * static_cast<size_t>(lay.chunk)) : y;
+    scat_status s = plan->fused3 ? forward_3d_fused(plan, x, op, pc, lay.area, st)
+                                 : forward_3d(plan, x, op, 0, pc, st);
+    if (s != SCAT_OK) return s;
+    if (lay.pad_out > 0) {
+      const long maps = pc * K;
+      hipLaunchKernelGGL(k_crop3, dim3(stream_blocks(maps * static_cast<long>(on))), dim3(256), 0, st, op, y, maps,
+                         whole[0], whole[1], whole[2], o[0], o[1], o[2]);
+      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
+    }
+  }
+  return SCAT_OK;
+}
+
+// The chunk loop of a backward call of a 3-D plan.
+scat_status backward_chunks_3d(scat_plan *plan, const float *in, const float *grad_out, float *grad_in, long batch,
+                               const Layout3 &lay, hipStream_t st) {
+  CallScope scope(plan, true);
+  const Sizes3 sz = sizes_3d(*plan);
+  const int *u = plan->padded ? plan->user_shape3 : plan->h3.shape, *g = plan->h3.shape;
+  const int Jo = plan->h3.out_shift(), K = plan->h3.K;
+  const int whole[3] = {g[0] >> Jo, g[1] >> Jo, g[2] >> Jo};
+  const int *o = plan->padded ? plan->user_out3 : whole;
+  const size_t un = static_cast<size_t>(u[0]) * u[1] * u[2], on = static_cast<size_t>(o[0]) * o[1] * o[2];
+  for (long p0 = 0; p0 < batch; p0 += lay.chunk) {
+    const long pc = batch - p0 < lay.chunk ? batch - p0 : lay.chunk;
+    const float *x = in + static_cast<size_t>(p0) * un;
+    const float *go = grad_out + static_cast<size_t>(p0) * K * on;
+    float *gi = grad_in + static_cast<size_t>(p0) * un;
+    // padded plans: gradient on the periodic grid, extended input, zero-extended output gradient
+    float *gxp = reinterpret_cast<float *>(static_cast<char *>(plan->work) + lay.core);
+    if (plan->padded && !plan->fused3) {
+      float *xp = gxp + sz.n * static_cast<size_t>(lay.chunk);
+      hipLaunchKernelGGL(k_pad_symmetric3, dim3(stream_blocks(pc * static_cast<long>(sz.n))), dim3(256), 0, st, x,
+                         xp, pc, u[0], u[1], u[2], g[0], g[1], g[2]);
+      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
+      x = xp;
+    }
+    if (lay.pad_out > 0) {
+      float *gop = gxp + lay.pad_in / sizeof(float) * static_cast<size_t>(lay.chunk);
+      hipLaunchKernelGGL(k_uncrop3, dim3(stream_blocks(pc * K * static_cast<long>(sz.mout))), dim3(256), 0, st, go,
+                         gop, pc * K, whole[0], whole[1], whole[2], o[0], o[1], o[2]);
+      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
+      go = gop;
+    }
+    float *dst = plan->padded ? gxp : gi;
+    scat_status s = plan->fused3 ? backward_3d_fused(plan, x, go, dst, pc, lay.area, st)
+                                 : backward_3d(plan, x, go, dst, 0, pc, st);
+    if (s != SCAT_OK) return s;
+    if (plan->padded) {
+      hipLaunchKernelGGL(k_unpad_symmetric3, dim3(stream_blocks(pc * static_cast<long>(un))), dim3(256), 0, st, gxp,
+                         gi, pc, u[0], u[1], u[2], g[0], g[1], g[2]);
+      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
+    }
+  }
+  return SCAT_OK;
+}
 
 // The chunk loop of a forward call: `lay.chunk` planes at a time through the schedule of the
 // plan, all on `st`, using the scratch plan->work points at (lay.per_plane * lay.chunk bytes).
 scat_status forward_chunks(scat_plan *plan, const float *in, float *out, long batch, const Layout &lay,
                            hipStream_t st, bool observe = true) {
-  struct NoObserver {
-    scat_plan *p;
-    bool was;
-    explicit NoObserver(scat_plan *q, bool off) : p(q), was(q->timer.enabled) {
-      if (off) p->timer.enabled = false;
-    }
-    ~NoObserver() { p->timer.enabled = was; }
-  } no_observer(plan, !observe);  // (the timer creates HIP events on demand)
-  ObserverScope observer_scope(plan);
+  CallScope scope(plan, observe);
   const scat::HostPlan &h = plan->host;
   for (long p0 = 0; p0 < batch; p0 += lay.chunk) {
     long pc = batch - p0 < lay.chunk ? batch - p0 : lay.chunk;
@@ -2416,39 +2709,22 @@ scat_status forward_chunks(scat_plan *plan, const float *in, float *out, long ba
                    (lay.xh + lay.t + lay.u + lay.v + lay.w) * static_cast<size_t>(lay.chunk);
       xp = reinterpret_cast<float *>(tail);
       op = reinterpret_cast<float *>(tail + lay.pad_in * static_cast<size_t>(lay.chunk));
-      if (h.dims == 3) {
-        const int *u = plan->user_shape3, *g = plan->h3.shape;
-        hipLaunchKernelGGL(k_pad_symmetric3, dim3(stream_blocks(pc * static_cast<long>(plan->h3.points()))),
-                           dim3(256), 0, st, in + static_cast<size_t>(p0) * u[0] * u[1] * u[2], xp, pc,
-                           u[0], u[1], u[2], g[0], g[1], g[2]);
-      } else {
-        const int ur = plan->user_shape[0], uc = plan->user_shape[1];
-        hipLaunchKernelGGL(k_pad_symmetric, dim3(stream_blocks(pc * h.shape[0] * h.shape[1])),
-                           dim3(256), 0, st, in + static_cast<size_t>(p0) * ur * uc, xp, pc, ur, uc,
-                           h.shape[0], h.shape[1]);
-      }
+      const int ur = plan->user_shape[0], uc = plan->user_shape[1];
+      hipLaunchKernelGGL(k_pad_symmetric, dim3(stream_blocks(pc * h.shape[0] * h.shape[1])),
+                         dim3(256), 0, st, in + static_cast<size_t>(p0) * ur * uc, xp, pc, ur, uc,
+                         h.shape[0], h.shape[1]);
       if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
       cin = xp;
       cout = op;
       cp0 = 0;
     }
-    scat_status s = h.dims == 3   ? (plan->fused3 ? forward_3d_fused(plan, cin, cout, cp0, pc, st)
-                                                  : forward_3d(plan, cin, cout, cp0, pc, st))
-                    : h.dims == 1 ? forward_1d(plan, cin, cout, cp0, pc, lay, st)
+    scat_status s = h.dims == 1   ? forward_1d(plan, cin, cout, cp0, pc, lay, st)
                     : plan->tree  ? forward_2d_tree(plan, cin, cout, cp0, pc, lay, st)
                     : plan->node  ? forward_2d_node(plan, cin, cout, cp0, pc, lay, st)
                     : plan->fused ? forward_2d_fused(plan, cin, cout, cp0, pc, lay, st)
                                   : forward_2d(plan, cin, cout, cp0, pc, lay, st);
     if (s != SCAT_OK) return s;
-    if (plan->padded && h.dims == 3) {
-      const int Jo = plan->h3.out_shift();
-      const int *g = plan->h3.shape, *o = plan->user_out3;
-      const long maps = pc * h.K;
-      hipLaunchKernelGGL(k_crop3, dim3(stream_blocks(maps * o[0] * o[1] * o[2])), dim3(256), 0, st, op,
-                         out + static_cast<size_t>(p0) * h.K * o[0] * o[1] * o[2], maps, g[0] >> Jo,
-                         g[1] >> Jo, g[2] >> Jo, o[0], o[1], o[2]);
-      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
-    } else if (plan->padded) {
+    if (plan->padded) {
       const int m_r = h.dims == 2 ? h.shape[0] >> h.res(h.J) : 1, m_c = h.shape[1] >> h.res(h.J);
       const int o_r = plan->user_out[0], o_c = plan->user_out[1];
       hipLaunchKernelGGL(k_crop, dim3(stream_blocks(pc * h.K * o_r * o_c)), dim3(256), 0, st, op,
@@ -2516,6 +2792,12 @@ scat_status scat_forward(scat_plan *plan, const float *in, float *out, long batc
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != plan->device) return SCAT_ERR_DEVICE;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (plan->host.dims == 3) {
+    const Layout3 lay3 = layout_3d(*plan, batch, 0, false);
+    const scat_status grown = ensure_scratch(plan, lay3.total());
+    if (grown != SCAT_OK) return grown;
+    return forward_chunks_3d(plan, in, out, batch, lay3, st);
+  }
   const Layout lay = make_layout(*plan, batch);
   const size_t need = lay.per_plane * static_cast<size_t>(lay.chunk);
   {
@@ -2546,6 +2828,12 @@ scat_status scat_forward_static(scat_plan *plan, const float *in, float *out, lo
   if (!plan->has_device || plan->static_scratch == nullptr) return SCAT_ERR_DEVICE;
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != plan->device) return SCAT_ERR_DEVICE;
+  if (plan->host.dims == 3) {
+    const Layout3 lay3 = layout_3d(*plan, batch, kStaticScratchBytes, false);
+    if (lay3.total() > kStaticScratchBytes) return SCAT_ERR_WORKSPACE;
+    plan->work = plan->static_scratch;
+    return forward_chunks_3d(plan, in, out, batch, lay3, static_cast<hipStream_t>(stream), false);
+  }
   const Layout lay = make_layout(*plan, batch, kStaticScratchBytes);
   if (lay.per_plane > kStaticScratchBytes) return SCAT_ERR_WORKSPACE;
   plan->work = plan->static_scratch;
@@ -2563,51 +2851,10 @@ scat_status scat_backward(scat_plan *plan, const float *in, const float *grad_ou
     if (!plan->has_device) return SCAT_ERR_DEVICE;
     int dev3 = -1;
     if (hipGetDevice(&dev3) != hipSuccess || dev3 != plan->device) return SCAT_ERR_DEVICE;
-    hipStream_t st3 = static_cast<hipStream_t>(stream);
-    // padded plans: extended input, its gradient and the zero-extended output gradient
-    // sit behind the periodic pass's buffers
-    const size_t n3 = plan->h3.points(), mout3 = n3 >> (3 * plan->h3.out_shift());
-    const size_t core = bytes_per_volume_3d_bwd(*plan);
-    const size_t per = core + (plan->padded ? (2 * n3 + h.K * mout3) * sizeof(float) : 0);
-    long chunk = static_cast<long>(scratch_budget() / per);
-    if (chunk < 1) chunk = 1;
-    if (chunk > batch) chunk = batch;
-    const size_t need3 = per * static_cast<size_t>(chunk);
-    {
-    const scat_status grown = ensure_scratch(plan, need3);
+    const Layout3 lay3 = layout_3d(*plan, batch, 0, true);
+    const scat_status grown = ensure_scratch(plan, lay3.total());
     if (grown != SCAT_OK) return grown;
-  }
-  ObserverScope observer_scope(plan);
-    for (long p0 = 0; p0 < batch; p0 += chunk) {
-      const long pc = batch - p0 < chunk ? batch - p0 : chunk;
-      if (!plan->padded) {
-        scat_status s3 = backward_3d(plan, in, grad_out, grad_in, p0, pc, st3);
-        if (s3 != SCAT_OK) return s3;
-        continue;
-      }
-      const int *u = plan->user_shape3, *g = plan->h3.shape, *o = plan->user_out3;
-      const int Jo = plan->h3.out_shift();
-      const size_t un = static_cast<size_t>(u[0]) * u[1] * u[2];
-      const size_t on = static_cast<size_t>(o[0]) * o[1] * o[2];
-      float *xp = reinterpret_cast<float *>(static_cast<char *>(plan->work) +
-                                            core * static_cast<size_t>(chunk));
-      float *gxp = xp + n3 * chunk;
-      float *gop = gxp + n3 * chunk;
-      hipLaunchKernelGGL(k_pad_symmetric3, dim3(stream_blocks(pc * static_cast<long>(n3))), dim3(256), 0,
-                         st3, in + static_cast<size_t>(p0) * un, xp, pc, u[0], u[1], u[2], g[0], g[1],
-                         g[2]);
-      hipLaunchKernelGGL(k_uncrop3, dim3(stream_blocks(pc * h.K * static_cast<long>(mout3))), dim3(256),
-                         0, st3, grad_out + static_cast<size_t>(p0) * h.K * on, gop, pc * h.K,
-                         g[0] >> Jo, g[1] >> Jo, g[2] >> Jo, o[0], o[1], o[2]);
-      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
-      scat_status s3 = backward_3d(plan, xp, gop, gxp, 0, pc, st3);
-      if (s3 != SCAT_OK) return s3;
-      hipLaunchKernelGGL(k_unpad_symmetric3, dim3(stream_blocks(pc * static_cast<long>(un))), dim3(256),
-                         0, st3, gxp, grad_in + static_cast<size_t>(p0) * un, pc, u[0], u[1], u[2], g[0],
-                         g[1], g[2]);
-      if (hipGetLastError() != hipSuccess) return SCAT_ERR_DEVICE;
-    }
-    return SCAT_OK;
+    return backward_chunks_3d(plan, in, grad_out, grad_in, batch, lay3, static_cast<hipStream_t>(stream));
   }
   if (h.dims == 1) {
     // signals are n1 x n2 matrices: n1-point column transforms, row transforms of n2 >> r
@@ -2634,7 +2881,7 @@ scat_status scat_backward(scat_plan *plan, const float *in, const float *grad_ou
     const scat_status grown = ensure_scratch(plan, need);
     if (grown != SCAT_OK) return grown;
   }
-  ObserverScope observer_scope(plan);
+  CallScope scope(plan, true);
   for (long p0 = 0; p0 < batch; p0 += bl.chunk) {
     long pc = batch - p0 < bl.chunk ? batch - p0 : bl.chunk;
     if (!plan->padded) {
@@ -2674,14 +2921,7 @@ scat_status scat_backward(scat_plan *plan, const float *in, const float *grad_ou
 
 size_t scat_plan_backward_workspace_bytes(const scat_plan *plan, long batch) {
   if (plan == nullptr || batch <= 0) return 0;
-  if (plan->host.dims == 3) {
-    const size_t n3 = plan->h3.points(), mout3 = n3 >> (3 * plan->h3.out_shift());
-    const size_t per = bytes_per_volume_3d_bwd(*plan) +
-                       (plan->padded ? (2 * n3 + plan->host.K * mout3) * sizeof(float) : 0);
-    long chunk = static_cast<long>(scratch_budget() / per);
-    if (chunk < 1) chunk = 1;
-    return per * static_cast<size_t>(chunk > batch ? batch : chunk);
-  }
+  if (plan->host.dims == 3) return layout_3d(*plan, batch, 0, true).total();
   const BwdLayout bl = make_bwd_layout(*plan, batch);
   return bl.per_plane * static_cast<size_t>(bl.chunk);
 }
@@ -2746,6 +2986,7 @@ scat_status scat_plan_coeff_index(const scat_plan *plan, int c, int idx[5]) {
 
 size_t scat_plan_workspace_bytes(const scat_plan *plan, long batch) {
   if (plan == nullptr || batch <= 0) return 0;
+  if (plan->host.dims == 3) return layout_3d(*plan, batch, 0, false).total();
   const Layout lay = make_layout(*plan, batch);
   return lay.per_plane * static_cast<size_t>(lay.chunk);
 }

@@ -311,13 +311,58 @@ hipError_t launch_tile_accum(float2 *dst, const float *filt, const float2 *G, lo
 // [volumes][n0][n1][n2] (sides 4...256) and the pointwise steps of the cascade
 // fused 3-D passes (slabs of axes 1 and 2 held by one workgroup); see scat_3d.hip
 bool fused3_supported(int n0, int n1, int n2, int J);
-hipError_t launch3_slab_mul_inv(const float2 *Fh, const float2 *tab, float2 *W, long volumes, int n0,
-                                int n1, int n2, int M, const float2 *tw, int tw_n, hipStream_t st);
-hipError_t launch3_slab_fwd_low(const float2 *Tin, float2 *Uout, const float *phi, float2 *P,
-                                long volumes, int n0, int n1, int n2, int J, int K, int chan,
-                                const float2 *tw, int tw_n, hipStream_t st);
-hipError_t launch3_axis0_rho(const float2 *W, const float *xreal, float2 *dst, long volumes, int n0,
-                             int Mc, int M, const float2 *tw, int tw_n, hipStream_t st);
+// A node of a fused 3-D launch (every launch takes a list of them, one per blockIdx.y):
+//   src  F^ of its source [volumes][n0][n1][n2]; tab its M pair tables [M][n0][n1][n2]
+//   W    its M signals [M][volumes][n0][n1][n2]
+//   T    axis-0 spectra [volumes][n0/2+1][n1][n2] (backward, half == 0: [volumes][n0][n1][n2])
+//   U    null, or where its own spectrum goes; chan its output channel
+struct Node3 {
+  const float2 *src, *tab;
+  float2 *W, *T, *U;
+  int M, chan, half;
+};
+constexpr int kMaxNodes3 = 24;
+struct Nodes3 {
+  int n;
+  Node3 v[kMaxNodes3];
+};
+// T = inverse slab transform of (channel chan's lowpass adjoint + the spectra A[first ... first+count))
+struct Sum3 {
+  float2 *T;
+  int first, count, chan;
+};
+constexpr int kMaxSpectra3 = 32;
+struct Sums3 {
+  int n;
+  Sum3 v[kMaxNodes3];
+  const float2 *A[kMaxSpectra3];
+};
+hipError_t launch3_slab_mul_inv(const Nodes3 &nodes, long volumes, int n0, int n1, int n2, const float2 *tw,
+                                int tw_n, hipStream_t st);
+// phi == nullptr: spectra only, no lowpass; P [volumes][K][n0][n1>>J][n2>>J]
+hipError_t launch3_slab_fwd_low(const Nodes3 &nodes, const float *phi, float2 *P, long volumes, int n0, int n1,
+                                int n2, int J, int K, const float2 *tw, int tw_n, hipStream_t st);
+// xreal (one node, its T is written): real input, of user[0] x user[1] x user[2] samples extended
+// symmetrically where user is not null; else the nodes' signals W
+hipError_t launch3_axis0_rho(const Nodes3 &nodes, const float *xreal, const int *user, long volumes, int n0,
+                             int n2, int Mc, const float2 *tw, int tw_n, hipStream_t st);
+// W <- forward axis-0 transform of (gradient of rho in T) y / rho, in place
+hipError_t launch3_axis0_back(const Nodes3 &nodes, long volumes, int n0, int Mc, const float2 *tw, int tw_n,
+                              hipStream_t st);
+hipError_t launch3_axis0_real(const float2 *src, float *out, long volumes, int n0, int Mc, const float2 *tw,
+                              int tw_n, hipStream_t st);
+// W_0 <- sum_p conj(c_p) forward slab transform of W_p
+hipError_t launch3_slab_fwd_mulacc(const Nodes3 &nodes, long volumes, int n0, int n1, int n2, const float2 *tw,
+                                   int tw_n, hipStream_t st);
+hipError_t launch3_slab_sum_inv(const Sums3 &sums, const float *phi, const float2 *Gs, long volumes, int n0,
+                                int n1, int n2, int J, int K, const float2 *tw, int tw_n, hipStream_t st);
+hipError_t launch3_sum_spectra(const Sums3 &sums, float2 *dst, long total, hipStream_t st);
+// output grids one workgroup holds: P -> the first o[0] x o[1] x o[2] output samples, and its adjoint
+bool out3_supported(int m0, int m1, int m2);
+hipError_t launch3_out(const float2 *P, float *out, long maps, int n0, int m0, int m1, int m2, const int *o,
+                       hipStream_t st);
+hipError_t launch3_out_adj(const float *gout, float2 *Gs, long maps, int m0, int m1, int m2, const int *o,
+                           hipStream_t st);
 hipError_t launch3_fold0(const float2 *P, float2 *Q, long groups, int n0, int m0, int slab,
                          hipStream_t st);
 hipError_t launch3_real_part(const float2 *src, float *out, long total, hipStream_t st);
@@ -326,19 +371,10 @@ hipError_t launch3_fft(float2 *data, long volumes, int n0, int n1, int n2, bool 
 hipError_t launch3_real_to_complex(const float *x, float2 *out, long total, hipStream_t st);
 // dst[v][e] = src[v][e] * filt[e], e < n
 hipError_t launch3_mul_table(const float2 *src, const float *filt, float2 *dst, long volumes, long n,
-                             hipStream_t st, int fstride = 1, bool accumulate = false);
-// backward pass of the 3-D transform: lowpass adjoint, pair-table products, gradient through rho
+                             hipStream_t st, bool accumulate = false);
+// backward pass of the 3-D transform: lowpass adjoint, gradient through rho
 hipError_t launch3_tile_phi(const float2 *Gs, const float *phi, float2 *dst, long volumes, int K,
                             int chan, int n0, int n1, int n2, int J, bool accumulate, hipStream_t st);
-hipError_t launch3_mul_ctable(const float2 *src, const float2 *ctab, float2 *dst, long volumes, long n,
-                              bool conj_table, bool accumulate, hipStream_t st);
-// fused backward passes (plans whose slabs fit a workgroup): axis 0 of the P pair signals in
-// place (mode 0: inverse transform + sum of squared moduli; mode 1: gradient through rho +
-// forward transform), and the adjoint of launch3_slab_mul_inv accumulated into A
-hipError_t launch3_axis0_back(int mode, float2 *W, float *acc, const float2 *gu, long volumes, int n0,
-                              int Mc, int P, const float2 *tw, int tw_n, hipStream_t st);
-hipError_t launch3_slab_fwd_mulacc(const float2 *W, const float2 *tab, float2 *A, long volumes, int n0,
-                                   int n1, int n2, int P, const float2 *tw, int tw_n, hipStream_t st);
 hipError_t launch3_rho_back(const float2 *gu, const float *acc, float2 *y, long total,
                             hipStream_t st);
 // acc[i] = |y[i]|^2 (first) or acc[i] + |y[i]|^2

@@ -54,24 +54,24 @@ struct Slab {
 
   // The way back: v holds 16 points of column c (rows t1 + T1 i); after the call the thread's
   // 16 points of row r (columns t + T2 i) of the slab transformed along both axes.
-  template <bool INV>
+  template <bool INV, bool WAVE = false>
   static __device__ __forceinline__ void transform_back(float2 (&v)[16], float2 *area, int r, int t,
                                                         int c, int t1, const float2 *__restrict__ tw,
                                                         int tw_n) {
     {
       float2 wc[16];
       load_twiddles<16, T1>(wc, t1, tw, tw_n);
-      fft_core<16, T1, INV, false>(v, t1, area + c, T1 * RS, RS, wc);
+      fft_core<16, T1, INV, WAVE>(v, t1, area + c, T1 * RS, RS, wc);
     }
 #pragma unroll
     for (int i = 0; i < 16; ++i) area[(t1 + T1 * i) * RS + c] = v[i];
-    __syncthreads();
+    group_sync<WAVE>();
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = area[r * RS + t + T2 * i];
-    __syncthreads();
+    group_sync<WAVE>();
     float2 wr[16];
     load_twiddles<16, T2>(wr, t, tw, tw_n);
-    fft_core<16, T2, INV, false>(v, t, area + r * RS, T2 + 1, 1, wr);
+    fft_core<16, T2, INV, WAVE>(v, t, area + r * RS, T2 + 1, 1, wr);
   }
   // The same two transforms with the threads' twiddles in LDS tables instead of registers
   // (for kernels short of registers): wtr[k T2 + t] = exp(-2 pi i t k / N2), k < 16, t < T2,
@@ -86,17 +86,17 @@ struct Slab {
       tab[N2 + idx] = tw[(idx / T1) * (idx % T1) * (tw_n / N1)];
     if (sync) __syncthreads();  // (else: the caller has a barrier of its own before the first use)
   }
-  template <bool INV>
+  template <bool INV, bool WAVE = false>
   static __device__ __forceinline__ void transform_tab(float2 (&v)[16], float2 *area, int r, int t,
                                                        int c, int t1, const float2 *tab) {
-    fft_core_tab<16, T2, INV, false>(v, t, area + r * RS, T2 + 1, 1, tab + t, T2);
+    fft_core_tab<16, T2, INV, WAVE>(v, t, area + r * RS, T2 + 1, 1, tab + t, T2);
 #pragma unroll
     for (int i = 0; i < 16; ++i) area[r * RS + t + T2 * i] = v[i];
-    __syncthreads();
+    group_sync<WAVE>();
 #pragma unroll
     for (int i = 0; i < 16; ++i) v[i] = area[(t1 + T1 * i) * RS + c];
-    __syncthreads();
-    fft_core_tab<16, T1, INV, false>(v, t1, area + c, T1 * RS, RS, tab + N2 + t1, T1);
+    group_sync<WAVE>();
+    fft_core_tab<16, T1, INV, WAVE>(v, t1, area + c, T1 * RS, RS, tab + N2 + t1, T1);
   }
   template <bool INV>
   static __device__ __forceinline__ void transform_back_tab(float2 (&v)[16], float2 *area, int r,
