@@ -135,6 +135,13 @@ struct scat_plan {
   // table value above 1e-7 of the table's peak (lane_words_64); L tables contiguous
   unsigned *d_lane_masks = nullptr;
   std::map<std::pair<int, int>, size_t> lane_mask_off;
+  // 2-D, fused plans: nodes of at most 8192 points are computed whole by k_node_rect
+  // (scat_rect.hip).  (source resolution, octave) -> L pairs of words in d_rect_masks, and per
+  // resolution the lowpass taps.
+  bool rect = false;
+  unsigned long long *d_rect_masks = nullptr;
+  std::map<std::pair<int, int>, size_t> rect_mask_off;
+  std::vector<size_t> rect_taps_r_off, rect_taps_c_off;
   // 3-D solid harmonic plans (host.dims == 3; host carries J, LQ = L, max_order, K only)
   scat::HostPlan3D h3;
   std::vector<size_t> psi3_off;  // per (j, l): its 2l+1 tables, contiguous
@@ -328,6 +335,8 @@ void free_device(scat_plan *p) {
   if (p->d_scratch) (void)hipFree(p->d_scratch);
   if (p->d_masks64) (void)hipFree(p->d_masks64);
   p->d_masks64 = nullptr;
+  if (p->d_rect_masks) (void)hipFree(p->d_rect_masks);
+  p->d_rect_masks = nullptr;
   if (p->d_lane_masks) (void)hipFree(p->d_lane_masks);
   p->d_lane_masks = nullptr;
   if (p->d_chan1d) (void)hipFree(p->d_chan1d);
@@ -396,6 +405,68 @@ size_t append_vec(std::vector<float> &pool, const std::vector<double> &v) {
   const double scale = 1.0 / static_cast<double>(v.size());
   for (double d : v) pool.push_back(static_cast<float>(d * scale));
   return off;
+}
+
+// Can k_node_rect compute the nodes of octave j of a plan from sources of resolution r?
+bool rect_node_fits(const scat_plan &p, int r, int j) {
+  const scat::HostPlan &h = p.host;
+  const int rj = h.res(j);
+  return p.rect && scat::node_rect_supported(p.n1 >> rj, p.n2 >> rj, 1 << (rj - r), 1 << (h.res(h.J) - rj));
+}
+
+// Tables of k_node_rect: which alias-block halves of every wavelet are in use (1e-8 of the peak,
+// below the rounding of a sum over the block), and the lowpass as spatial taps.
+scat_status upload_rect(scat_plan *p, std::vector<float> &pool) {
+  const scat::HostPlan &h = p->host;
+  std::vector<unsigned long long> words;
+  for (int j = 0; j < h.J; ++j)
+    for (int r = 0; r <= h.res(j); ++r) {
+      if (p->rect_mask_off.count({r, j}) != 0 || !rect_node_fits(*p, r, j)) continue;
+      if (r > 0 && (h.max_order < 2 || r >= j)) continue;  // no such table
+      const int rows = p->n1 >> h.res(j), cols = p->n2 >> h.res(j), A = 1 << (h.res(j) - r);
+      p->rect_mask_off[{r, j}] = words.size();
+      for (int l = 0; l < h.LQ; ++l) {
+        const FilterTable &t = *h.find(r == 0 ? 1 : 2, j * h.LQ + l, r);
+        double peak = 0.0;
+        for (double v : t.v) peak = std::max(peak, std::fabs(v));
+        unsigned long long m[2] = {0, 0};
+        for (int kr = 0; kr < rows * A; ++kr)
+          for (int kc = 0; kc < cols * A; ++kc)
+            if (std::fabs(t.v[static_cast<size_t>(kr) * cols * A + kc]) > 1e-8 * peak)
+              m[(kr % rows) / (rows / 2)] |= 1ull << (kr / rows * A + kc / cols);
+        words.push_back(m[0]);
+        words.push_back(m[1]);
+      }
+    }
+  if (words.empty()) {
+    p->rect = false;
+    return SCAT_OK;
+  }
+  if (hipMalloc(&p->d_rect_masks, words.size() * sizeof(words[0])) != hipSuccess) return SCAT_ERR_ALLOC;
+  if (hipMemcpy(p->d_rect_masks, words.data(), words.size() * sizeof(words[0]), hipMemcpyHostToDevice) != hipSuccess)
+    return SCAT_ERR_DEVICE;
+  // taps[d + R] = phi[d], |d| <= R; those that the period of a short axis would count twice are 0
+  auto push_taps = [&](const std::vector<double> &ph, int R) {
+    const double two_pi = 6.283185307179586476925286766559;
+    const int len = static_cast<int>(ph.size());
+    const size_t off = pool.size();
+    for (int d = -R; d <= R; ++d) {
+      double acc = 0.0;
+      if (2 * d >= -len && 2 * d < len)
+        for (int k = 0; k < len; ++k) acc += ph[k] * std::cos(two_pi * ((static_cast<long>(k) * (d + len)) % len) / len);
+      pool.push_back(static_cast<float>(acc / len));
+    }
+    return off;
+  };
+  p->rect_taps_r_off.assign(h.J, 0);
+  p->rect_taps_c_off.assign(h.J, 0);
+  for (int j = 0; j < h.J; ++j) {
+    const int r = h.res(j), R = scat::rect_reach(1 << (h.res(h.J) - r));
+    if (!rect_node_fits(*p, r, j)) continue;
+    p->rect_taps_r_off[r] = push_taps(h.phi_rows[r], R);
+    p->rect_taps_c_off[r] = push_taps(h.phi_cols[r], R);
+  }
+  return SCAT_OK;
 }
 
 scat_status upload(scat_plan *p) {
@@ -527,6 +598,10 @@ scat_status upload(scat_plan *p) {
                     hipMemcpyHostToDevice) != hipSuccess)
         return SCAT_ERR_DEVICE;
     }
+  }
+  if (p->rect) {
+    const scat_status e = upload_rect(p, pool);
+    if (e != SCAT_OK) return e;
   }
   if (p->node_taps) {
     const int N = p->n1;
@@ -850,6 +925,8 @@ scat_status create_common(scat_plan **out_plan, int dims, const int *user_shape,
   p->node_tables = dims == 2 && oversampling == 0 && p->n1 == p->n2 &&
                    ((p->n1 == 256 && J == 3) || (p->n1 == 128 && J == 2));
   p->node = node_kernels && p->node_tables;
+  // (an oversampled plan's lowpass is wider, in output steps, than k_node_rect's filter)
+  p->rect = node_kernels && p->fused && !p->tree && !p->node && oversampling == 0;
   p->node_taps = dims == 2 && oversampling == 0 && p->n1 == p->n2 && J < 31 && (p->n1 >> J) == 32;
   if (padded) {
     p->padded = true;
@@ -1258,21 +1335,58 @@ scat_status forward_2d_fused(scat_plan *p, const float *in, float *out, long p0,
     return scat::launch_row_lowpass(W, nodes, m_r, Mc, m_c, pcs, o, cm, K, tw, tw_n, st);
   };
 
+  // Octave j's nodes whole (k_node_rect) from sources of resolution r?  (first order: only if the
+  // children can read the row-and-column spectra such a node leaves)
+  auto whole = [&](int r, int j) { return tape == nullptr && rect_node_fits(*p, r, j); };
+  auto whole_first = [&](int j1) {
+    bool ok = whole(0, j1);
+    for (int j2 = j1 + 1; h.max_order == 2 && j2 < J; ++j2) ok = ok && whole(h.res(j1), j2);
+    return ok;
+  };
+  auto rect_nodes = [&](const float2 *src, long ns, int r, int j, size_t filt, float2 *uc, int G, int base, int cs) {
+    const int rj = h.res(j);
+    scat::RectNode n;
+    n.N1 = Nr >> rj;
+    n.N2 = Nc >> rj;
+    n.A = 1 << (rj - r);
+    n.dec = 1 << (rJ - rj);
+    n.src = src;
+    n.filt = tab + filt;
+    n.mask = p->d_rect_masks + p->rect_mask_off.at({r, j});
+    n.taps_r = tab + p->rect_taps_r_off[rj];
+    n.taps_c = tab + p->rect_taps_c_off[rj];
+    n.uout = uc;
+    n.out = o;
+    n.NS = ns;
+    n.F = L;
+    n.G = G;
+    n.chan_base = base;
+    n.chan_src = cs;
+    n.chan_f = 1;
+    n.K = K;
+    n.tw = tw;
+    n.tw_n = tw_n;
+    return scat::launch_node_rect(n, st);
+  };
+
   SCAT_TRY(col_and_lowpass(0, x, pc, Nr, Nc, 0, XC, ChanMap{1, 1, 0, 0}));
-  // every first-order octave in one row pass over x's column spectra
+  // the other first-order octaves in one row pass over x's column spectra
   std::vector<float2 *> t1(J);
   {
     scat::FusedLevel lv[4];
     size_t off = 0;
+    int nlev = 0;
     for (int j1 = 0; j1 < J; ++j1) {
+      if (whole_first(j1)) continue;
       const bool kids = h.max_order == 2 && j1 < J - 1;
       t1[j1] = T + off;
       if (tape != nullptr && !kids)
         t1[j1] = tape->base + tape->y1_off[j1] * pc;  // straight to the tape, no column pass
-      lv[j1] = scat::FusedLevel{h.res(j1), L, tab + p->psi1_off[j1], t1[j1]};
+      lv[nlev++] = scat::FusedLevel{h.res(j1), L, tab + p->psi1_off[j1], t1[j1]};
       off += static_cast<size_t>(pc) * L * (n >> (2 * h.res(j1)));
     }
-    SCAT_TRY(scat::launch_rows_fused(XC, true, pc, Nr, Nc, lv, J, tw, tw_n, st));
+    if (nlev > 0) SCAT_TRY(scat::launch_rows_fused(XC, true, pc, Nr, Nc, lv, nlev, tw, tw_n, st));
+    if (nlev < J) SCAT_TRY(scat::launch_row_fwd(XC, pc * (Nr / 2 + 1), Nc, tw, tw_n, st));
   }
   int s2_base = 1 + J * L;
   for (int j1 = 0; j1 < J; ++j1) {
@@ -1280,7 +1394,11 @@ scat_status forward_2d_fused(scat_plan *p, const float *in, float *out, long p0,
     const int M1r = Nr >> r1, M1c = Nc >> r1;
     const bool kids = h.max_order == 2 && j1 < J - 1;
     if (tape != nullptr && !kids) continue;
-    SCAT_TRY(col_and_lowpass(1, t1[j1], pc * L, M1r, M1c, r1, kids ? U : nullptr,
+    const bool whole1 = whole_first(j1);
+    if (whole1)
+      SCAT_TRY(rect_nodes(XC, pc, 0, j1, p->psi1_off[j1], kids ? U : nullptr, 1, 1 + j1 * L, 0));
+    else
+      SCAT_TRY(col_and_lowpass(1, t1[j1], pc * L, M1r, M1c, r1, kids ? U : nullptr,
                              ChanMap{L, L, 0, 1 + j1 * L}));
     if (!kids) continue;
     const int octs = J - 1 - j1;
@@ -1316,20 +1434,30 @@ scat_status forward_2d_fused(scat_plan *p, const float *in, float *out, long p0,
       s2_base += L * L * octs;
       continue;
     }
+    // children: those computed whole read the nodes' row-and-column spectra, the others before
+    // them the column spectra
     std::vector<float2 *> t2(J);
     {
       scat::FusedLevel lv[4];
       size_t off = 0;
+      int nlev = 0;
       for (int j2 = j1 + 1; j2 < J; ++j2) {
+        if (whole(r1, j2)) continue;
         t2[j2] = V + off;
         if (tape != nullptr)
           t2[j2] = tape->base + tape->y2_off.at({j1, j2}) * pc;
-        lv[j2 - j1 - 1] = scat::FusedLevel{h.res(j2) - r1, L, tab + p->psi2_off[{r1, j2}], t2[j2]};
+        lv[nlev++] = scat::FusedLevel{h.res(j2) - r1, L, tab + p->psi2_off[{r1, j2}], t2[j2]};
         off += static_cast<size_t>(pc) * L * L * (n >> (2 * h.res(j2)));
       }
-      SCAT_TRY(scat::launch_rows_fused(U, true, pc * L, M1r, M1c, lv, octs, tw, tw_n, st));
+      if (nlev > 0) SCAT_TRY(scat::launch_rows_fused(U, true, pc * L, M1r, M1c, lv, nlev, tw, tw_n, st));
+      if (nlev < octs && !whole1) SCAT_TRY(scat::launch_row_fwd(U, pc * L * (M1r / 2 + 1), M1c, tw, tw_n, st));
     }
     for (int j2 = j1 + 1; j2 < J; ++j2) {
+      if (whole(r1, j2)) {
+        SCAT_TRY(rect_nodes(U, pc * L, r1, j2, p->psi2_off[{r1, j2}], nullptr, L,
+                            s2_base + (j2 - j1 - 1) * L, octs * L));
+        continue;
+      }
       const int r2 = h.res(j2);
       const int M2r = Nr >> r2, M2c = Nc >> r2;
       if (tape != nullptr) continue;

@@ -254,6 +254,32 @@ hipError_t launch_node(const NodeLaunch &n, hipStream_t st);
 hipError_t launch_sum4(const float *part, float *out, long nodes, int G, int K, int chan_base,
                        hipStream_t st);
 
+// Whole nodes of N1 x N2 points for grids of any shape (scat_rect.hip): the spectrum from the
+// source's half spectrum (S = A N1 x A N2 points, rows 0 .. A N1 / 2 stored), inverse transform,
+// modulus, lowpass by a FIR filter of 2 rect_reach(dec) + 1 taps and subsampling by dec per axis.
+//   src    [NS][A N1/2+1][A N2]; filt [F][A N1][A N2], pre-scaled
+//   mask   [F][2] device words: bit a_r A + a_c of word h clear = the filter is negligible on the
+//          h-th half of the rows of that N1 x N2 alias block
+//   uout   null or [NS * F][N1/2+1][N2] half spectra of the moduli
+//   out    [planes][K][N1/dec][N2/dec], channels as in NodeLaunch
+struct RectNode {
+  int N1, N2, A, dec;
+  const float2 *src;
+  const float *filt;
+  const unsigned long long *mask;
+  const float *taps_r, *taps_c;
+  float2 *uout;
+  float *out;
+  long NS;
+  int F, G;
+  int chan_base, chan_src, chan_f, K;
+  const float2 *tw;
+  int tw_n;
+};
+bool node_rect_supported(int N1, int N2, int A, int dec);
+int rect_reach(int dec);
+hipError_t launch_node_rect(const RectNode &n, hipStream_t st);
+
 // Modulus backward step of whole nodes in one pass (k_node_modback): data [nodes][Mr][Mc]
 // gradient spectra in, gradient spectra of the taped y [nodes][Mr][Mc] out, in place.  The
 // _low form starts from the node's adjoint lowpass instead (arguments as

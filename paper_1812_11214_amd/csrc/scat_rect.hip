@@ -1,0 +1,319 @@
+// Whole nodes of the 2-D cascade for grids of any shape: the nodes of at most 8192 points (sides
+// 16 ... 128, square or 2 : 1) below an input or a first-order modulus whose spectrum is stored.
+//
+// One slab of N1 N2 / 16 threads (16 points each) computes a node: filter product with the source's
+// half spectrum + periodisation, inverse 2-D transform, modulus, lowpass and subsampling as a
+// separable FIR filter with the spatial taps of phi, and, for nodes with children, the forward
+// transform of the modulus.  Against the passes that serve these nodes otherwise (k_rows_fused,
+// k_col_fast, k_row_lowpass_fast) the node never goes to memory, between the row and the column
+// transform as little as after the modulus: 8 + 8 + 4 bytes per point saved.  The nodes that fit
+// always take it: 96 planes of 128 x 128, J = 3, 613 -> 299 us (their 6144 + 6144 second-order nodes
+// of octave 0: 331 -> 128 us); 48 planes of 200 x 120, 555 -> 345 us.  What bounds it now is the
+// source spectrum and filter reads through L2 (130 KB per 64 x 64 child of a 128 x 128 node, 9 TB/s)
+// together with the transforms' LDS exchanges.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <string>
+
+#include "fft_regs.hpp"
+#include "scat_kernels.hpp"
+
+namespace scat {
+
+namespace {
+
+// Row slots of the slab in LDS.  The lanes of one half-wavefront hold 32 / T2 rows x T2 adjacent
+// columns, and a slot stride of (odd multiple of T2) mod 32 elements puts them on distinct banks;
+// the row exchange is unpadded (16 T2 = N2 elements), which keeps a 64 x 64 node at 36 KB and so
+// four workgroups on a compute unit.
+constexpr int rect_row_stride(int N2) { return N2 + N2 / 16; }
+constexpr int kRectReach = 5;  // taps each side in output steps: 6.25 standard deviations of phi
+
+struct RectArgs {
+  const float2 *src;               // [NS][Sr/2+1][Sc]
+  const float *filt;               // [F][Sr][Sc]
+  const unsigned long long *mask;  // [F][2]: see RectNode
+  const float *taps_r, *taps_c;    // [2 R + 1]
+  float2 *uout;
+  float *out;
+  unsigned nodes, blocks;
+  int F, G, Sr, lgA;
+  int chan_base, chan_src, chan_f, K;
+  const float2 *tw;
+  int tw_n;
+};
+
+template <int N1, int N2>
+struct RectShape {
+  static constexpr int T1 = N1 / 16, T2 = N2 / 16;
+  static constexpr int TS = N1 * N2 / 16;
+  static constexpr int NT = TS < 256 ? 256 : TS;
+  static constexpr int SPW = NT / TS;
+  static constexpr int RS = rect_row_stride(N2);
+  static constexpr size_t lds_bytes = (static_cast<size_t>(SPW) * N1 * RS + N1 + N2) * sizeof(float2);
+  static_assert(TS >= 16 && TS <= 512, "node shape");
+};
+
+// OPT adjacent outputs of the FIR filter from a periodic line of N samples in LDS (stride ST):
+// acc[j] = sum_ti taps[ti] line[e0 + DEC j + 2 R - ti].  Each half of the filter is summed from its
+// tail to its centre, by itself: the partial sums stay small for as long as possible (error of the
+// coefficients 5 to 20 % below that of the Fourier-domain lowpass of the passes, which one sweep
+// over all taps exceeds by 5 to 35 %; the time is the same).
+template <int DEC, int OPT, int N, int ST>
+__device__ __forceinline__ void fir(float (&acc)[OPT], const float *line, int e0, const float *__restrict__ taps) {
+  constexpr int R = kRectReach * DEC, NTAP = 2 * R + 1, NIN = DEC * (OPT - 1) + NTAP;
+  constexpr int SEG = DEC == 2 ? 2 : 4;  // e0 is a multiple of SEG: runs of inputs that do not wrap
+  static_assert((DEC * OPT) % SEG == 0 && R % SEG == 0, "runs");
+  float hi[OPT];
+#pragma unroll
+  for (int j = 0; j < OPT; ++j) acc[j] = hi[j] = 0.f;
+#pragma unroll
+  for (int k = 0; k * SEG <= R + DEC * (OPT - 1); ++k) {
+    const float *p = line + ((e0 + SEG * k) & (N - 1)) * ST;
+#pragma unroll
+    for (int e = SEG * k; e < SEG * k + SEG; ++e) {
+#pragma unroll
+      for (int j = 0; j < OPT; ++j) {
+        const int ti = DEC * j + 2 * R - e;
+        if (ti >= R && ti < NTAP) hi[j] = fmaf(taps[ti], p[(e - SEG * k) * ST], hi[j]);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = (NIN - 1) / SEG; (k + 1) * SEG > R + 1; --k) {
+    const float *p = line + ((e0 + SEG * k) & (N - 1)) * ST;
+#pragma unroll
+    for (int e = SEG * k + SEG - 1; e >= SEG * k; --e) {
+#pragma unroll
+      for (int j = 0; j < OPT; ++j) {
+        const int ti = DEC * j + 2 * R - e;
+        if (ti >= 0 && ti < R) acc[j] = fmaf(taps[ti], p[(e - SEG * k) * ST], acc[j]);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < OPT; ++j) acc[j] += hi[j];
+}
+
+// The slabs of a workgroup take consecutive nodes (filter fastest), and each XCD (workgroups are
+// dealt to the eight in turn) a contiguous run of them: the filters of a source meet in one L2.
+template <int N1, int N2, int DEC>
+__global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectArgs a) {
+  using S = RectShape<N1, N2>;
+  constexpr int T1 = S::T1, T2 = S::T2, TS = S::TS, RS = S::RS;
+  constexpr bool WAVE = TS <= 64;  // a slab is (part of) one wavefront
+  constexpr int MR = N1 / DEC, MC = N2 / DEC, R = kRectReach * DEC;
+  extern __shared__ __attribute__((aligned(16))) float2 lds[];
+  // (the slab is the same for all lanes of a wave from 64 threads on: its node stays scalar)
+  const int slab = TS >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / TS) : threadIdx.x / TS;
+  const int q = threadIdx.x % TS;
+  const unsigned blk = (blockIdx.x & 7) * (a.blocks >> 3) + (blockIdx.x >> 3);
+  if (blk * S::SPW >= a.nodes) return;
+  const bool live = blk * S::SPW + slab < a.nodes;
+  const unsigned node = live ? blk * S::SPW + slab : a.nodes - 1;  // idle slabs shadow the last node, store nothing
+  const unsigned s = node / static_cast<unsigned>(a.F);
+  const int f = static_cast<int>(node - s * a.F);
+  float2 *area = lds + slab * (N1 * RS);
+  float2 *wtab = lds + S::SPW * (N1 * RS);
+  for (int i = threadIdx.x; i < N2; i += S::NT) wtab[i] = a.tw[(i / T2) * (i % T2) * (a.tw_n / N2)];
+  for (int i = threadIdx.x; i < N1; i += S::NT) wtab[N2 + i] = a.tw[(i / T1) * (i % T1) * (a.tw_n / N1)];
+  const int r = q / T2, t = q % T2;  // row layout: row r, columns t + T2 i
+  const int c = q % N2;              // column layout: column c, rows t1 + T1 i
+  const int t1 = N2 >= 64 ? __builtin_amdgcn_readfirstlane(q / N2) : q / N2;
+
+  // ---- 1. spectrum of the node in column layout: lanes read adjacent columns.  One turn of the
+  // inner loop takes one alias block of one half of the node's rows (16 loads in flight); the
+  // block halves on which the filter is negligible are left out.
+  float2 v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = make_float2(0.f, 0.f);
+  {
+    const int Sr = a.Sr, Sc = N2 << a.lgA, A = 1 << a.lgA;
+    const float2 *src = a.src + static_cast<size_t>(s) * (Sr / 2 + 1) * Sc;
+    const float *filt = a.filt + static_cast<size_t>(f) * Sr * Sc;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      unsigned long long rem = a.mask[2 * f + h];
+      while (rem != 0ull) {
+        const int bit = __ffsll(static_cast<long long>(rem)) - 1;
+        rem &= rem - 1ull;
+        const int ar = bit >> a.lgA, ac = bit & (A - 1);
+        const int kc = c + N2 * ac, kcm = (Sc - kc) & (Sc - 1);
+        float2 x[8];
+        float w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          // rows above Sr / 2 are the conjugates of the stored ones
+          const int kr = t1 + T1 * (8 * h + i) + N1 * ar;
+          const bool mir = kr > Sr / 2;
+          x[i] = src[(mir ? Sr - kr : kr) * Sc + (mir ? kcm : kc)];
+          w[i] = filt[kr * Sc + kc];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const bool mir = t1 + T1 * (8 * h + i) + N1 * ar > Sr / 2;
+          float2 &z = v[8 * h + i];
+          z.x = fmaf(x[i].x, w[i], z.x);
+          z.y = fmaf(x[i].y, mir ? -w[i] : w[i], z.y);
+        }
+      }
+    }
+  }
+  __syncthreads();  // the twiddles
+
+  // ---- 2. inverse transform: columns, transpose, rows
+  fft_core_tab<16, T1, true, WAVE>(v, t1, area + c, T1 * RS, RS, wtab + N2 + t1, T1);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) area[(t1 + T1 * i) * RS + c] = v[i];
+  group_sync<WAVE>();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = area[r * RS + t + T2 * i];
+  group_sync<WAVE>();
+  fft_core_tab<16, T2, true, WAVE>(v, t, area + r * RS, T2, 1, wtab + t, T2);
+
+  // ---- 3. modulus
+  float u[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) u[i] = __builtin_amdgcn_sqrtf(v[i].x * v[i].x + v[i].y * v[i].y);
+
+  // ---- 4. lowpass + subsampling by DEC: along the rows, then along the columns
+  constexpr int US = N2 + 1, HS = MC + 4;
+  static_assert(N1 * (US + HS) <= 2 * N1 * RS, "LDS of the lowpass");
+  float *ub = reinterpret_cast<float *>(area);  // [N1][US]
+  float *hb = ub + N1 * US;                     // [N1][HS]
+#pragma unroll
+  for (int i = 0; i < 16; ++i) ub[r * US + t + T2 * i] = u[i];
+  group_sync<WAVE>();
+  {
+    constexpr int OPT = 16 / DEC;  // outputs per thread, adjacent columns
+    const int rr = q % N1, mg = q / N1;
+    float acc[OPT];
+    fir<DEC, OPT, N2, 1>(acc, ub + rr * US, DEC * OPT * mg - R, a.taps_c);
+#pragma unroll
+    for (int j = 0; j < OPT; ++j) hb[rr * HS + OPT * mg + j] = acc[j];
+  }
+  group_sync<WAVE>();
+  {
+    constexpr int OPV = DEC >= 4 ? 1 : 16 / (DEC * DEC);  // outputs per thread, adjacent rows
+    const int mc = q % MC, ng = q / MC;
+    if (DEC <= 4 || ng < MR) {
+      float acc[OPV];
+      fir<DEC, OPV, N1, HS>(acc, hb + mc, DEC * OPV * ng - R, a.taps_r);
+      if (live) {
+        const unsigned plane = s / static_cast<unsigned>(a.G);
+        const int g = static_cast<int>(s - plane * a.G);
+        float *op = a.out + (static_cast<size_t>(plane) * a.K + a.chan_base + g * a.chan_src + f * a.chan_f) * (MR * MC);
+#pragma unroll
+        for (int j = 0; j < OPV; ++j) op[(OPV * ng + j) * MC + mc] = acc[j];
+      }
+    }
+  }
+  if (a.uout == nullptr) return;
+
+  // ---- 5. spectrum of the modulus for the children (rows 0 .. N1/2)
+  group_sync<WAVE>();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = make_float2(u[i], 0.f);
+  fft_core_tab<16, T2, false, WAVE>(v, t, area + r * RS, T2, 1, wtab + t, T2);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) area[r * RS + t + T2 * i] = v[i];
+  group_sync<WAVE>();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = area[(t1 + T1 * i) * RS + c];
+  group_sync<WAVE>();
+  fft_core_tab<16, T1, false, WAVE>(v, t1, area + c, T1 * RS, RS, wtab + N2 + t1, T1);
+  if (live) {
+    float2 *up = a.uout + static_cast<size_t>(node) * (N1 / 2 + 1) * N2 + c;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (t1 + T1 * i <= N1 / 2) up[(t1 + T1 * i) * N2] = v[i];
+  }
+}
+
+double log2d(double n) { return n > 1 ? std::log2(n) : 0.0; }
+
+template <int N1, int N2, int DEC>
+hipError_t launch_rect_t(RectArgs &a, hipStream_t st) {
+  using S = RectShape<N1, N2>;
+  if (a.tw_n % N1 != 0 || a.tw_n % N2 != 0) return hipErrorInvalidValue;
+  a.blocks = ((a.nodes + S::SPW - 1) / S::SPW + 7) / 8 * 8;
+  const std::string name =
+      "k_node_rect<" + std::to_string(N1) + ", " + std::to_string(N2) + ", " + std::to_string(DEC) + ">";
+  const double nodes = static_cast<double>(a.nodes), pts = static_cast<double>(N1) * N2;
+  const double spts = static_cast<double>(a.Sr) * (N2 << a.lgA);
+  const double fft = 5.0 * pts * log2d(pts);
+  LaunchScope obs(name.c_str(),
+                  nodes / a.F * spts * 4 + a.F * spts * 4 + nodes * pts / (DEC * DEC) * 4 +
+                      (a.uout ? nodes * pts * 4 : 0),
+                  nodes * (4.0 * spts + fft * (a.uout ? 1.5 : 1.0) + 4.0 * pts +
+                           2.0 * (2 * kRectReach * DEC + 1) * pts * (1.0 / DEC + 1.0 / (DEC * DEC))),
+                  st);
+  if (S::lds_bytes > 65536) {
+    static unsigned long long lds_ok = 0;
+    hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k_node_rect<N1, N2, DEC>), lds_ok);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k_node_rect<N1, N2, DEC>), dim3(static_cast<unsigned>(a.blocks)), dim3(S::NT), S::lds_bytes, st,
+                     a);
+  return hipGetLastError();
+}
+
+bool pow2i(int n) { return n > 0 && (n & (n - 1)) == 0; }
+
+}  // namespace
+
+int rect_reach(int dec) { return kRectReach * dec; }
+
+bool node_rect_supported(int N1, int N2, int A, int dec) {
+  return pow2i(N1) && pow2i(N2) && N1 >= 16 && N2 >= 16 && N1 * N2 <= 8192 &&
+         (N1 == N2 || N1 == 2 * N2 || N2 == 2 * N1) && (dec == 2 || dec == 4 || dec == 8) && pow2i(A) && A <= 8;
+}
+
+hipError_t launch_node_rect(const RectNode &n, hipStream_t st) {
+  if (n.NS <= 0) return hipSuccess;
+  if (!node_rect_supported(n.N1, n.N2, n.A, n.dec) || n.F < 1 || n.G < 1 || n.mask == nullptr ||
+      n.NS > 0x7fff0000L / n.F)
+    return hipErrorInvalidValue;
+  RectArgs a;
+  a.src = n.src;
+  a.filt = n.filt;
+  a.mask = n.mask;
+  a.taps_r = n.taps_r;
+  a.taps_c = n.taps_c;
+  a.uout = n.uout;
+  a.out = n.out;
+  a.nodes = static_cast<unsigned>(n.NS * n.F);
+  a.F = n.F;
+  a.G = n.G;
+  a.Sr = n.N1 * n.A;
+  a.lgA = n.A == 1 ? 0 : n.A == 2 ? 1 : n.A == 4 ? 2 : 3;
+  a.chan_base = n.chan_base;
+  a.chan_src = n.chan_src;
+  a.chan_f = n.chan_f;
+  a.K = n.K;
+  a.tw = n.tw;
+  a.tw_n = n.tw_n;
+#define SCAT_RECT(N1_, N2_)                                          \
+  case (N1_ << 12) | N2_:                                            \
+    switch (n.dec) {                                                 \
+      case 2: return launch_rect_t<N1_, N2_, 2>(a, st);              \
+      case 4: return launch_rect_t<N1_, N2_, 4>(a, st);              \
+      default: return launch_rect_t<N1_, N2_, 8>(a, st);             \
+    }
+  switch ((n.N1 << 12) | n.N2) {
+    SCAT_RECT(16, 16)
+    SCAT_RECT(16, 32)
+    SCAT_RECT(32, 16)
+    SCAT_RECT(32, 32)
+    SCAT_RECT(32, 64)
+    SCAT_RECT(64, 32)
+    SCAT_RECT(64, 64)
+    SCAT_RECT(64, 128)
+    SCAT_RECT(128, 64)
+    default: return hipErrorInvalidValue;
+  }
+#undef SCAT_RECT
+}
+
+}  // namespace scat

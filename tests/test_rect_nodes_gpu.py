@@ -1,0 +1,75 @@
+"""Whole-node kernel for grids of any shape (k_node_rect): every node shape and subsampling it is
+built for, source counts that do not fill a workgroup or the last group of eight, padded and
+first-order plans, against the oracle and against the pass kernels of the same plan."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1812_11214_amd as scat
+
+from parity import TOL, order_of_channels, per_order_errors
+
+pytestmark = pytest.mark.gpu
+
+
+def run(shape, J, L, max_order, padded, x, **kw):
+    plan = scat.Scattering(shape, J, L, max_order, padded=padded, **kw)
+    try:
+        plan.timing_begin(None)
+        y = plan.forward(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        return y.cpu().numpy(), set(plan.timing_end()), plan.coeff_index()
+    finally:
+        plan.close()
+
+
+@pytest.mark.parametrize("shape,J,L,max_order,padded,batch", [
+    ((128, 128), 3, 8, 2, False, 2),   # 64 x 64 and 32 x 32 nodes, octave 0 on the passes
+    ((128, 128), 4, 3, 2, False, 1),   # 64, 32 and 16 a side, subsampling 8, 4 and 2
+    ((64, 64), 2, 5, 2, False, 3),     # 15 first-order nodes: a last workgroup that is not full
+    ((64, 64), 3, 1, 2, False, 9),     # one angle; more sources than a group of eight
+    ((128, 64), 3, 3, 2, False, 3),    # tall nodes down to 32 x 16
+    ((64, 128), 2, 4, 2, False, 1),    # wide nodes
+    ((200, 120), 3, 4, 2, True, 2),    # padded to 256 x 128: 128 x 64 nodes
+    ((120, 200), 3, 2, 2, True, 1),    # padded to 128 x 256: 64 x 128 nodes
+    ((256, 128), 3, 2, 1, False, 2),   # first order only
+    ((256, 256), 4, 2, 2, False, 1),   # octaves 0 and 1 on the passes, their grandchildren whole
+])
+def test_rect_nodes(shape, J, L, max_order, padded, batch):
+    rng = np.random.default_rng(shape[0] * 1000 + shape[1] * 10 + J)
+    x = rng.standard_normal((batch,) + shape).astype(np.float32)
+    x[0] = np.cumsum(x[0], axis=0) * 0.1 + 3
+    got, names, rows = run(shape, J, L, max_order, padded, x)
+    assert any(n.startswith("k_node_rect<") for n in names), names
+    want = (oracle.scattering2d_padded if padded else oracle.scattering2d)(x, J, L, max_order)
+    errs = per_order_errors(got, want, order_of_channels(rows), x)
+    print("rect", shape, J, L, errs, flush=True)
+    assert max(errs.values()) <= TOL, errs
+    old, names, _ = run(shape, J, L, max_order, padded, x, node_kernels=False)
+    assert not any(n.startswith("k_node_rect<") for n in names), names
+    # five chained transforms and two sums in fp32 on either side: 2 * 3e-6 of the order's maximum
+    errs = per_order_errors(got, old, order_of_channels(rows), x)
+    assert max(errs.values()) <= 6e-6, errs
+
+
+def test_oversampled_plans_keep_the_passes():
+    x = np.random.default_rng(1).standard_normal((1, 64, 64)).astype(np.float32)
+    got, names, rows = run((64, 64), 3, 3, 2, False, x, oversampling=1)
+    assert not any(n.startswith("k_node_rect<") for n in names), names
+    want = oracle.scattering2d(x, 3, 3, 2, oversampling=1)
+    errs = per_order_errors(got, want, order_of_channels(rows), x)
+    assert max(errs.values()) <= TOL, errs
+
+
+def test_special_values():
+    x = np.zeros((4, 128, 64), dtype=np.float32)
+    x[0] = -2.5
+    x[1, 3, 50] = 1.0
+    x[2] = np.random.default_rng(2).standard_normal((128, 64)) * 1e4
+    x[3, 0, 0] = np.inf
+    got, _, rows = run((128, 64), 3, 4, 2, False, x)
+    want = oracle.scattering2d(x[:3], 3, 4)
+    errs = per_order_errors(got[:3], want, order_of_channels(rows), x[:3])
+    assert max(errs.values()) <= TOL, errs
+    assert np.isnan(got[3]).all()
