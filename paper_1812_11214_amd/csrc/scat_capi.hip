@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/scat.h"
+#include "pad.hpp"
 #include "scat_host.hpp"
 #include "scat_host3d.hpp"
 #include "scat_kernels.hpp"
@@ -142,6 +143,23 @@ struct scat_plan {
   unsigned long long *d_rect_masks = nullptr;
   std::map<std::pair<int, int>, size_t> rect_mask_off;
   std::vector<size_t> rect_taps_r_off, rect_taps_c_off;
+  // 1-D: the periodic grid has at most 8192 samples and every node is computed by one workgroup
+  // (scat_line.hip).  Tables in natural frequency order, offsets into d_tables: the Q wavelets of
+  // an octave, (source resolution, j2) -> its wavelet, per resolution phi.
+  bool line = false;
+  std::vector<size_t> line_psi1_off, line_phi_off;
+  std::map<std::pair<int, int>, size_t> line_psi2_off;
+  // alias blocks in use (see NodeSeg in scat_line.hip): octave -> Q pairs of words, (source
+  // resolution, j2) -> one pair, in d_line_masks
+  unsigned long long *d_line_masks = nullptr;
+  std::vector<size_t> line_mask1_off;
+  std::map<std::pair<int, int>, size_t> line_mask2_off;
+  // the same by blocks of samples a thread of the adjoint holds: wavelets of children, phi
+  std::map<std::pair<int, int>, unsigned> line_kid_mask;
+  std::vector<unsigned> line_phi_mask;
+  std::vector<int> line_reach;  // per resolution: phi is negligible beyond reach + 1/2 output bands
+  float2 *d_line_tw = nullptr;  // see line_twiddles
+  int *d_line_list = nullptr;   // see LineSum
   // 3-D solid harmonic plans (host.dims == 3; host carries J, LQ = L, max_order, K only)
   scat::HostPlan3D h3;
   std::vector<size_t> psi3_off;  // per (j, l): its 2l+1 tables, contiguous
@@ -166,6 +184,8 @@ namespace {
 
 using scat::ChanMap;
 using scat::FilterTable;
+using scat::for_each_image;
+using scat::pad_source;
 
 // ---- scratch of scat_forward_static: one array per GPU in the library's device image, for
 // callers that may not allocate.  Host code never uses the array's name as an address: the
@@ -301,6 +321,11 @@ Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
     size_t w0 = l * m_r * p.n2;                       // first order at octave 0
     size_t w2 = second ? l * l * m_r * (p.n2 >> h.res(1)) : 0;  // second order at octave 1
     L.w = (w0 > w2 ? w0 : w2) * sizeof(float);
+  } else if (p.line) {
+    // xh, u, w: half spectra of x, of the first-order moduli with children, of the outputs
+    L.xh = (n / 2 + 1) * c8;
+    for (int j = 0; second && j + 1 < h.J; ++j) L.u += h.LQ * ((n >> h.res(j)) / 2 + 1) * c8;
+    L.w = static_cast<size_t>(h.K) * ((n >> h.res(h.J)) / 2 + 1) * c8;
   } else {
     // t: see t_elems_1d; u: one octave's moduli (column spectra); v: one second-order
     // level's; w: row-pass outputs of the lowpass for all K channels
@@ -316,7 +341,7 @@ Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
     L.v = kids * c8;
     L.w = static_cast<size_t>(h.K) * (n >> h.res(h.J)) * c8;
   }
-  if (p.padded) {
+  if (p.padded && !p.line) {
     L.pad_in = n * sizeof(float);
     const size_t m_r = h.dims == 2 ? h.shape[0] >> h.res(h.J) : 1;
     L.pad_out = static_cast<size_t>(h.K) * m_r * (h.shape[1] >> h.res(h.J)) * sizeof(float);
@@ -337,6 +362,12 @@ void free_device(scat_plan *p) {
   p->d_masks64 = nullptr;
   if (p->d_rect_masks) (void)hipFree(p->d_rect_masks);
   p->d_rect_masks = nullptr;
+  if (p->d_line_masks) (void)hipFree(p->d_line_masks);
+  p->d_line_masks = nullptr;
+  if (p->d_line_tw) (void)hipFree(p->d_line_tw);
+  p->d_line_tw = nullptr;
+  if (p->d_line_list) (void)hipFree(p->d_line_list);
+  p->d_line_list = nullptr;
   if (p->d_lane_masks) (void)hipFree(p->d_lane_masks);
   p->d_lane_masks = nullptr;
   if (p->d_chan1d) (void)hipFree(p->d_chan1d);
@@ -469,9 +500,135 @@ scat_status upload_rect(scat_plan *p, std::vector<float> &pool) {
   return SCAT_OK;
 }
 
+// Does scat_line.hip serve a 1-D plan?  A node of 8192 samples takes 66 KB of LDS (two workgroups on
+// a compute unit) and twice that has no room; nodes of fewer than 32 samples and output grids of
+// fewer than 16 have no shape, more than 64 alias blocks no mask.  Where it can, it always does: 1.7
+// to 7 times as fast as the passes at 64 ... 8192 samples, batches of 1 ... 8000.
+bool line_fits(const scat::HostPlan &h, int n, int J) {
+  if (h.dims != 1 || J > scat::kLineMaxOctaves || n > 8192) return false;
+  const int fine = h.res(J - 1);
+  return n >> fine >= 32 && n >> h.res(J) >= 16 && fine <= 6;
+}
+
+int log2i(int v) {
+  int r = 0;
+  while ((1 << r) < v) ++r;
+  return r;
+}
+
+// Twiddles of every line length M = 16 ... N, at 2 M: [E][T] exp(-2 pi i e t / M), then, above 256
+// samples, those of the T-point transforms [E][T/E] exp(-2 pi i e t / T) (E = samples a thread).
+std::vector<float2> line_twiddles(int N) {
+  std::vector<float2> tw(static_cast<size_t>(4) * N);
+  const double two_pi = 6.283185307179586476925286766559;
+  for (int M = 16; M <= N; M *= 2) {
+    const int T = scat::line_block(log2i(M)), E = M / T;
+    auto fill = [&](size_t at, int cols, int period) {
+      for (int e = 0; e < E; ++e)
+        for (int t = 0; t < cols; ++t) {
+          const double ang = -two_pi * ((static_cast<long>(e) * t) % period) / period;
+          tw[at + static_cast<size_t>(e) * cols + t] =
+              make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(std::sin(ang)));
+        }
+    };
+    fill(static_cast<size_t>(2) * M, T, M);
+    if (M > 256) fill(static_cast<size_t>(3) * M, T / E, T);
+  }
+  return tw;
+}
+
+// Tables of the 1-D whole-node schedule.  Values below 1e-8 of a table's peak are left out by blocks:
+// below the rounding of a sum over the block.
+scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
+  const scat::HostPlan &h = p->host;
+  const int N = p->n1 * p->n2, J = h.J, Q = h.LQ;
+  std::vector<unsigned long long> words;
+  auto peak_of = [](const FilterTable &t) {
+    double peak = 0.0;
+    for (double v : t.v) peak = std::max(peak, std::fabs(v));
+    return peak;
+  };
+  auto push_masks = [&](const FilterTable &t, int M) {
+    const double thr = 1e-8 * peak_of(t);
+    unsigned long long m[2] = {0, 0};
+    for (size_t k = 0; k < t.v.size(); ++k)
+      if (std::fabs(t.v[k]) > thr) m[(k % M) / (M / 2)] |= 1ull << (k / M);
+    words.push_back(m[0]);
+    words.push_back(m[1]);
+  };
+  auto thread_blocks = [&](const FilterTable &t) {
+    const double thr = 1e-8 * peak_of(t);
+    const int T = scat::line_block(log2i(static_cast<int>(t.v.size())));
+    unsigned m = 0;
+    for (size_t k = 0; k < t.v.size(); ++k)
+      if (std::fabs(t.v[k]) > thr) m |= 1u << (k / T);
+    return m;
+  };
+  const int blocks = (N + 255) / 256;
+  std::vector<std::vector<int>> active(blocks);
+  for (int j = 0; j < J; ++j) {
+    p->line_mask1_off.push_back(words.size());
+    for (int q = 0; q < Q; ++q) {
+      const FilterTable &t = *h.find(1, j * Q + q, 0);
+      const size_t off = append_table(pool, t, 1, 1);
+      if (q == 0) p->line_psi1_off.push_back(off);
+      push_masks(t, N >> h.res(j));
+      const double thr = 1e-8 * peak_of(t);
+      for (int b = 0; b < blocks; ++b) {
+        bool on = false;
+        for (int k = 256 * b; k < std::min(N, 256 * (b + 1)); ++k) on = on || std::fabs(t.v[k]) > thr;
+        if (on) active[b].push_back(j * Q + q);
+      }
+    }
+  }
+  for (int j1 = 0; h.max_order == 2 && j1 + 1 < J; ++j1)
+    for (int j2 = j1 + 1; j2 < J; ++j2) {
+      const std::pair<int, int> key{h.res(j1), j2};
+      if (p->line_psi2_off.count(key) != 0) continue;
+      const FilterTable &t = *h.find(2, j2, h.res(j1));
+      p->line_psi2_off[key] = append_table(pool, t, 1, 1);
+      p->line_mask2_off[key] = words.size();
+      push_masks(t, N >> h.res(j2));
+      p->line_kid_mask[key] = thread_blocks(t);
+    }
+  for (int r = 0; r <= h.res(J - 1); ++r) {
+    const FilterTable &t = *h.find(0, 0, r);
+    p->line_phi_off.push_back(append_table(pool, t, 1, 1));
+    p->line_phi_mask.push_back(thread_blocks(t));
+    const int M = static_cast<int>(t.v.size()), m = N >> h.res(J);
+    const double thr = 1e-9 * peak_of(t);
+    int far = 0;
+    for (int k = 0; k < M; ++k)
+      if (std::fabs(t.v[k]) > thr) far = std::max(far, std::min(k, M - k));
+    int reach = 0;
+    while (reach < 64 && (2 * reach + 1) * m < 2 * far) ++reach;
+    p->line_reach.push_back(reach);
+  }
+  std::vector<int> list(blocks + 1);
+  for (int b = 0; b < blocks; ++b) {
+    list[b] = static_cast<int>(list.size());
+    list.insert(list.end(), active[b].begin(), active[b].end());
+  }
+  list[blocks] = static_cast<int>(list.size());
+  const std::vector<float2> tw = line_twiddles(N);
+  if (hipMalloc(&p->d_line_masks, words.size() * sizeof(words[0])) != hipSuccess ||
+      hipMalloc(&p->d_line_list, list.size() * sizeof(int)) != hipSuccess ||
+      hipMalloc(&p->d_line_tw, tw.size() * sizeof(float2)) != hipSuccess)
+    return SCAT_ERR_ALLOC;
+  if (hipMemcpy(p->d_line_masks, words.data(), words.size() * sizeof(words[0]), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(p->d_line_list, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(p->d_line_tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess)
+    return SCAT_ERR_DEVICE;
+  return SCAT_OK;
+}
+
 scat_status upload(scat_plan *p) {
   const scat::HostPlan &h = p->host;
   std::vector<float> pool;
+  if (p->line) {
+    const scat_status s = upload_line(p, pool);
+    if (s != SCAT_OK) return s;
+  }
   p->psi1_off.assign(h.J, 0);
   for (int j = 0; j < h.J; ++j)
     for (int l = 0; l < h.LQ; ++l) {
@@ -928,6 +1085,7 @@ scat_status create_common(scat_plan **out_plan, int dims, const int *user_shape,
   // (an oversampled plan's lowpass is wider, in output steps, than k_node_rect's filter)
   p->rect = node_kernels && p->fused && !p->tree && !p->node && oversampling == 0;
   p->node_taps = dims == 2 && oversampling == 0 && p->n1 == p->n2 && J < 31 && (p->n1 >> J) == 32;
+  p->line = node_kernels && line_fits(p->host, p->n1 * p->n2, J);
   if (padded) {
     p->padded = true;
     for (int d = 0; d < dims; ++d) {
@@ -957,14 +1115,6 @@ scat_status create_common(scat_plan **out_plan, int dims, const int *user_shape,
 // Symmetric periodic extension of `planes` signals of n_r x n_c to P_r x P_c: the margin's
 // first half mirrors the right/bottom edge, the rest mirrors the left/top edge of the next
 // period, so the periodic signal has no jump; reflections repeat with period 2n.
-__device__ __forceinline__ int pad_source(int i, int n, int P) {
-  const int h = (P - n + 1) / 2;
-  int v = i < n + h ? i : i - P;
-  v %= 2 * n;
-  if (v < 0) v += 2 * n;
-  return v < n ? v : 2 * n - 1 - v;
-}
-
 __global__ __launch_bounds__(256) void k_pad_symmetric(const float *__restrict__ in,
                                                        float *__restrict__ out, long planes,
                                                        int n_r, int n_c, int P_r, int P_c) {
@@ -1040,20 +1190,6 @@ __global__ __launch_bounds__(256) void k_uncrop(const float *__restrict__ in, fl
     const int r = static_cast<int>(t % m_r);
     const long m = t / m_r;
     out[i] = (r < o_r && c < o_c) ? in[(m * o_r + r) * o_c + c] : 0.f;
-  }
-}
-
-// Positions of the period-P extension that mirror sample r of n (see pad_source): virtual
-// positions v = r + 2 n t and v = 2 n - 1 - r + 2 n t inside [-(P - n - h), n + h), stored
-// at v (v >= 0) or v + P.  Calls f(position) for each.
-template <class Fn>
-__device__ __forceinline__ void for_each_image(int r, int n, int P, Fn f) {
-  const int h = (P - n + 1) / 2, lo = P - n - h;
-  const int reps = P / (2 * n) + 1;
-  for (int t = -reps; t <= reps; ++t) {
-    const int v0 = r + 2 * n * t, v1 = 2 * n - 1 - r + 2 * n * t;
-    if (v0 >= -lo && v0 < n + h) f(v0 >= 0 ? v0 : v0 + P);
-    if (v1 >= -lo && v1 < n + h) f(v1 >= 0 ? v1 : v1 + P);
   }
 }
 
@@ -1602,7 +1738,19 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
   const scat::HostPlan &h = p.host;
   const size_t n = static_cast<size_t>(p.n1) * p.n2, l = h.LQ, c8 = sizeof(float2);
   const bool second = h.max_order == 2 && h.J >= 2;
-  if (h.dims == 1) {
+  if (p.line) {
+    // half spectra of x and of the first-order moduli with children; gradient spectra of x, of all
+    // first-order and of all second-order nodes; half spectra of the output gradients
+    b.fwd.xh = (n / 2 + 1) * c8;
+    b.gx = n;
+    for (int j = 0; j < h.J; ++j) {
+      if (second && j + 1 < h.J) b.fwd.u += l * ((n >> h.res(j)) / 2 + 1) * c8;
+      b.gu += l * (n >> h.res(j));
+      if (second) b.ga += static_cast<size_t>(j) * l * (n >> h.res(j));
+    }
+    b.gh = static_cast<size_t>(h.K) * ((n >> h.res(h.J)) / 2 + 1);
+    b.per_plane = b.fwd.xh + b.fwd.u + (b.gx + b.gu + b.ga + b.gh) * c8;
+  } else if (h.dims == 1) {
     // forward buffers as in make_layout; gradients: x spectrum, one octave's first-order
     // spectra, one (j1, j2) level's second-order spectra, output-grid spectra
     b.fwd.xh = n * c8;
@@ -2709,6 +2857,169 @@ scat_status forward_1d(scat_plan *p, const float *in, float *out, long p0, long 
   return SCAT_OK;
 }
 
+// ---- 1-D, whole nodes (scat_line.hip): per order one launch over all nodes
+std::vector<scat::LineNodes> line_nodes(const scat_plan &p, long pc, int order, const float2 *XH, float2 *U) {
+  const scat::HostPlan &h = p.host;
+  const int J = h.J, Q = h.LQ, N = p.n1 * p.n2;
+  std::vector<scat::LineNodes> list;
+  int s2 = 1 + J * Q;
+  for (int j1 = 0; j1 < J; ++j1) {
+    const int r1 = h.res(j1), octs = J - 1 - j1;
+    if (order == 1) {
+      scat::LineNodes g{};
+      g.src = XH;
+      g.filt = p.d_tables + p.line_psi1_off[j1];
+      g.mask = p.d_line_masks + p.line_mask1_off[j1];
+      g.nodes = pc * Q;
+      g.F = Q;
+      g.base = 1 + j1 * Q;
+      g.stride = 1;
+      g.lgA = r1;
+      g.lgM = log2i(N) - r1;
+      list.push_back(g);
+    } else {
+      for (int j2 = j1 + 1; j2 < J; ++j2) {
+        const int r2 = h.res(j2);
+        scat::LineNodes g{};
+        g.src = U;
+        g.filt = p.d_tables + p.line_psi2_off.at({r1, j2});
+        g.mask = p.d_line_masks + p.line_mask2_off.at({r1, j2});
+        g.nodes = pc * Q;
+        g.F = 1;
+        g.base = s2 + (j2 - j1 - 1);
+        g.stride = octs;
+        g.lgA = r2 - r1;
+        g.lgM = log2i(N) - r2;
+        list.push_back(g);
+      }
+      s2 += Q * octs;
+      if (octs > 0) U += static_cast<size_t>(pc) * Q * ((N >> r1) / 2 + 1);
+    }
+  }
+  for (scat::LineNodes &g : list) {
+    const int r = log2i(N) - g.lgM;
+    g.G = Q;
+    g.phi = p.d_tables + p.line_phi_off[r];
+    g.phi_mask = p.line_phi_mask[r];
+    g.reach = p.line_reach[r];
+  }
+  return list;
+}
+
+scat::LineEnd line_end(const scat_plan &p, long rows, int lg, int len) {
+  scat::LineEnd e{};
+  e.rows = rows;
+  e.lg = lg;
+  e.len = len;
+  e.lgm = log2i((p.n1 * p.n2) >> p.host.res(p.host.J));
+  e.K = p.host.K;
+  e.phi = p.d_tables + p.line_phi_off[0];
+  e.reach = p.line_reach[0];
+  e.tw = p.d_line_tw;
+  return e;
+}
+
+// Half spectra of the first-order moduli go to U where there are children; low: where the half
+// spectra of the outputs go (null: not formed)
+scat_status line_first_order(const scat_plan &p, long pc, const float2 *XH, float2 *U, float2 *low, hipStream_t st) {
+  const scat::HostPlan &h = p.host;
+  const int N = p.n1 * p.n2, lgm = log2i(N >> h.res(h.J));
+  std::vector<scat::LineNodes> list = line_nodes(p, pc, 1, XH, nullptr);
+  if (h.max_order == 2)
+    for (int j = 0; j + 1 < h.J; ++j) {
+      list[j].dst = U;
+      U += static_cast<size_t>(pc) * h.LQ * ((N >> h.res(j)) / 2 + 1);
+    }
+  int n = static_cast<int>(list.size());
+  if (low == nullptr) n = h.max_order == 2 ? h.J - 1 : 0;  // nodes with children only
+  if (n > 0) SCAT_TRY(scat::launch_line_nodes(list.data(), n, low, lgm, h.K, p.d_line_tw, false, st));
+  return SCAT_OK;
+}
+
+scat_status forward_1d_line(scat_plan *p, const float *in, float *out, long p0, long pc, const Layout &lay,
+                            hipStream_t st) {
+  const scat::HostPlan &h = p->host;
+  const int N = p->n1 * p->n2, m = N >> h.res(h.J);
+  const int len = p->padded ? p->user_shape[1] : N, olen = p->padded ? p->user_out[1] : m;
+  char *base = static_cast<char *>(p->work);
+  float2 *XH = reinterpret_cast<float2 *>(base);
+  float2 *U = reinterpret_cast<float2 *>(base + lay.xh * pc);
+  float2 *TL = reinterpret_cast<float2 *>(base + (lay.xh + lay.u) * pc);
+  scat::LineEnd ie = line_end(*p, pc, log2i(N), len);
+  ie.low = TL;
+  SCAT_TRY(scat::launch_line_in(in + static_cast<size_t>(p0) * len, XH, ie, st));
+  const scat_status s = line_first_order(*p, pc, XH, U, TL, st);
+  if (s != SCAT_OK) return s;
+  if (h.max_order == 2 && h.J >= 2) {
+    const std::vector<scat::LineNodes> list = line_nodes(*p, pc, 2, nullptr, U);
+    SCAT_TRY(scat::launch_line_nodes(list.data(), static_cast<int>(list.size()), TL, log2i(m), h.K, p->d_line_tw, false,
+                                     st));
+  }
+  SCAT_TRY(scat::launch_line_out(TL, out + static_cast<size_t>(p0) * h.K * olen,
+                                 line_end(*p, pc * h.K, log2i(m), olen), st));
+  return SCAT_OK;
+}
+
+scat_status backward_1d_line(scat_plan *p, const float *in, const float *gout, float *gin, long p0, long pc,
+                             const BwdLayout &bl, hipStream_t st) {
+  const scat::HostPlan &h = p->host;
+  const int N = p->n1 * p->n2, m = N >> h.res(h.J), J = h.J, Q = h.LQ, lgm = log2i(m);
+  const int len = p->padded ? p->user_shape[1] : N, olen = p->padded ? p->user_out[1] : m;
+  char *base = static_cast<char *>(p->work);
+  float2 *XH = reinterpret_cast<float2 *>(base);
+  float2 *U = reinterpret_cast<float2 *>(base + bl.fwd.xh * pc);
+  float2 *GX = reinterpret_cast<float2 *>(base + (bl.fwd.xh + bl.fwd.u) * pc);
+  float2 *GU = GX + bl.gx * pc;
+  float2 *GA = GU + bl.gu * pc;
+  float2 *GH = GA + bl.ga * pc;
+  const bool second = h.max_order == 2 && J >= 2;
+  SCAT_TRY(scat::launch_line_in(in + static_cast<size_t>(p0) * len, XH, line_end(*p, pc, log2i(N), len), st));
+  const scat_status s = line_first_order(*p, pc, XH, U, nullptr, st);
+  if (s != SCAT_OK) return s;
+  SCAT_TRY(scat::launch_line_grad_out(gout + static_cast<size_t>(p0) * h.K * olen, GH,
+                                      line_end(*p, pc * h.K, lgm, olen), st));
+  std::vector<scat::LineNodes> first = line_nodes(*p, pc, 1, XH, nullptr);
+  std::vector<scat::LineKid> kids;
+  if (second) {
+    std::vector<scat::LineNodes> list = line_nodes(*p, pc, 2, nullptr, U);
+    size_t i = 0;
+    for (int j1 = 0; j1 + 1 < J; ++j1)
+      for (int j2 = j1 + 1; j2 < J; ++j2, ++i) {
+        const std::pair<int, int> key{h.res(j1), j2};
+        list[i].dst = GA;
+        kids.push_back(scat::LineKid{GA, p->d_tables + p->line_psi2_off.at(key), p->line_kid_mask.at(key), list[i].lgM});
+        GA += static_cast<size_t>(pc) * Q << list[i].lgM;
+      }
+    SCAT_TRY(scat::launch_line_nodes(list.data(), static_cast<int>(list.size()), GH, lgm, h.K, p->d_line_tw, true, st));
+  }
+  scat::LineSum sum{};
+  size_t kid = 0;
+  for (int j = 0; j < J; ++j) {
+    first[j].dst = GU;
+    first[j].kids = second ? J - 1 - j : 0;
+    first[j].kid = kids.data() + kid;
+    kid += first[j].kids;
+    sum.g[j] = GU;
+    sum.lgM[j] = first[j].lgM;
+    GU += static_cast<size_t>(pc) * Q << first[j].lgM;
+  }
+  SCAT_TRY(scat::launch_line_nodes(first.data(), J, GH, lgm, h.K, p->d_line_tw, true, st));
+  sum.dst = GX;
+  sum.gh = GH;
+  sum.phi = p->d_tables + p->line_phi_off[0];
+  sum.filt = p->d_tables + p->line_psi1_off[0];
+  sum.list = p->d_line_list;
+  sum.signals = pc;
+  sum.lgN = log2i(N);
+  sum.lgm = lgm;
+  sum.K = h.K;
+  sum.J = J;
+  sum.Q = Q;
+  SCAT_TRY(scat::launch_line_sum(sum, st));
+  SCAT_TRY(scat::launch_line_grad_in(GX, gin + static_cast<size_t>(p0) * len, line_end(*p, pc, log2i(N), len), st));
+  return SCAT_OK;
+}
+
 // Makes the plan's scratch buffer at least `need` bytes (growing it synchronises the device).
 scat_status ensure_scratch(scat_plan *plan, size_t need) {
   plan->work = plan->d_scratch;
@@ -2827,6 +3138,11 @@ scat_status forward_chunks(scat_plan *plan, const float *in, float *out, long ba
   const scat::HostPlan &h = plan->host;
   for (long p0 = 0; p0 < batch; p0 += lay.chunk) {
     long pc = batch - p0 < lay.chunk ? batch - p0 : lay.chunk;
+    if (plan->line) {
+      const scat_status s = forward_1d_line(plan, in, out, p0, pc, lay, st);
+      if (s != SCAT_OK) return s;
+      continue;
+    }
     const float *cin = in;
     float *cout = out;
     long cp0 = p0;
@@ -3012,6 +3328,11 @@ scat_status scat_backward(scat_plan *plan, const float *in, const float *grad_ou
   CallScope scope(plan, true);
   for (long p0 = 0; p0 < batch; p0 += bl.chunk) {
     long pc = batch - p0 < bl.chunk ? batch - p0 : bl.chunk;
+    if (plan->line) {
+      const scat_status s = backward_1d_line(plan, in, grad_out, grad_in, p0, pc, bl, st);
+      if (s != SCAT_OK) return s;
+      continue;
+    }
     if (!plan->padded) {
       scat_status s = h.dims == 1 ? backward_1d(plan, in, grad_out, grad_in, p0, pc, bl, st)
                                   : backward_2d(plan, in, grad_out, grad_in, p0, pc, bl, st);

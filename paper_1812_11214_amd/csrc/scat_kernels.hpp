@@ -411,4 +411,60 @@ hipError_t launch3_sqrt(const float *acc, float2 *out, long total, hipStream_t s
 hipError_t launch3_sample(const float2 *src, float *out, long volumes, int K, int chan, int n0,
                           int n1, int n2, int J, hipStream_t st);
 
+// ---- 1-D plans of at most 8192 samples, whole nodes (scat_line.hip).  Spectra in natural order;
+// half spectra are [M/2+1].
+constexpr int kLineMaxSegs = 28;    // pairs of octaves
+constexpr int kLineMaxOctaves = 8;
+struct LineKid {
+  const float2 *g;    // [nodes][1 << lgM] gradient spectra of the children, numbered as their parents
+  const float *filt;  // their wavelet on the parent's grid
+  unsigned mask;      // blocks of line_block(parent's lgM) values on which it is not negligible
+  int lgM;
+};
+// `nodes` nodes of 1 << lgM samples: wavelet node % F on source node / F, whose half spectra have
+// 1 << (lgM + lgA) samples; output channel base + (node % G) stride of signal node / G
+struct LineNodes {
+  const float2 *src;
+  const float *filt;
+  const unsigned long long *mask;  // per wavelet two words: alias blocks in use by either half of the node
+  const float *phi;
+  float2 *dst;  // forward: half spectra for the children (or null); adjoint: gradient spectra
+  long nodes;
+  int F, G, base, stride, lgM, lgA, reach;
+  unsigned phi_mask;   // as LineKid::mask
+  const LineKid *kid;  // adjoint
+  int kids;
+};
+int line_block(int lgM);  // samples between two that a thread holds
+// low [signals][K][(1 << lgm)/2+1]: the outputs' half spectra, written (null: not formed), or with
+// `back` those of the output gradients, read
+hipError_t launch_line_nodes(const LineNodes *list, int n, float2 *low, int lgm, int K, const float2 *tw, bool back,
+                             hipStream_t st);
+// transforms of `rows` lines of 1 << lg samples, of which `len` are the caller's
+struct LineEnd {
+  long rows;
+  int lg, len;
+  float2 *low;  // launch_line_in: also the half spectrum of channel 0, or null
+  const float *phi;
+  int lgm, K, reach;
+  const float2 *tw;
+};
+hipError_t launch_line_in(const float *x, float2 *spec, const LineEnd &e, hipStream_t st);
+hipError_t launch_line_out(const float2 *spec, float *out, const LineEnd &e, hipStream_t st);
+hipError_t launch_line_grad_out(const float *g, float2 *spec, const LineEnd &e, hipStream_t st);
+hipError_t launch_line_grad_in(const float2 *spec, float *out, const LineEnd &e, hipStream_t st);
+struct LineSum {
+  float2 *dst;
+  const float2 *gh;
+  const float *phi, *filt;
+  // per block of 256 frequencies the first-order wavelets in use: the blocks' starts in `list`
+  // (one more than there are blocks), then the wavelets
+  const int *list;
+  const float2 *g[kLineMaxOctaves];
+  int lgM[kLineMaxOctaves];
+  long signals;
+  int lgN, lgm, K, J, Q;
+};
+hipError_t launch_line_sum(const LineSum &s, hipStream_t st);
+
 }  // namespace scat
