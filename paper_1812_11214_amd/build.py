@@ -13,7 +13,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libscat.so")
 SOURCES = ("scat_host.cpp", "scat_host3d.cpp", "scat_kernels.hip", "scat_tree.hip", "scat_node.hip",
-           "scat_rect.hip", "scat_line.hip", "scat_backward.hip", "scat_3d.hip", "scat_capi.hip")
+           "scat_rect.hip", "scat_line.hip", "scat_plane.hip",
+           "scat_backward.hip", "scat_3d.hip", "scat_capi.hip")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]

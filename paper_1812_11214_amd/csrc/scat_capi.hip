@@ -160,6 +160,12 @@ struct scat_plan {
   std::vector<int> line_reach;  // per resolution: phi is negligible beyond reach + 1/2 output bands
   float2 *d_line_tw = nullptr;  // see line_twiddles
   int *d_line_list = nullptr;   // see LineSum
+  // 2-D: the backward pass runs on whole-node kernels (scat_plane.hip).  (source resolution, octave)
+  // -> L triples of words in d_plane_masks (see PlaneNodes), and the list of PlaneSum.
+  bool plane = false;
+  unsigned long long *d_plane_masks = nullptr;
+  std::map<std::pair<int, int>, size_t> plane_mask_off;
+  int *d_plane_list = nullptr;
   // 3-D solid harmonic plans (host.dims == 3; host carries J, LQ = L, max_order, K only)
   scat::HostPlan3D h3;
   std::vector<size_t> psi3_off;  // per (j, l): its 2l+1 tables, contiguous
@@ -368,6 +374,10 @@ void free_device(scat_plan *p) {
   p->d_line_tw = nullptr;
   if (p->d_line_list) (void)hipFree(p->d_line_list);
   p->d_line_list = nullptr;
+  if (p->d_plane_masks) (void)hipFree(p->d_plane_masks);
+  p->d_plane_masks = nullptr;
+  if (p->d_plane_list) (void)hipFree(p->d_plane_list);
+  p->d_plane_list = nullptr;
   if (p->d_lane_masks) (void)hipFree(p->d_lane_masks);
   p->d_lane_masks = nullptr;
   if (p->d_chan1d) (void)hipFree(p->d_chan1d);
@@ -622,9 +632,69 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
   return SCAT_OK;
 }
 
+// Does scat_plane.hip serve the backward pass of a 2-D plan?  Every grid of the cascade has to be one of
+// its shapes and an alias mask one word.  Where it can, it always does: 1.03 (128 x 128, J = 2) to 2.5
+// times (one plane of 32 x 32) as fast as the passes.
+bool plane_fits(const scat::HostPlan &h, int n1, int n2) {
+  if (h.dims != 2 || h.J > scat::kPlaneMaxOctaves || h.res(h.J - 1) > 3) return false;
+  for (int j = 0; j < h.J; ++j)
+    if (!scat::plane_supported(n1 >> h.res(j), n2 >> h.res(j))) return false;
+  return true;
+}
+
+// Which blocks of the wavelets matter (1e-8 of the peak, below the rounding of a sum over a block).
+scat_status upload_plane(scat_plan *p) {
+  const scat::HostPlan &h = p->host;
+  std::vector<unsigned long long> words;
+  const int blocks = p->n1 * p->n2 / 256;
+  std::vector<std::vector<int>> active(blocks);
+  for (int j = 0; j < h.J; ++j)
+    for (int j1 = -1; j1 < (h.max_order == 2 ? j : 0); ++j1) {
+      const int r = j1 < 0 ? 0 : h.res(j1);
+      if (p->plane_mask_off.count({r, j}) != 0) continue;
+      const int Sr = p->n1 >> r, Sc = p->n2 >> r, rows = p->n1 >> h.res(j), cols = p->n2 >> h.res(j);
+      const int A = 1 << (h.res(j) - r);
+      p->plane_mask_off[{r, j}] = words.size();
+      for (int l = 0; l < h.LQ; ++l) {
+        const FilterTable &t = *h.find(r == 0 ? 1 : 2, j * h.LQ + l, r);
+        double peak = 0.0;
+        for (double v : t.v) peak = std::max(peak, std::fabs(v));
+        unsigned long long m[3] = {0, 0, 0};
+        for (int kr = 0; kr < Sr; ++kr)
+          for (int kc = 0; kc < Sc; ++kc) {
+            if (std::fabs(t.v[static_cast<size_t>(kr) * Sc + kc]) <= 1e-8 * peak) continue;
+            m[(kr % rows) / (rows / 2)] |= 1ull << (kr / rows * A + kc / cols);
+            m[2] |= 1ull << (kr / (Sr / 16));
+            if (r == 0) {
+              std::vector<int> &on = active[(kr * Sc + kc) / 256];
+              if (on.empty() || on.back() != j * h.LQ + l) on.push_back(j * h.LQ + l);
+            }
+          }
+        words.insert(words.end(), m, m + 3);
+      }
+    }
+  std::vector<int> list(blocks + 1);
+  for (int b = 0; b < blocks; ++b) {
+    list[b] = static_cast<int>(list.size());
+    list.insert(list.end(), active[b].begin(), active[b].end());
+  }
+  list[blocks] = static_cast<int>(list.size());
+  if (hipMalloc(&p->d_plane_masks, words.size() * sizeof(words[0])) != hipSuccess ||
+      hipMalloc(&p->d_plane_list, list.size() * sizeof(int)) != hipSuccess)
+    return SCAT_ERR_ALLOC;
+  if (hipMemcpy(p->d_plane_masks, words.data(), words.size() * sizeof(words[0]), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(p->d_plane_list, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+    return SCAT_ERR_DEVICE;
+  return SCAT_OK;
+}
+
 scat_status upload(scat_plan *p) {
   const scat::HostPlan &h = p->host;
   std::vector<float> pool;
+  if (p->plane) {
+    const scat_status s = upload_plane(p);
+    if (s != SCAT_OK) return s;
+  }
   if (p->line) {
     const scat_status s = upload_line(p, pool);
     if (s != SCAT_OK) return s;
@@ -1085,6 +1155,7 @@ scat_status create_common(scat_plan **out_plan, int dims, const int *user_shape,
   // (an oversampled plan's lowpass is wider, in output steps, than k_node_rect's filter)
   p->rect = node_kernels && p->fused && !p->tree && !p->node && oversampling == 0;
   p->node_taps = dims == 2 && oversampling == 0 && p->n1 == p->n2 && J < 31 && (p->n1 >> J) == 32;
+  p->plane = node_kernels && plane_fits(p->host, p->n1, p->n2);
   p->line = node_kernels && line_fits(p->host, p->n1 * p->n2, J);
   if (padded) {
     p->padded = true;
@@ -1776,7 +1847,12 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
                   b.pad_floats * sizeof(float);
   } else {
     const size_t t1 = l * n, t2 = second ? l * l * (n >> (2 * h.res(1))) : 0;
-    if (p.fused) {
+    if (p.plane) {
+      // half spectra of x and of the first-order moduli with children
+      auto half = [&](int r) { return static_cast<size_t>((p.n1 >> r) / 2 + 1) * (p.n2 >> r) * c8; };
+      b.fwd.xh = half(0);
+      for (int j = 0; second && j + 1 < h.J; ++j) b.fwd.u += l * half(h.res(j));
+    } else if (p.fused) {
       // buffers of the fused forward schedule (see make_layout)
       size_t ft1 = 0, ft2 = 0;
       for (int j = 0; j < h.J; ++j) ft1 += l * (n >> (2 * h.res(j)));
@@ -1791,7 +1867,7 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
       b.fwd.t = (t1 > t2 ? t1 : t2) * c8;
       b.fwd.u = second ? l * n * c8 : 0;
     }
-    b.tape = make_tape(p);
+    if (!p.plane) b.tape = make_tape(p);
     b.gx = n;
     // spectra of the output-grid gradient planes of one launch (at most L*L, or L, nodes)
     const size_t mm = static_cast<size_t>(p.n1 >> h.res(h.J)) * (p.n2 >> h.res(h.J));
@@ -1802,6 +1878,7 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
     for (int j = 0; j < h.J; ++j) b.gu += l * (n >> (2 * h.res(j)));
     for (int j = 1; second && j < h.J; ++j) b.ga += l * l * (n >> (2 * h.res(j)));
     b.gh += (l + 1) * mm;
+    if (p.plane) b.gh = static_cast<size_t>(h.K) * mm;  // all channels at once
     if (p.padded)
       b.pad_floats = 2 * n + static_cast<size_t>(h.K) * (p.n1 >> h.res(h.J)) * (p.n2 >> h.res(h.J));
     b.per_plane = b.fwd.xh + b.fwd.t + b.fwd.u + b.fwd.v +
@@ -1953,8 +2030,106 @@ scat_status backward_2d_rows_adjoint(scat_plan *p, const float *go, float *gi, l
   return SCAT_OK;
 }
 
+// ---- backward pass on whole-node kernels (scat_plane.hip): first-order nodes with children again,
+// then the adjoints of the second-order nodes of one parent octave and of that octave's nodes
+scat_status backward_2d_plane(scat_plan *p, const float *x, const float *go, float *gi, long pc, const BwdLayout &bl,
+                              hipStream_t st) {
+  const scat::HostPlan &h = p->host;
+  const int J = h.J, L = h.LQ, K = h.K, Nr = p->n1, Nc = p->n2;
+  const int rJ = h.res(J), m_r = Nr >> rJ, m_c = Nc >> rJ;
+  const bool second = h.max_order == 2 && J >= 2;
+  char *base = static_cast<char *>(p->work);
+  float2 *XH = reinterpret_cast<float2 *>(base);
+  float2 *U = reinterpret_cast<float2 *>(base + bl.fwd.xh * pc);
+  float2 *GX = reinterpret_cast<float2 *>(base + (bl.fwd.xh + bl.fwd.u) * pc);
+  float2 *GU = GX + bl.gx * pc;
+  float2 *GA = GU + bl.gu * pc;
+  float2 *GH = GA + bl.ga * pc;
+  const float *tab = p->d_tables;
+  const float2 *tw = p->d_tw;
+  const int tw_n = p->tw_n;
+  SCAT_TRY(scat::launch_plane_in(x, XH, pc, Nr, Nc, tw, tw_n, st));
+  SCAT_TRY(scat::launch_small_fft2(go, pc * K, ChanMap{K, K, 0, 0}, K, m_r, m_c, GH, tw, tw_n, st));
+  // the nodes of octave j under sources of resolution r
+  auto nodes = [&](const float2 *src, long ns, int r, int j, size_t filt) {
+    scat::PlaneNodes n{};
+    const int rj = h.res(j);
+    n.src = src;
+    n.NS = ns;
+    n.N1 = Nr >> rj;
+    n.N2 = Nc >> rj;
+    n.A = 1 << (rj - r);
+    n.filt = tab + filt;
+    n.F = L;
+    n.mask = p->d_plane_masks + p->plane_mask_off.at({r, j});
+    n.gh = GH;
+    n.phi_r = tab + p->phi_rows_off[rj];
+    n.phi_c = tab + p->phi_cols_off[rj];
+    n.m_r = m_r;
+    n.m_c = m_c;
+    n.G = 1;
+    n.K = K;
+    n.L = L;
+    n.tw = tw;
+    n.tw_n = tw_n;
+    return n;
+  };
+  scat::PlaneSum sum{};
+  int s2_base = 1 + J * L;
+  for (int j1 = 0; j1 < J; ++j1) {
+    const int r1 = h.res(j1), octs = J - 1 - j1;
+    const int M1r = Nr >> r1, M1c = Nc >> r1;
+    scat::PlaneNodes first = nodes(XH, pc, 0, j1, p->psi1_off[j1]);
+    if (second && octs > 0) {
+      first.dst = U;
+      SCAT_TRY(scat::launch_plane_nodes(first, false, st));
+      float2 *GAj = GA;
+      for (int j2 = j1 + 1; j2 < J; ++j2) {
+        const int M2r = Nr >> h.res(j2), M2c = Nc >> h.res(j2);
+        scat::PlaneNodes kid = nodes(U, pc * L, r1, j2, p->psi2_off.at({r1, j2}));
+        kid.dst = GAj;
+        kid.G = L;
+        kid.chan_base = s2_base + (j2 - j1 - 1) * L;
+        kid.chan_src = octs * L;
+        SCAT_TRY(scat::launch_plane_nodes(kid, true, st));
+        first.kid[first.kids++] = scat::PlaneKidNodes{GAj, kid.filt, kid.mask, M2r, M2c};
+        GAj += static_cast<size_t>(pc) * L * L * M2r * M2c;
+      }
+      s2_base += L * L * octs;
+      U += static_cast<size_t>(pc) * L * (M1r / 2 + 1) * M1c;
+    }
+    first.dst = GU;
+    first.chan_base = 1 + j1 * L;
+    SCAT_TRY(scat::launch_plane_nodes(first, true, st));
+    sum.g[j1] = GU;
+    sum.res[j1] = r1;
+    GU += static_cast<size_t>(pc) * L * M1r * M1c;
+  }
+  sum.dst = GX;
+  sum.gh = GH;
+  sum.phi_r = tab + p->phi_rows_off[0];
+  sum.phi_c = tab + p->phi_cols_off[0];
+  sum.filt = tab + p->psi1_off[0];
+  sum.list = p->d_plane_list;
+  sum.planes = pc;
+  sum.N1 = Nr;
+  sum.N2 = Nc;
+  sum.m_r = m_r;
+  sum.m_c = m_c;
+  sum.K = K;
+  sum.J = J;
+  sum.L = L;
+  SCAT_TRY(scat::launch_plane_sum(sum, st));
+  SCAT_TRY(scat::launch_plane_real(GX, gi, pc, Nr, Nc, tw, tw_n, st));
+  return SCAT_OK;
+}
+
 scat_status backward_2d(scat_plan *p, const float *in, const float *gout, float *gin, long p0,
                         long pc, BwdLayout &bl, hipStream_t st) {
+  if (p->plane) {
+    const size_t n0 = static_cast<size_t>(p->n1) * p->n2, mm = n0 >> (2 * p->host.res(p->host.J));
+    return backward_2d_plane(p, in + p0 * n0, gout + p0 * p->host.K * mm, gin + p0 * n0, pc, bl, st);
+  }
   const scat::HostPlan &h = p->host;
   const int J = h.J, L = h.LQ, K = h.K;
   const int Nr = p->n1, Nc = p->n2;

@@ -411,6 +411,53 @@ hipError_t launch3_sqrt(const float *acc, float2 *out, long total, hipStream_t s
 hipError_t launch3_sample(const float2 *src, float *out, long volumes, int K, int chan, int n0,
                           int n1, int n2, int J, hipStream_t st);
 
+// ---- backward pass of 2-D plans whose every node is one workgroup (scat_plane.hip)
+constexpr int kPlaneMaxOctaves = 8;
+struct PlaneKidNodes {
+  const float2 *g;                 // [nodes][L][Mr][Mc] gradient spectra of the children
+  const float *filt;               // their L wavelets on the parent's grid
+  const unsigned long long *mask;  // as PlaneNodes::mask
+  int Mr, Mc;
+};
+// NS * F nodes of N1 x N2 points: wavelet node % F on source node / F of A N1 x A N2 points
+struct PlaneNodes {
+  const float2 *src;  // [NS][A N1 / 2 + 1][A N2]
+  long NS;
+  int N1, N2, A;
+  const float *filt;
+  int F;
+  // per wavelet three words: the alias blocks (bit a_r A + a_c) in use by the upper and by the lower
+  // half of the node's rows; the sixteenths of the source's rows in use
+  const unsigned long long *mask;
+  float2 *dst;  // half spectra of the moduli; adjoint: gradient spectra
+  // adjoint: spectra of the output gradients [planes][K][m_r][m_c], phi's factors; node of source s
+  // and wavelet f: channel chan_base + (s % G) chan_src + f of plane s / G
+  const float2 *gh;
+  const float *phi_r, *phi_c;
+  int m_r, m_c, G, chan_base, chan_src, K, L;
+  PlaneKidNodes kid[kPlaneMaxOctaves];
+  int kids;
+  const float2 *tw;
+  int tw_n;
+};
+bool plane_supported(int N1, int N2);
+hipError_t launch_plane_nodes(const PlaneNodes &n, bool back, hipStream_t st);
+hipError_t launch_plane_in(const float *x, float2 *spec, long planes, int N1, int N2, const float2 *tw, int tw_n,
+                           hipStream_t st);
+hipError_t launch_plane_real(const float2 *spec, float *out, long planes, int N1, int N2, const float2 *tw, int tw_n,
+                             hipStream_t st);
+struct PlaneSum {
+  float2 *dst;
+  const float2 *gh;
+  const float *phi_r, *phi_c, *filt;
+  const int *list;  // as LineSum::list, blocks of 256 points of the plane
+  const float2 *g[kPlaneMaxOctaves];
+  int res[kPlaneMaxOctaves];
+  long planes;
+  int N1, N2, m_r, m_c, K, J, L;
+};
+hipError_t launch_plane_sum(const PlaneSum &s, hipStream_t st);
+
 // ---- 1-D plans of at most 8192 samples, whole nodes (scat_line.hip).  Spectra in natural order;
 // half spectra are [M/2+1].
 constexpr int kLineMaxSegs = 28;    // pairs of octaves

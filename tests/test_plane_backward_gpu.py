@@ -1,0 +1,89 @@
+"""Whole-node backward kernels of 2-D plans (k_plane_nodes): every node shape, node counts that do not
+fill a workgroup, padded, oversampled and first-order plans, against the oracle in 64 bits and against
+the pass kernels of the same plan."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1812_11214_amd as scat
+
+pytestmark = pytest.mark.gpu
+
+
+def run(shape, J, L, max_order, x, g, padded, o, **kw):
+    plan = scat.Scattering(shape, J, L, max_order, padded=padded, oversampling=o, **kw)
+    try:
+        gd = torch.from_numpy(g((plan.K,) + plan.out_shape)).cuda()
+        plan.timing_begin(None)
+        gi = plan.backward(torch.from_numpy(x).cuda(), gd)
+        torch.cuda.synchronize()
+        return gi.cpu().numpy(), set(plan.timing_end()), gd.cpu().numpy()
+    finally:
+        plan.close()
+
+
+def rel(a, b):
+    return np.linalg.norm(a.astype(np.float64) - b) / np.linalg.norm(b)
+
+
+@pytest.mark.parametrize("shape,J,L,max_order,padded,o,batch", [
+    ((32, 32), 2, 8, 2, False, 0, 3),    # a last workgroup that is not full
+    ((64, 64), 3, 3, 2, False, 0, 2),    # 64, 32 and 16 a side
+    ((64, 128), 3, 2, 2, False, 0, 1),   # wide
+    ((128, 64), 2, 1, 2, False, 0, 5),   # tall; one angle
+    ((128, 128), 3, 4, 2, False, 0, 1),  # octave 0 fills a compute unit
+    ((128, 128), 4, 2, 2, False, 0, 2),
+    ((64, 32), 2, 5, 1, False, 0, 2),    # first order only
+    ((32, 64), 1, 4, 2, False, 0, 2),    # no children
+    ((64, 64), 3, 2, 2, False, 2, 2),    # oversampled: octaves of one size
+    ((28, 27), 2, 8, 2, True, 0, 3),
+    ((50, 33), 2, 3, 2, True, 0, 2),
+])
+def test_plane_backward(shape, J, L, max_order, padded, o, batch):
+    rng = np.random.default_rng(shape[0] * 1000 + shape[1] * 10 + J + o)
+    x = rng.standard_normal((batch,) + shape).astype(np.float32)
+    seed = int(rng.integers(1 << 30))
+
+    def g(per):
+        return np.random.default_rng(seed).standard_normal((batch,) + per).astype(np.float32)
+
+    print("plane", shape, J, L, max_order, padded, o, flush=True)
+    got, names, gg = run(shape, J, L, max_order, x, g, padded, o)
+    assert any(s.startswith("k_plane_nodes<") for s in names), names
+    old, names, _ = run(shape, J, L, max_order, x, g, padded, o, node_kernels=False)
+    assert not any(s.startswith("k_plane_") for s in names), names
+    if padded:
+        want = oracle.scattering2d_padded_backward(x.astype(np.float64), gg.astype(np.float64), J, L, max_order)
+    else:
+        want = oracle.scattering2d_backward(x.astype(np.float64), gg.astype(np.float64), J, L, max_order,
+                                            oversampling=o)
+    for p in range(batch):
+        new, before = rel(got[p], want[p]), rel(old[p], want[p])
+        mid, mid_before = median(got[p], want[p]), median(old[p], want[p])
+        print(p, new, before, mid, mid_before, flush=True)
+        # Through y / |y| the rounding of y (3e-7 of its r.m.s.) becomes a phase error of 3e-7 / rho at a
+        # sample of rho r.m.s.; of N samples of noise one has rho < N^-1/2 / 10 in a hundred planes, which
+        # alone moves the gradient by 3e-6 in relative L2 (in either schedule, by its own rounding: no
+        # bound on their ratio).  So the L2 bar is 1e-5, and the median over the pixels, which such a
+        # sample does not reach, is held to the rounding of nine chained transforms.
+        assert new <= 1e-5, (p, new, before)
+        assert mid <= max(3e-7, 1.5 * mid_before), (p, mid, mid_before)
+
+
+def median(a, b):
+    return np.median(np.abs(a.astype(np.float64) - b)) / np.sqrt(np.mean(b ** 2))
+
+
+def test_grids_out_of_range_keep_the_passes():
+    for shape, J in (((32, 32), 3), ((256, 128), 2), ((128, 32), 2)):
+        plan = scat.Scattering(shape, J, 2, 2)
+        try:
+            x = torch.randn((1,) + shape, device="cuda")
+            g = torch.randn((1, plan.K) + plan.out_shape, device="cuda")
+            plan.timing_begin(None)
+            plan.backward(x, g)
+            torch.cuda.synchronize()
+            assert not any(s.startswith("k_plane_") for s in plan.timing_end())
+        finally:
+            plan.close()
