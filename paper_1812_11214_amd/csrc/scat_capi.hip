@@ -158,7 +158,7 @@ struct scat_plan {
   std::map<std::pair<int, int>, unsigned> line_kid_mask;
   std::vector<unsigned> line_phi_mask;
   std::vector<int> line_reach;  // per resolution: phi is negligible beyond reach + 1/2 output bands
-  float2 *d_line_tw = nullptr;  // see line_twiddles
+  // (d_tw: see line_twiddles)
   int *d_line_list = nullptr;   // see LineSum
   // 2-D: the backward pass runs on whole-node kernels (scat_plane.hip).  (source resolution, octave)
   // -> L triples of words in d_plane_masks (see PlaneNodes), and the list of PlaneSum.
@@ -274,6 +274,22 @@ size_t kids_elems_1d(const scat::HostPlan &h, size_t n) {
   return all;
 }
 
+// Can k_node_rect compute the nodes of octave j of a plan from sources of resolution r?
+bool rect_node_fits(const scat_plan &p, int r, int j) {
+  const scat::HostPlan &h = p.host;
+  const int rj = h.res(j);
+  return p.rect && scat::node_rect_supported(p.n1 >> rj, p.n2 >> rj, 1 << (rj - r), 1 << (h.res(h.J) - rj));
+}
+
+// Does it compute all nodes of the plan?  (then no row-pass output is ever stored)
+bool rect_everywhere(const scat_plan &p) {
+  const scat::HostPlan &h = p.host;
+  for (int j = 0; j < h.J; ++j)
+    for (int j1 = -1; j1 < (h.max_order == 2 ? j : 0); ++j1)
+      if (!rect_node_fits(p, j1 < 0 ? 0 : h.res(j1), j)) return false;
+  return true;
+}
+
 // budget: bytes of scratch one chunk may use (0 = scratch_budget())
 Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
   Layout L;
@@ -316,6 +332,10 @@ Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
     size_t w0 = l * m_r * p.n2;
     size_t w2 = second ? l * l * m_r * (p.n2 >> h.res(1)) : 0;
     L.w = (w0 > w2 ? w0 : w2) * sizeof(float);
+    if (rect_everywhere(p)) {
+      L.t = L.v = 0;
+      L.w = m_r * p.n2 * sizeof(float);  // S0 only
+    }
   } else if (h.dims == 2) {
     const size_t l = h.LQ;
     L.xh = n * c8;
@@ -370,8 +390,6 @@ void free_device(scat_plan *p) {
   p->d_rect_masks = nullptr;
   if (p->d_line_masks) (void)hipFree(p->d_line_masks);
   p->d_line_masks = nullptr;
-  if (p->d_line_tw) (void)hipFree(p->d_line_tw);
-  p->d_line_tw = nullptr;
   if (p->d_line_list) (void)hipFree(p->d_line_list);
   p->d_line_list = nullptr;
   if (p->d_plane_masks) (void)hipFree(p->d_plane_masks);
@@ -448,13 +466,6 @@ size_t append_vec(std::vector<float> &pool, const std::vector<double> &v) {
   return off;
 }
 
-// Can k_node_rect compute the nodes of octave j of a plan from sources of resolution r?
-bool rect_node_fits(const scat_plan &p, int r, int j) {
-  const scat::HostPlan &h = p.host;
-  const int rj = h.res(j);
-  return p.rect && scat::node_rect_supported(p.n1 >> rj, p.n2 >> rj, 1 << (rj - r), 1 << (h.res(h.J) - rj));
-}
-
 // Tables of k_node_rect: which alias-block halves of every wavelet are in use (1e-8 of the peak,
 // below the rounding of a sum over the block), and the lowpass as spatial taps.
 scat_status upload_rect(scat_plan *p, std::vector<float> &pool) {
@@ -529,17 +540,15 @@ int log2i(int v) {
 // Twiddles of every line length M = 16 ... N, at 2 M: [E][T] exp(-2 pi i e t / M), then, above 256
 // samples, those of the T-point transforms [E][T/E] exp(-2 pi i e t / T) (E = samples a thread).
 std::vector<float2> line_twiddles(int N) {
-  std::vector<float2> tw(static_cast<size_t>(4) * N);
+  std::vector<float2> tw(static_cast<size_t>(4) * N), unit(N);
   const double two_pi = 6.283185307179586476925286766559;
+  for (int k = 0; k < N; ++k)
+    unit[k] = make_float2(static_cast<float>(std::cos(two_pi * k / N)), static_cast<float>(-std::sin(two_pi * k / N)));
   for (int M = 16; M <= N; M *= 2) {
     const int T = scat::line_block(log2i(M)), E = M / T;
     auto fill = [&](size_t at, int cols, int period) {
       for (int e = 0; e < E; ++e)
-        for (int t = 0; t < cols; ++t) {
-          const double ang = -two_pi * ((static_cast<long>(e) * t) % period) / period;
-          tw[at + static_cast<size_t>(e) * cols + t] =
-              make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(std::sin(ang)));
-        }
+        for (int t = 0; t < cols; ++t) tw[at + static_cast<size_t>(e) * cols + t] = unit[e * t % period * (N / period)];
     };
     fill(static_cast<size_t>(2) * M, T, M);
     if (M > 256) fill(static_cast<size_t>(3) * M, T / E, T);
@@ -558,20 +567,24 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
     for (double v : t.v) peak = std::max(peak, std::fabs(v));
     return peak;
   };
-  auto push_masks = [&](const FilterTable &t, int M) {
-    const double thr = 1e-8 * peak_of(t);
+  // does any of values [k, k + n) of a table exceed thr?
+  auto above = [](const FilterTable &t, size_t k, size_t n, double thr) {
+    for (size_t i = k; i < k + n; ++i)
+      if (std::fabs(t.v[i]) > thr) return true;
+    return false;
+  };
+  auto push_masks = [&](const FilterTable &t, size_t M, double thr) {
     unsigned long long m[2] = {0, 0};
-    for (size_t k = 0; k < t.v.size(); ++k)
-      if (std::fabs(t.v[k]) > thr) m[(k % M) / (M / 2)] |= 1ull << (k / M);
+    for (size_t k = 0; k < t.v.size(); k += M / 2)
+      if (above(t, k, M / 2, thr)) m[k % M / (M / 2)] |= 1ull << (k / M);
     words.push_back(m[0]);
     words.push_back(m[1]);
   };
-  auto thread_blocks = [&](const FilterTable &t) {
-    const double thr = 1e-8 * peak_of(t);
+  auto thread_blocks = [&](const FilterTable &t, double thr) {
     const int T = scat::line_block(log2i(static_cast<int>(t.v.size())));
     unsigned m = 0;
-    for (size_t k = 0; k < t.v.size(); ++k)
-      if (std::fabs(t.v[k]) > thr) m |= 1u << (k / T);
+    for (size_t k = 0; k < t.v.size(); k += T)
+      if (above(t, k, T, thr)) m |= 1u << (k / T);
     return m;
   };
   const int blocks = (N + 255) / 256;
@@ -582,13 +595,10 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
       const FilterTable &t = *h.find(1, j * Q + q, 0);
       const size_t off = append_table(pool, t, 1, 1);
       if (q == 0) p->line_psi1_off.push_back(off);
-      push_masks(t, N >> h.res(j));
       const double thr = 1e-8 * peak_of(t);
-      for (int b = 0; b < blocks; ++b) {
-        bool on = false;
-        for (int k = 256 * b; k < std::min(N, 256 * (b + 1)); ++k) on = on || std::fabs(t.v[k]) > thr;
-        if (on) active[b].push_back(j * Q + q);
-      }
+      push_masks(t, N >> h.res(j), thr);
+      for (int b = 0; b < blocks; ++b)
+        if (above(t, 256 * b, std::min(256, N - 256 * b), thr)) active[b].push_back(j * Q + q);
     }
   }
   for (int j1 = 0; h.max_order == 2 && j1 + 1 < J; ++j1)
@@ -598,15 +608,16 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
       const FilterTable &t = *h.find(2, j2, h.res(j1));
       p->line_psi2_off[key] = append_table(pool, t, 1, 1);
       p->line_mask2_off[key] = words.size();
-      push_masks(t, N >> h.res(j2));
-      p->line_kid_mask[key] = thread_blocks(t);
+      const double thr = 1e-8 * peak_of(t);
+      push_masks(t, N >> h.res(j2), thr);
+      p->line_kid_mask[key] = thread_blocks(t, thr);
     }
   for (int r = 0; r <= h.res(J - 1); ++r) {
     const FilterTable &t = *h.find(0, 0, r);
     p->line_phi_off.push_back(append_table(pool, t, 1, 1));
-    p->line_phi_mask.push_back(thread_blocks(t));
     const int M = static_cast<int>(t.v.size()), m = N >> h.res(J);
     const double thr = 1e-9 * peak_of(t);
+    p->line_phi_mask.push_back(thread_blocks(t, thr));
     int far = 0;
     for (int k = 0; k < M; ++k)
       if (std::fabs(t.v[k]) > thr) far = std::max(far, std::min(k, M - k));
@@ -620,14 +631,11 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
     list.insert(list.end(), active[b].begin(), active[b].end());
   }
   list[blocks] = static_cast<int>(list.size());
-  const std::vector<float2> tw = line_twiddles(N);
   if (hipMalloc(&p->d_line_masks, words.size() * sizeof(words[0])) != hipSuccess ||
-      hipMalloc(&p->d_line_list, list.size() * sizeof(int)) != hipSuccess ||
-      hipMalloc(&p->d_line_tw, tw.size() * sizeof(float2)) != hipSuccess)
+      hipMalloc(&p->d_line_list, list.size() * sizeof(int)) != hipSuccess)
     return SCAT_ERR_ALLOC;
   if (hipMemcpy(p->d_line_masks, words.data(), words.size() * sizeof(words[0]), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p->d_line_list, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p->d_line_tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess)
+      hipMemcpy(p->d_line_list, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
     return SCAT_ERR_DEVICE;
   return SCAT_OK;
 }
@@ -688,6 +696,21 @@ scat_status upload_plane(scat_plan *p) {
   return SCAT_OK;
 }
 
+// The plan's tables and twiddles, to the current device.
+scat_status upload_pool(scat_plan *p, const std::vector<float> &pool, const std::vector<float2> &tw) {
+  if (hipGetDevice(&p->device) != hipSuccess) return SCAT_ERR_DEVICE;
+  if (hipMalloc(&p->d_tables, pool.size() * sizeof(float)) != hipSuccess) return SCAT_ERR_ALLOC;
+  if (hipMalloc(&p->d_tw, tw.size() * sizeof(float2)) != hipSuccess) return SCAT_ERR_ALLOC;
+  if (hipMemcpy(p->d_tables, pool.data(), pool.size() * sizeof(float), hipMemcpyHostToDevice) !=
+      hipSuccess)
+    return SCAT_ERR_DEVICE;
+  if (hipMemcpy(p->d_tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) !=
+      hipSuccess)
+    return SCAT_ERR_DEVICE;
+  p->has_device = true;
+  return note_static_scratch(p);
+}
+
 scat_status upload(scat_plan *p) {
   const scat::HostPlan &h = p->host;
   std::vector<float> pool;
@@ -695,9 +718,9 @@ scat_status upload(scat_plan *p) {
     const scat_status s = upload_plane(p);
     if (s != SCAT_OK) return s;
   }
-  if (p->line) {
+  if (p->line) {  // (none of the tables below is read)
     const scat_status s = upload_line(p, pool);
-    if (s != SCAT_OK) return s;
+    return s != SCAT_OK ? s : upload_pool(p, pool, line_twiddles(p->n1 * p->n2));
   }
   p->psi1_off.assign(h.J, 0);
   for (int j = 0; j < h.J; ++j)
@@ -1011,17 +1034,7 @@ scat_status upload(scat_plan *p) {
     double a = -two_pi * j / p->tw_n;
     tw[j] = make_float2(static_cast<float>(std::cos(a)), static_cast<float>(std::sin(a)));
   }
-  if (hipGetDevice(&p->device) != hipSuccess) return SCAT_ERR_DEVICE;
-  if (hipMalloc(&p->d_tables, pool.size() * sizeof(float)) != hipSuccess) return SCAT_ERR_ALLOC;
-  if (hipMalloc(&p->d_tw, tw.size() * sizeof(float2)) != hipSuccess) return SCAT_ERR_ALLOC;
-  if (hipMemcpy(p->d_tables, pool.data(), pool.size() * sizeof(float), hipMemcpyHostToDevice) !=
-      hipSuccess)
-    return SCAT_ERR_DEVICE;
-  if (hipMemcpy(p->d_tw, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice) !=
-      hipSuccess)
-    return SCAT_ERR_DEVICE;
-  p->has_device = true;
-  return note_static_scratch(p);
+  return upload_pool(p, pool, tw);
 }
 
 // Activity words of the table `key` (scat_plan::lane_mask_off), or null: every load is made
@@ -3090,7 +3103,7 @@ scat::LineEnd line_end(const scat_plan &p, long rows, int lg, int len) {
   e.K = p.host.K;
   e.phi = p.d_tables + p.line_phi_off[0];
   e.reach = p.line_reach[0];
-  e.tw = p.d_line_tw;
+  e.tw = p.d_tw;
   return e;
 }
 
@@ -3107,7 +3120,7 @@ scat_status line_first_order(const scat_plan &p, long pc, const float2 *XH, floa
     }
   int n = static_cast<int>(list.size());
   if (low == nullptr) n = h.max_order == 2 ? h.J - 1 : 0;  // nodes with children only
-  if (n > 0) SCAT_TRY(scat::launch_line_nodes(list.data(), n, low, lgm, h.K, p.d_line_tw, false, st));
+  if (n > 0) SCAT_TRY(scat::launch_line_nodes(list.data(), n, low, lgm, h.K, p.d_tw, false, st));
   return SCAT_OK;
 }
 
@@ -3127,7 +3140,7 @@ scat_status forward_1d_line(scat_plan *p, const float *in, float *out, long p0, 
   if (s != SCAT_OK) return s;
   if (h.max_order == 2 && h.J >= 2) {
     const std::vector<scat::LineNodes> list = line_nodes(*p, pc, 2, nullptr, U);
-    SCAT_TRY(scat::launch_line_nodes(list.data(), static_cast<int>(list.size()), TL, log2i(m), h.K, p->d_line_tw, false,
+    SCAT_TRY(scat::launch_line_nodes(list.data(), static_cast<int>(list.size()), TL, log2i(m), h.K, p->d_tw, false,
                                      st));
   }
   SCAT_TRY(scat::launch_line_out(TL, out + static_cast<size_t>(p0) * h.K * olen,
@@ -3165,7 +3178,7 @@ scat_status backward_1d_line(scat_plan *p, const float *in, const float *gout, f
         kids.push_back(scat::LineKid{GA, p->d_tables + p->line_psi2_off.at(key), p->line_kid_mask.at(key), list[i].lgM});
         GA += static_cast<size_t>(pc) * Q << list[i].lgM;
       }
-    SCAT_TRY(scat::launch_line_nodes(list.data(), static_cast<int>(list.size()), GH, lgm, h.K, p->d_line_tw, true, st));
+    SCAT_TRY(scat::launch_line_nodes(list.data(), static_cast<int>(list.size()), GH, lgm, h.K, p->d_tw, true, st));
   }
   scat::LineSum sum{};
   size_t kid = 0;
@@ -3178,7 +3191,7 @@ scat_status backward_1d_line(scat_plan *p, const float *in, const float *gout, f
     sum.lgM[j] = first[j].lgM;
     GU += static_cast<size_t>(pc) * Q << first[j].lgM;
   }
-  SCAT_TRY(scat::launch_line_nodes(first.data(), J, GH, lgm, h.K, p->d_line_tw, true, st));
+  SCAT_TRY(scat::launch_line_nodes(first.data(), J, GH, lgm, h.K, p->d_tw, true, st));
   sum.dst = GX;
   sum.gh = GH;
   sum.phi = p->d_tables + p->line_phi_off[0];
