@@ -241,6 +241,7 @@ struct Layout {
   // element offsets are expressed per plane; buffers are laid out chunk-major
   size_t xh = 0, t = 0, u = 0, v = 0, w = 0;  // per-plane sizes in bytes
   size_t pad_in = 0, pad_out = 0;             // padded plans: extended input, uncropped output
+  bool whole = false;  // 2-D: nodes that fit k_node_rect run on it (rect_pays)
 };
 
 struct Layout3 {
@@ -279,6 +280,25 @@ bool rect_node_fits(const scat_plan &p, int r, int j) {
   const scat::HostPlan &h = p.host;
   const int rj = h.res(j);
   return p.rect && scat::node_rect_supported(p.n1 >> rj, p.n2 >> rj, 1 << (rj - r), 1 << (h.res(h.J) - rj));
+}
+
+// Does it where it can, in a forward call of `batch` planes?  Where octave 0 stays on the passes, its
+// row pass takes the other first-order octaves with it in the same launch, while their whole nodes are a
+// chain of launches and each node one of loads (up to 64 alias blocks one after another: 25 us for one
+// 16 x 16 node under a 128 x 128 plane).  Few nodes of few angles do not hide that.  Passes -> whole
+// nodes, us, one angle, first order only, J = 4: 128 x 128, one plane 63 -> 84, 256 planes 118 -> 122, 400
+// 160 -> 146; 256 x 128, one 64 -> 82, 200 planes 183 -> 163; four angles, 128 x 128, 50 planes 87 -> 94, 100
+// 117 -> 107.  With second-order nodes half as many planes and angles break even (128 x 128, one angle, 32
+// planes 173 -> 208, 200 planes 249 -> 246), and in larger grids fewer angles (256 x 256, first order, 32
+// planes: two angles 113 -> 130, three, 42 planes, 159 -> 148).  At J = 3 only rows of 256 lose (128 x 256,
+// one angle, first order, 64 planes 71 -> 85, 400 planes even).
+bool rect_pays(const scat_plan &p, long batch) {
+  const scat::HostPlan &h = p.host;
+  const double angles = static_cast<double>(h.LQ) * h.max_order, nodes = static_cast<double>(batch) * angles;
+  if (h.J == 4)
+    return angles > 4 || angles * angles * p.n1 * p.n2 > 4 * 4 * 128 * 128 || nodes * std::max(p.n1, 128) > 256 * 128;
+  if (h.J == 3 && p.n2 == 256) return angles * h.max_order > 4 || nodes * h.max_order > 512;
+  return true;
 }
 
 // Does it compute all nodes of the plan?  (then no row-pass output is ever stored)
@@ -320,6 +340,7 @@ Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
     // (sum over j of L*n/4^j); u: column spectra of one octave's moduli; v: second-order
     // row-pass outputs of all child octaves of one first-order octave
     const size_t l = h.LQ;
+    L.whole = p.rect && rect_pays(p, batch);
     L.xh = n * c8;
     size_t t1 = 0;
     for (int j = 0; j < h.J; ++j) t1 += l * (n >> (2 * h.res(j)));
@@ -1557,7 +1578,7 @@ scat_status forward_2d_fused(scat_plan *p, const float *in, float *out, long p0,
 
   // Octave j's nodes whole (k_node_rect) from sources of resolution r?  (first order: only if the
   // children can read the row-and-column spectra such a node leaves)
-  auto whole = [&](int r, int j) { return tape == nullptr && rect_node_fits(*p, r, j); };
+  auto whole = [&](int r, int j) { return tape == nullptr && lay.whole && rect_node_fits(*p, r, j); };
   auto whole_first = [&](int j1) {
     bool ok = whole(0, j1);
     for (int j2 = j1 + 1; h.max_order == 2 && j2 < J; ++j2) ok = ok && whole(h.res(j1), j2);

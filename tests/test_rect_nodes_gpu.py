@@ -53,6 +53,32 @@ def test_rect_nodes(shape, J, L, max_order, padded, batch):
     assert max(errs.values()) <= 6e-6, errs
 
 
+@pytest.mark.parametrize("shape,J,L,max_order,few,many", [
+    ((128, 128), 4, 1, 1, 2, 300),
+    ((128, 128), 4, 1, 2, 1, 150),
+    ((256, 128), 4, 2, 1, 1, 80),
+    ((128, 256), 3, 1, 1, 3, 520),
+    ((128, 128), 4, 5, 1, None, 1),   # more angles: whole nodes at any batch
+])
+def test_few_nodes_of_few_angles_keep_the_passes(shape, J, L, max_order, few, many):
+    """Calls that k_node_rect makes slower (few first-order nodes beside an octave 0 on the passes)
+    run on the passes, larger ones of the same plan do not; the coefficients are the same."""
+    rng = np.random.default_rng(shape[1] + 7 * J + L)
+    x = rng.standard_normal((many,) + shape).astype(np.float32)
+    got, names, rows = run(shape, J, L, max_order, False, x)
+    assert any(n.startswith("k_node_rect<") for n in names), names
+    n = min(few or 1, 2)
+    want = oracle.scattering2d(x[:n], J, L, max_order)
+    errs = per_order_errors(got[:n], want, order_of_channels(rows), x[:n])
+    assert max(errs.values()) <= TOL, errs
+    if few is None:
+        return
+    got, names, rows = run(shape, J, L, max_order, False, x[:few])
+    assert not any(n.startswith("k_node_rect<") for n in names), names
+    errs = per_order_errors(got[:n], want, order_of_channels(rows), x[:n])
+    assert max(errs.values()) <= TOL, errs
+
+
 def test_oversampled_plans_keep_the_passes():
     x = np.random.default_rng(1).standard_normal((1, 64, 64)).astype(np.float32)
     got, names, rows = run((64, 64), 3, 3, 2, False, x, oversampling=1)
