@@ -661,14 +661,27 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
   return SCAT_OK;
 }
 
-// Does scat_plane.hip serve the backward pass of a 2-D plan?  Every grid of the cascade has to be one of
-// its shapes and an alias mask one word.  Where it can, it always does: 1.03 (128 x 128, J = 2) to 2.5
-// times (one plane of 32 x 32) as fast as the passes.
+// Can scat_plane.hip serve the backward pass of a 2-D plan?  Every grid of the cascade has to be one of
+// its shapes and an alias mask one word.
 bool plane_fits(const scat::HostPlan &h, int n1, int n2) {
   if (h.dims != 2 || h.J > scat::kPlaneMaxOctaves || h.res(h.J - 1) > 3) return false;
   for (int j = 0; j < h.J; ++j)
     if (!scat::plane_supported(n1 >> h.res(j), n2 >> h.res(j))) return false;
   return true;
+}
+
+// Does it where it can, in a call of `batch` planes?  1.03 to 2.5 times as fast as the passes, except few
+// nodes with rows of 128 points: an octave then is a workgroup or two that take the latency of their own
+// chain (128 x 128: 1024 threads each), octave pair after octave pair.  Passes -> here, us, one angle: 128 x
+// 128, J = 4, one plane 218 -> 276, 64 planes 268 -> 342, 256 planes 388 -> 369; J = 3 150 -> 177, 182 -> 206,
+// 286 -> 246, 128 planes even; J = 1 54 -> 58 (one plane); 64 x 128, J = 3, 32 planes 155 -> 170, 256 planes
+// 202 -> 193.  Two and three angles (128 x 128, J = 3, one plane 164 -> 196; J = 4, three, 275 -> 301) stay
+// here, as do more than 4000 nodes of 128 x 128 at J <= 2, 1 to 6 % slower with half the scratch.
+constexpr long kPlaneFew = 128;  // larger batches always do
+bool plane_pays(const scat_plan &p, long batch) {
+  const scat::HostPlan &h = p.host;
+  if (p.n2 < 128 || h.oversampling > 0 || h.LQ > 1) return true;
+  return h.J <= 2 ? p.n1 < 128 || batch > 2 : batch > kPlaneFew;
 }
 
 // Which blocks of the wavelets matter (1e-8 of the peak, below the rounding of a sum over a block).
@@ -1827,6 +1840,7 @@ struct BwdLayout {
   Tape tape;
   size_t gx = 0, gu = 0, ga = 0, gh = 0;  // elements per plane
   size_t pad_floats = 0;  // padded plans: extended input + extended gradients, floats per plane
+  bool plane = false;     // 2-D: on the whole-node kernels of scat_plane.hip
 };
 
 // 1-D backward pass: the schedule built on the adjoint of the forward row kernel needs every
@@ -1881,7 +1895,8 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
                   b.pad_floats * sizeof(float);
   } else {
     const size_t t1 = l * n, t2 = second ? l * l * (n >> (2 * h.res(1))) : 0;
-    if (p.plane) {
+    b.plane = p.plane && plane_pays(p, batch);
+    if (b.plane) {
       // half spectra of x and of the first-order moduli with children
       auto half = [&](int r) { return static_cast<size_t>((p.n1 >> r) / 2 + 1) * (p.n2 >> r) * c8; };
       b.fwd.xh = half(0);
@@ -1901,7 +1916,7 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
       b.fwd.t = (t1 > t2 ? t1 : t2) * c8;
       b.fwd.u = second ? l * n * c8 : 0;
     }
-    if (!p.plane) b.tape = make_tape(p);
+    if (!b.plane) b.tape = make_tape(p);
     b.gx = n;
     // spectra of the output-grid gradient planes of one launch (at most L*L, or L, nodes)
     const size_t mm = static_cast<size_t>(p.n1 >> h.res(h.J)) * (p.n2 >> h.res(h.J));
@@ -1912,7 +1927,7 @@ BwdLayout make_bwd_layout(const scat_plan &p, long batch) {
     for (int j = 0; j < h.J; ++j) b.gu += l * (n >> (2 * h.res(j)));
     for (int j = 1; second && j < h.J; ++j) b.ga += l * l * (n >> (2 * h.res(j)));
     b.gh += (l + 1) * mm;
-    if (p.plane) b.gh = static_cast<size_t>(h.K) * mm;  // all channels at once
+    if (b.plane) b.gh = static_cast<size_t>(h.K) * mm;  // all channels at once
     if (p.padded)
       b.pad_floats = 2 * n + static_cast<size_t>(h.K) * (p.n1 >> h.res(h.J)) * (p.n2 >> h.res(h.J));
     b.per_plane = b.fwd.xh + b.fwd.t + b.fwd.u + b.fwd.v +
@@ -2160,7 +2175,7 @@ scat_status backward_2d_plane(scat_plan *p, const float *x, const float *go, flo
 
 scat_status backward_2d(scat_plan *p, const float *in, const float *gout, float *gin, long p0,
                         long pc, BwdLayout &bl, hipStream_t st) {
-  if (p->plane) {
+  if (bl.plane) {
     const size_t n0 = static_cast<size_t>(p->n1) * p->n2, mm = n0 >> (2 * p->host.res(p->host.J));
     return backward_2d_plane(p, in + p0 * n0, gout + p0 * p->host.K * mm, gin + p0 * n0, pc, bl, st);
   }
@@ -3467,7 +3482,11 @@ scat_status scat_plan_reserve(scat_plan *plan, long batch, int with_backward) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev != plan->device) return SCAT_ERR_DEVICE;
   size_t need = scat_plan_workspace_bytes(plan, batch);
-  if (with_backward) need = std::max(need, scat_plan_backward_workspace_bytes(plan, batch));
+  if (with_backward) {
+    need = std::max(need, scat_plan_backward_workspace_bytes(plan, batch));
+    // (smaller calls may take the passes, whose scratch per plane is the larger one)
+    if (plan->plane) need = std::max(need, scat_plan_backward_workspace_bytes(plan, std::min(batch, kPlaneFew)));
+  }
   if (need <= plan->scratch_bytes) return SCAT_OK;
   return ensure_scratch(plan, need);
 }

@@ -75,6 +75,32 @@ def median(a, b):
     return np.median(np.abs(a.astype(np.float64) - b)) / np.sqrt(np.mean(b ** 2))
 
 
+@pytest.mark.parametrize("shape,J,few,many", [((128, 128), 4, 2, 130), ((64, 128), 3, 128, 129), ((128, 128), 1, 1, 3)])
+def test_few_nodes_of_one_angle_keep_the_passes(shape, J, few, many):
+    """Calls that the whole-node kernels make slower run on the passes, larger ones of the same plan
+    do not; neither allocates after scat_plan_reserve for the larger one."""
+    rng = np.random.default_rng(shape[0] + J)
+    plan = scat.Scattering(shape, J, 1, 2)
+    try:
+        plan.reserve(many, with_backward=True)
+        x = rng.standard_normal((many,) + shape).astype(np.float32)
+        g = rng.standard_normal((many, plan.K) + plan.out_shape).astype(np.float32)
+        xd, gd = torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda()
+        out = torch.empty_like(xd)
+        free = torch.cuda.mem_get_info()[0]
+        want = oracle.scattering2d_backward(x[:1].astype(np.float64), g[:1].astype(np.float64), J, 1)
+        for n, whole in ((few, False), (many, True)):
+            plan.timing_begin(None)
+            plan.backward(xd[:n], gd[:n], out[:n])
+            torch.cuda.synchronize()
+            names = set(plan.timing_end())
+            assert any(s.startswith("k_plane_nodes<") for s in names) == whole, names
+            assert rel(out[:1].cpu().numpy(), want) <= 1e-5   # (the bar of test_plane_backward)
+        assert torch.cuda.mem_get_info()[0] == free
+    finally:
+        plan.close()
+
+
 def test_grids_out_of_range_keep_the_passes():
     for shape, J in (((32, 32), 3), ((256, 128), 2), ((128, 32), 2)):
         plan = scat.Scattering(shape, J, 2, 2)
