@@ -301,13 +301,38 @@ bool rect_pays(const scat_plan &p, long batch) {
   return true;
 }
 
-// Does it compute all nodes of the plan?  (then no row-pass output is ever stored)
-bool rect_everywhere(const scat_plan &p) {
+// Are the first-order nodes of octave j1 whole?  (only if all their children can read the
+// row-and-column spectra such nodes leave)
+bool rect_first_fits(const scat_plan &p, int j1) {
   const scat::HostPlan &h = p.host;
-  for (int j = 0; j < h.J; ++j)
-    for (int j1 = -1; j1 < (h.max_order == 2 ? j : 0); ++j1)
-      if (!rect_node_fits(p, j1 < 0 ? 0 : h.res(j1), j)) return false;
-  return true;
+  bool ok = rect_node_fits(p, 0, j1);
+  for (int j2 = j1 + 1; h.max_order == 2 && j2 < h.J; ++j2) ok = ok && rect_node_fits(p, h.res(j1), j2);
+  return ok;
+}
+
+// Scratch of the fused schedule (bytes per plane) besides the spectra, for the nodes that are not whole.
+// t: first-order row-pass outputs, all octaves at once; v: second-order ones, all child octaves of one
+// first-order octave; w: row halves of the lowpass of x or of one octave's nodes.
+void fused_scratch(const scat_plan &p, bool whole, Layout &L) {
+  const scat::HostPlan &h = p.host;
+  const size_t n = static_cast<size_t>(p.n1) * p.n2, l = h.LQ, m_r = p.n1 >> h.res(h.J);
+  size_t t = 0, v = 0, w = m_r * p.n2;
+  for (int j1 = 0; j1 < h.J; ++j1) {
+    if (!(whole && rect_first_fits(p, j1))) {
+      t += l * (n >> (2 * h.res(j1)));
+      w = std::max(w, l * m_r * (p.n2 >> h.res(j1)));
+    }
+    size_t kids = 0;
+    for (int j2 = j1 + 1; h.max_order == 2 && j2 < h.J; ++j2) {
+      if (whole && rect_node_fits(p, h.res(j1), j2)) continue;
+      kids += l * l * (n >> (2 * h.res(j2)));
+      w = std::max(w, l * l * m_r * (p.n2 >> h.res(j2)));
+    }
+    v = std::max(v, kids);
+  }
+  L.t = std::max(L.t, t * sizeof(float2));
+  L.v = std::max(L.v, v * sizeof(float2));
+  L.w = std::max(L.w, w * sizeof(float));
 }
 
 // budget: bytes of scratch one chunk may use (0 = scratch_budget())
@@ -336,27 +361,14 @@ Layout make_layout(const scat_plan &p, long batch, size_t budget = 0) {
     L.u = most * c8;
     L.w = p.n1 > 128 ? l * 4 * 32 * 32 * sizeof(float) : 0;
   } else if (h.dims == 2 && p.fused) {
-    // xh: column spectra of x; t: first-order row-pass outputs of all octaves at once
-    // (sum over j of L*n/4^j); u: column spectra of one octave's moduli; v: second-order
-    // row-pass outputs of all child octaves of one first-order octave
-    const size_t l = h.LQ;
+    // xh: column spectra of x; u: column spectra of one octave's moduli; t, v, w: fused_scratch
+    // (where smaller calls take the passes the scratch per plane holds either way: it does not
+    // depend on the batch)
     L.whole = p.rect && rect_pays(p, batch);
     L.xh = n * c8;
-    size_t t1 = 0;
-    for (int j = 0; j < h.J; ++j) t1 += l * (n >> (2 * h.res(j)));
-    L.t = t1 * c8;
-    L.u = second ? l * n * c8 : 0;
-    size_t t2 = 0;
-    for (int j = 1; j < h.J; ++j) t2 += l * l * (n >> (2 * h.res(j)));
-    L.v = second ? t2 * c8 : 0;
-    const size_t m_r = p.n1 >> h.res(h.J);
-    size_t w0 = l * m_r * p.n2;
-    size_t w2 = second ? l * l * m_r * (p.n2 >> h.res(1)) : 0;
-    L.w = (w0 > w2 ? w0 : w2) * sizeof(float);
-    if (rect_everywhere(p)) {
-      L.t = L.v = 0;
-      L.w = m_r * p.n2 * sizeof(float);  // S0 only
-    }
+    L.u = second ? h.LQ * n * c8 : 0;
+    fused_scratch(p, p.rect, L);
+    if (p.rect && !rect_pays(p, 1)) fused_scratch(p, false, L);
   } else if (h.dims == 2) {
     const size_t l = h.LQ;
     L.xh = n * c8;
@@ -1589,14 +1601,9 @@ scat_status forward_2d_fused(scat_plan *p, const float *in, float *out, long p0,
     return scat::launch_row_lowpass(W, nodes, m_r, Mc, m_c, pcs, o, cm, K, tw, tw_n, st);
   };
 
-  // Octave j's nodes whole (k_node_rect) from sources of resolution r?  (first order: only if the
-  // children can read the row-and-column spectra such a node leaves)
+  // Octave j's nodes whole (k_node_rect) from sources of resolution r?
   auto whole = [&](int r, int j) { return tape == nullptr && lay.whole && rect_node_fits(*p, r, j); };
-  auto whole_first = [&](int j1) {
-    bool ok = whole(0, j1);
-    for (int j2 = j1 + 1; h.max_order == 2 && j2 < J; ++j2) ok = ok && whole(h.res(j1), j2);
-    return ok;
-  };
+  auto whole_first = [&](int j1) { return tape == nullptr && lay.whole && rect_first_fits(*p, j1); };
   auto rect_nodes = [&](const float2 *src, long ns, int r, int j, size_t filt, float2 *uc, int G, int base, int cs) {
     const int rj = h.res(j);
     scat::RectNode n;

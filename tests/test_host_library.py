@@ -159,3 +159,45 @@ def test_reserve_argument_errors_need_no_gpu():
         assert L.scat_plan_reserve(ok, 4, 1) == 4     # SCAT_ERR_DEVICE: host-only plan
     finally:
         scat.scat_plan_destroy(ok)
+
+
+@pytest.mark.parametrize("shape,J,L,max_order,on_passes", [
+    ((128, 128), 3, 8, 2, (0,)),      # octave 0 on the passes, its children whole
+    ((256, 128), 3, 5, 1, (0,)),
+    ((256, 256), 4, 8, 2, (0, 1)),    # and the 128 x 128 children of octave 0
+    ((64, 64), 3, 8, 2, ()),          # every node whole
+])
+def test_scratch_of_whole_nodes(shape, J, L, max_order, on_passes):
+    """A forward call reserves row-pass outputs for the nodes that the passes compute, not for those
+    that one kernel computes whole."""
+    n, second = shape[0] * shape[1], max_order == 2
+    m_r = shape[0] >> J
+    spectra = 8 * n + (8 * L * n if second else 0)                     # x, one octave's moduli
+    first = sum(8 * L * (n >> (2 * j)) for j in on_passes)
+    kids = [8 * L * L * (n >> (2 * j)) for j in on_passes if j > 0] if second else []
+    low = [m_r * shape[1]] + [L * m_r * (shape[1] >> j) for j in on_passes]
+    if second:
+        low += [L * L * m_r * (shape[1] >> j) for j in on_passes if j > 0]
+    want = spectra + first + sum(kids) + 4 * max(low)
+    plan = scat.Scattering(shape, J, L, max_order, host_only=True)
+    passes = scat.Scattering(shape, J, L, max_order, host_only=True, node_kernels=False)
+    try:
+        assert plan.workspace_bytes(1) == want
+        assert passes.workspace_bytes(1) > want
+        assert plan.workspace_bytes(7) == 7 * want
+    finally:
+        plan.close()
+        passes.close()
+
+
+def test_scratch_covers_the_smaller_calls_that_take_the_passes():
+    """128 x 128, J = 4, one angle: small batches run on the passes, large ones do not; one plane
+    costs the same scratch either way, so a larger reservation covers them."""
+    plan = scat.Scattering((128, 128), 4, 1, host_only=True)
+    passes = scat.Scattering((128, 128), 4, 1, host_only=True, node_kernels=False)
+    try:
+        for b in (1, 100, 1000):
+            assert plan.workspace_bytes(b) == passes.workspace_bytes(b) == b * passes.workspace_bytes(1)
+    finally:
+        plan.close()
+        passes.close()
