@@ -499,26 +499,53 @@ size_t append_vec(std::vector<float> &pool, const std::vector<double> &v) {
   return off;
 }
 
+// Largest magnitudes of a wavelet: by row and block of columns [rows][blocks], and of all of it.
+struct Peaks {
+  std::vector<double> at;
+  double all = 0.0;
+};
+// The L wavelets of octave j at source resolution r, in blocks of n2 >> res(j) columns.  One pass over
+// each table (a plan of 128 x 128, J = 3, L = 8 has 28 of up to 16384 values), for upload_rect and
+// upload_plane alike.
+using PeakCache = std::map<std::pair<int, int>, std::vector<Peaks>>;
+const std::vector<Peaks> &peaks_of(const scat_plan &p, int r, int j, PeakCache &cache) {
+  std::vector<Peaks> &all = cache[{r, j}];
+  if (!all.empty()) return all;
+  const scat::HostPlan &h = p.host;
+  const size_t cols = p.n2 >> h.res(j);  // at least 16, a power of two
+  all.resize(h.LQ);
+  for (int l = 0; l < h.LQ; ++l) {
+    const std::vector<double> &v = h.find(r == 0 ? 1 : 2, j * h.LQ + l, r)->v;
+    all[l].at.resize(v.size() / cols);
+    for (size_t b = 0; b < all[l].at.size(); ++b) {
+      const double *x = v.data() + b * cols;
+      double m[4] = {0.0, 0.0, 0.0, 0.0};  // (four chains of comparisons instead of one)
+      for (size_t i = 0; i < cols; i += 4)
+        for (int u = 0; u < 4; ++u) m[u] = std::max(m[u], std::fabs(x[i + u]));
+      all[l].at[b] = std::max(std::max(m[0], m[1]), std::max(m[2], m[3]));
+      all[l].all = std::max(all[l].all, all[l].at[b]);
+    }
+  }
+  return all;
+}
+
 // Tables of k_node_rect: which alias-block halves of every wavelet are in use (1e-8 of the peak,
 // below the rounding of a sum over the block), and the lowpass as spatial taps.
-scat_status upload_rect(scat_plan *p, std::vector<float> &pool) {
+scat_status upload_rect(scat_plan *p, std::vector<float> &pool, PeakCache &cache) {
   const scat::HostPlan &h = p->host;
   std::vector<unsigned long long> words;
   for (int j = 0; j < h.J; ++j)
     for (int r = 0; r <= h.res(j); ++r) {
       if (p->rect_mask_off.count({r, j}) != 0 || !rect_node_fits(*p, r, j)) continue;
       if (r > 0 && (h.max_order < 2 || r >= j)) continue;  // no such table
-      const int rows = p->n1 >> h.res(j), cols = p->n2 >> h.res(j), A = 1 << (h.res(j) - r);
+      const int rows = p->n1 >> h.res(j), A = 1 << (h.res(j) - r);
       p->rect_mask_off[{r, j}] = words.size();
-      for (int l = 0; l < h.LQ; ++l) {
-        const FilterTable &t = *h.find(r == 0 ? 1 : 2, j * h.LQ + l, r);
-        double peak = 0.0;
-        for (double v : t.v) peak = std::max(peak, std::fabs(v));
+      for (const Peaks &t : peaks_of(*p, r, j, cache)) {
         unsigned long long m[2] = {0, 0};
         for (int kr = 0; kr < rows * A; ++kr)
-          for (int kc = 0; kc < cols * A; ++kc)
-            if (std::fabs(t.v[static_cast<size_t>(kr) * cols * A + kc]) > 1e-8 * peak)
-              m[(kr % rows) / (rows / 2)] |= 1ull << (kr / rows * A + kc / cols);
+          for (int a = 0; a < A; ++a)
+            if (t.at[static_cast<size_t>(kr) * A + a] > 1e-8 * t.all)
+              m[(kr % rows) / (rows / 2)] |= 1ull << (kr / rows * A + a);
         words.push_back(m[0]);
         words.push_back(m[1]);
       }
@@ -535,10 +562,12 @@ scat_status upload_rect(scat_plan *p, std::vector<float> &pool) {
     const double two_pi = 6.283185307179586476925286766559;
     const int len = static_cast<int>(ph.size());
     const size_t off = pool.size();
+    std::vector<double> unit(len);
+    for (int k = 0; k < len; ++k) unit[k] = std::cos(two_pi * k / len);
     for (int d = -R; d <= R; ++d) {
       double acc = 0.0;
       if (2 * d >= -len && 2 * d < len)
-        for (int k = 0; k < len; ++k) acc += ph[k] * std::cos(two_pi * ((static_cast<long>(k) * (d + len)) % len) / len);
+        for (int k = 0; k < len; ++k) acc += ph[k] * unit[(static_cast<long>(k) * (d + len)) % len];
       pool.push_back(static_cast<float>(acc / len));
     }
     return off;
@@ -697,7 +726,7 @@ bool plane_pays(const scat_plan &p, long batch) {
 }
 
 // Which blocks of the wavelets matter (1e-8 of the peak, below the rounding of a sum over a block).
-scat_status upload_plane(scat_plan *p) {
+scat_status upload_plane(scat_plan *p, PeakCache &cache) {
   const scat::HostPlan &h = p->host;
   std::vector<unsigned long long> words;
   const int blocks = p->n1 * p->n2 / 256;
@@ -706,21 +735,20 @@ scat_status upload_plane(scat_plan *p) {
     for (int j1 = -1; j1 < (h.max_order == 2 ? j : 0); ++j1) {
       const int r = j1 < 0 ? 0 : h.res(j1);
       if (p->plane_mask_off.count({r, j}) != 0) continue;
-      const int Sr = p->n1 >> r, Sc = p->n2 >> r, rows = p->n1 >> h.res(j), cols = p->n2 >> h.res(j);
+      const int Sr = p->n1 >> r, Sc = p->n2 >> r, rows = p->n1 >> h.res(j);
       const int A = 1 << (h.res(j) - r);
       p->plane_mask_off[{r, j}] = words.size();
+      const std::vector<Peaks> &tables = peaks_of(*p, r, j, cache);
       for (int l = 0; l < h.LQ; ++l) {
-        const FilterTable &t = *h.find(r == 0 ? 1 : 2, j * h.LQ + l, r);
-        double peak = 0.0;
-        for (double v : t.v) peak = std::max(peak, std::fabs(v));
+        const Peaks &t = tables[l];
         unsigned long long m[3] = {0, 0, 0};
         for (int kr = 0; kr < Sr; ++kr)
-          for (int kc = 0; kc < Sc; ++kc) {
-            if (std::fabs(t.v[static_cast<size_t>(kr) * Sc + kc]) <= 1e-8 * peak) continue;
-            m[(kr % rows) / (rows / 2)] |= 1ull << (kr / rows * A + kc / cols);
+          for (int a = 0; a < A; ++a) {
+            if (t.at[static_cast<size_t>(kr) * A + a] <= 1e-8 * t.all) continue;
+            m[(kr % rows) / (rows / 2)] |= 1ull << (kr / rows * A + a);
             m[2] |= 1ull << (kr / (Sr / 16));
-            if (r == 0) {
-              std::vector<int> &on = active[(kr * Sc + kc) / 256];
+            if (r == 0) {  // (a row has at most 128 points: it lies in one block of 256)
+              std::vector<int> &on = active[kr * Sc / 256];
               if (on.empty() || on.back() != j * h.LQ + l) on.push_back(j * h.LQ + l);
             }
           }
@@ -760,8 +788,9 @@ scat_status upload_pool(scat_plan *p, const std::vector<float> &pool, const std:
 scat_status upload(scat_plan *p) {
   const scat::HostPlan &h = p->host;
   std::vector<float> pool;
+  PeakCache cache;
   if (p->plane) {
-    const scat_status s = upload_plane(p);
+    const scat_status s = upload_plane(p, cache);
     if (s != SCAT_OK) return s;
   }
   if (p->line) {  // (none of the tables below is read)
@@ -896,7 +925,7 @@ scat_status upload(scat_plan *p) {
     }
   }
   if (p->rect) {
-    const scat_status e = upload_rect(p, pool);
+    const scat_status e = upload_rect(p, pool, cache);
     if (e != SCAT_OK) return e;
   }
   if (p->node_taps) {
