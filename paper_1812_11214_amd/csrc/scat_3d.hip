@@ -9,6 +9,7 @@
 #include <string>
 
 #include "fft_regs.hpp"
+#include "pad.hpp"
 #include "slab_fft.hpp"
 #include "scat_kernels.hpp"
 
@@ -167,15 +168,6 @@ __global__ __launch_bounds__(256) void k3_sample(const float2 *__restrict__ src,
 //                     subsampling by 2^J seen from the Fourier side)
 //   k3_out            the aliases of axis 0, the small inverse transform, real part and crop
 
-// symmetric extension of an axis of n samples to P (the caller's volume read in place)
-__device__ __forceinline__ int mirror_source(int i, int n, int P) {
-  const int h = (P - n + 1) / 2;
-  int v = i < n + h ? i : i - P;
-  v %= 2 * n;
-  if (v < 0) v += 2 * n;
-  return v < n ? v : 2 * n - 1 - v;
-}
-
 template <int N1, int N2, bool SPLIT>
 __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_mul_inv(Nodes3 nodes, long slabs, int n0,
                                                        size_t mstride,
@@ -323,11 +315,11 @@ __global__ __launch_bounds__(256) void k3_axis0_rho(Nodes3 nodes, const float *_
   if (xreal != nullptr) {
     if (u0 > 0) {
       const int b = (c0 + c) / n2, e = (c0 + c) % n2;
-      const float *x = xreal + (static_cast<size_t>(vol) * u0 * u1 + mirror_source(b, u1, Mc / n2)) * u2 +
-                       mirror_source(e, u2, n2);
+      const float *x = xreal + (static_cast<size_t>(vol) * u0 * u1 + pad_source(b, u1, Mc / n2)) * u2 +
+                       pad_source(e, u2, n2);
 #pragma unroll
       for (int i = 0; i < E; ++i)
-        v[i] = make_float2(x[static_cast<size_t>(mirror_source(t + T * i, u0, N0)) * u1 * u2], 0.f);
+        v[i] = make_float2(x[static_cast<size_t>(pad_source(t + T * i, u0, N0)) * u1 * u2], 0.f);
     } else {
 #pragma unroll
       for (int i = 0; i < E; ++i) v[i] = make_float2(xreal[off + i * step], 0.f);
