@@ -160,6 +160,7 @@ struct scat_plan {
   std::vector<int> line_reach;  // per resolution: phi is negligible beyond reach + 1/2 output bands
   // (d_tw: see line_twiddles)
   int *d_line_list = nullptr;   // see LineSum
+  long line_listed = 0, plane_listed = 0;
   // 2-D: the backward pass runs on whole-node kernels (scat_plane.hip).  (source resolution, octave)
   // -> L triples of words in d_plane_masks (see PlaneNodes), and the list of PlaneSum.
   bool plane = false;
@@ -693,6 +694,7 @@ scat_status upload_line(scat_plan *p, std::vector<float> &pool) {
     list.insert(list.end(), active[b].begin(), active[b].end());
   }
   list[blocks] = static_cast<int>(list.size());
+  p->line_listed = list[blocks] - list[0];
   if (hipMalloc(&p->d_line_masks, words.size() * sizeof(words[0])) != hipSuccess ||
       hipMalloc(&p->d_line_list, list.size() * sizeof(int)) != hipSuccess)
     return SCAT_ERR_ALLOC;
@@ -761,6 +763,7 @@ scat_status upload_plane(scat_plan *p, PeakCache &cache) {
     list.insert(list.end(), active[b].begin(), active[b].end());
   }
   list[blocks] = static_cast<int>(list.size());
+  p->plane_listed = list[blocks] - list[0];
   if (hipMalloc(&p->d_plane_masks, words.size() * sizeof(words[0])) != hipSuccess ||
       hipMalloc(&p->d_plane_list, list.size() * sizeof(int)) != hipSuccess)
     return SCAT_ERR_ALLOC;
@@ -2196,6 +2199,7 @@ scat_status backward_2d_plane(scat_plan *p, const float *x, const float *go, flo
   sum.phi_c = tab + p->phi_cols_off[0];
   sum.filt = tab + p->psi1_off[0];
   sum.list = p->d_plane_list;
+  sum.listed = p->plane_listed;
   sum.planes = pc;
   sum.N1 = Nr;
   sum.N2 = Nc;
@@ -3269,6 +3273,7 @@ scat_status backward_1d_line(scat_plan *p, const float *in, const float *gout, f
   sum.phi = p->d_tables + p->line_phi_off[0];
   sum.filt = p->d_tables + p->line_psi1_off[0];
   sum.list = p->d_line_list;
+  sum.listed = p->line_listed;
   sum.signals = pc;
   sum.lgN = log2i(N);
   sum.lgm = lgm;

@@ -453,7 +453,7 @@ struct PlaneSum {
   const int *list;  // as LineSum::list, blocks of 256 points of the plane
   const float2 *g[kPlaneMaxOctaves];
   int res[kPlaneMaxOctaves];
-  long planes;
+  long planes, listed;
   int N1, N2, m_r, m_c, K, J, L;
 };
 hipError_t launch_plane_sum(const PlaneSum &s, hipStream_t st);
@@ -509,7 +509,7 @@ struct LineSum {
   const int *list;
   const float2 *g[kLineMaxOctaves];
   int lgM[kLineMaxOctaves];
-  long signals;
+  long signals, listed;  // wavelets in the list, over all blocks
   int lgN, lgm, K, J, Q;
 };
 hipError_t launch_line_sum(const LineSum &s, hipStream_t st);

@@ -445,7 +445,8 @@ hipError_t run_end(int lg, const EndArgs &a, hipStream_t st) {
   static const char *const what[] = {"in", "out", "grad_out", "grad_in"};
   const std::string name = std::string("k_line_end<") + std::to_string(lg) + ", " + what[MODE] + ">";
   const double M = static_cast<double>(1 << lg), rows = a.rows;
-  LaunchScope obs(name.c_str(), rows * 4.0 * (a.len + (MODE == kGradIn ? 2.0 * M : M)), rows * 5.0 * M * lg, st);
+  LaunchScope obs(name.c_str(), rows * 4.0 * (a.len + (MODE == kGradIn ? 2.0 * M : M)),
+                  rows * M * (MODE == kGradIn ? 5.0 : 2.5) * lg, st);
   switch (lg) {
     case 4: return run_end_t<4, MODE>(a, st);
     case 5: return run_end_t<5, MODE>(a, st);
@@ -527,8 +528,14 @@ hipError_t launch_line_nodes(const LineNodes *list, int n, float2 *low, int lgm,
     g.reach = static_cast<signed char>(s.reach);
     for (int c = 0; c < s.kids; ++c) a.kid[kids++] = NodeKid{s.kid[c].g, s.kid[c].filt, s.kid[c].mask, s.kid[c].lgM};
     const double M = static_cast<double>(1 << s.lgM), nd = static_cast<double>(s.nodes);
-    bytes += nd / s.F * (M * (1 << s.lgA)) * 4 + nd * M * (back ? 8 : s.dst ? 4 : 0) + nd * 4.0 * (1 << lgm);
-    flops += nd * M * (5.0 * s.lgM * (back ? 3 : 1.5) + 10.0);
+    bytes += (nd / s.F + s.F) * (M * (1 << s.lgA)) * 4 + nd * M * (back ? 8 : s.dst ? 4 : 0) +
+             (low ? nd * 4.0 * (1 << lgm) : 0.0);
+    // transforms, filter product, modulus, lowpass; adjoint: children's products
+    flops += nd * M * (5.0 * s.lgM * (back ? 3 : 1.5) + 4.0 * (1 << s.lgA) + 4.0 + (low ? 4.0 : 0.0));
+    for (int c = 0; c < s.kids; ++c) {
+      bytes += nd * 8.0 * (1 << s.kid[c].lgM) + 4.0 * M;
+      flops += nd * 4.0 * M;
+    }
   }
   if (first > 0x7fffffffull) return hipErrorInvalidValue;
   const unsigned blocks = static_cast<unsigned>(first);
@@ -589,7 +596,10 @@ hipError_t launch_line_sum(const LineSum &s, hipStream_t st) {
   a.Q = s.Q;
   const unsigned long long blocks = (a.total + 255) / 256;
   if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
-  LaunchScope obs("k_line_sum", a.total * 16.0, a.total * 4.0 * s.Q, st);
+  const double n = static_cast<double>(1 << s.lgN), signals = static_cast<double>(s.signals);
+  double bytes = signals * (8.0 * n + 4.0 * (1 << s.lgm)) + 4.0 * n * (1 + s.J * s.Q);
+  for (int j = 0; j < s.J; ++j) bytes += signals * 8.0 * s.Q * (1 << s.lgM[j]);
+  LaunchScope obs("k_line_sum", bytes, signals * 4.0 * (n + (n < 256 ? n : 256.0) * s.listed), st);
   hipLaunchKernelGGL(k_line_sum, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
   return hipGetLastError();
 }

@@ -303,15 +303,27 @@ __global__ __launch_bounds__(256) void k_plane_sum(PlaneSumArgs a) {
   a.dst[at] = acc;
 }
 
+int lg2i(int n) {
+  int r = 0;
+  while ((1 << r) < n) ++r;
+  return r;
+}
+
 template <int N1, int N2, bool BACK>
 hipError_t run_nodes(PlaneArgs &a, hipStream_t st) {
   using P = Plane<N1, N2>;
   a.blocks = ((a.nodes + P::SPW - 1) / P::SPW + 7) / 8 * 8;
   const double pts = static_cast<double>(N1) * N2, nd = a.nodes;
   const std::string name = "k_plane_nodes<" + std::to_string(N1) + ", " + std::to_string(N2) + (BACK ? ", true>" : ", false>");
-  double bytes = nd / a.F * a.Sr * (N2 << a.lgA) * 4 + nd * pts * (BACK ? 8 : 4);
-  for (int o = 0; o < a.kids; ++o) bytes += nd * a.L * a.kid[o].Mr * a.kid[o].Mc * 8.0;
-  LaunchScope obs(name.c_str(), bytes, nd * pts * (5.0 * 13 * (BACK ? 3 : 1.5) + 10.0), st);
+  const double spts = static_cast<double>(a.Sr) * (N2 << a.lgA);
+  double bytes = nd / a.F * spts * 4 + a.F * spts * 4 + nd * pts * (BACK ? 8 : 4);
+  for (int o = 0; o < a.kids; ++o) bytes += nd * a.L * a.kid[o].Mr * a.kid[o].Mc * 8.0 + a.L * pts * 4;
+  if (BACK) bytes += nd * a.m_r * a.m_c * 8.0;
+  // transforms, filter product, modulus; adjoint: lowpass and children's products
+  LaunchScope obs(name.c_str(), bytes,
+                  nd * (5.0 * pts * lg2i(N1 * N2) * (BACK ? 3 : 1.5) + 4.0 * spts + 4.0 * pts +
+                        (BACK ? 4.0 * pts * (1 + a.kids * a.L) : 0.0)),
+                  st);
   if (P::lds_bytes > 65536) {
     static unsigned long long ok = 0;
     hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k_plane_nodes<N1, N2, BACK>), ok);
@@ -327,7 +339,7 @@ hipError_t run_end(const float *xin, float *xout, const float2 *sin, float2 *sou
   using P = Plane<N1, N2>;
   const std::string name = "k_plane_end<" + std::to_string(N1) + ", " + std::to_string(N2) + (IN ? ", true>" : ", false>");
   const double pts = static_cast<double>(N1) * N2 * planes;
-  LaunchScope obs(name.c_str(), pts * (IN ? 8 : 12), pts * 65, st);
+  LaunchScope obs(name.c_str(), pts * (IN ? 8 : 12), pts * (IN ? 2.5 : 5.0) * lg2i(N1 * N2), st);
   if (P::lds_bytes > 65536) {
     static unsigned long long ok = 0;
     hipError_t e = allow_large_lds(reinterpret_cast<const void *>(k_plane_end<N1, N2, IN>), ok);
@@ -339,12 +351,6 @@ hipError_t run_end(const float *xin, float *xout, const float2 *sin, float2 *sou
 }
 
 bool pow2i(int n) { return n > 0 && (n & (n - 1)) == 0; }
-
-int lg2i(int n) {
-  int r = 0;
-  while ((1 << r) < n) ++r;
-  return r;
-}
 
 #define SCAT_PLANES(N1_, N2_, CALL)                      \
   switch ((N1_) << 12 | (N2_)) {                         \
@@ -443,7 +449,10 @@ hipError_t launch_plane_sum(const PlaneSum &s, hipStream_t st) {
   a.L = s.L;
   const unsigned long long blocks = (a.total + 255) / 256;
   if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
-  LaunchScope obs("k_plane_sum", a.total * 16.0, a.total * 4.0 * s.J * s.L, st);
+  const double n = static_cast<double>(s.N1) * s.N2, planes = static_cast<double>(s.planes);
+  double bytes = planes * 8.0 * (n + s.m_r * s.m_c) + 4.0 * n * (1 + s.J * s.L);
+  for (int j = 0; j < s.J; ++j) bytes += planes * 8.0 * s.L * (s.N1 >> s.res[j]) * (s.N2 >> s.res[j]);
+  LaunchScope obs("k_plane_sum", bytes, planes * 4.0 * (n + 256.0 * s.listed), st);
   hipLaunchKernelGGL(k_plane_sum, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
