@@ -37,6 +37,27 @@ ALG_BYTES_PER_PLANE = {0: 4096 + 20736 + 17664, 1: 4096 + 20736 + 23, 2: 262144 
                        3: 1048576 + 1708032 + 1239552, 4: 262144 + 692224 + 237000}
 
 
+def measured_traffic(path, launches):
+    """{kernel: HBM bytes per launch} of a committed counter summary, for a step that launches the
+    kernels `launches` = {kernel: launches per step}.  Empty unless the summary is of this schedule:
+    every kernel of the step in it, each with the same multiple of its launches per step (a launch
+    that now serves a list of nodes keeps its kernel's name, not its traffic)."""
+    if not os.path.exists(path):
+        return {}
+    table = {}
+    with open(path) as f:
+        for line in f:
+            cols = line.rstrip("\n").split("\t")
+            if not line.startswith("#") and len(cols) == 5:
+                table[cols[0]] = (int(cols[1]), float(cols[4]))
+    if not all(k in table for k in launches):
+        return {}
+    steps = {table[k][0] / launches[k] for k in launches}
+    if len(steps) != 1 or set(table) != set(launches):
+        return {}
+    return {k: table[k][1] for k in launches}
+
+
 def oracle_worker(wl, start, count, t_start):
     """One process of the all-cores leg (`bench.py --oracle-worker wl start count t_start`):
     builds the filter bank and its planes untimed, waits for the common start time, runs the
@@ -246,19 +267,14 @@ def main():
     flops_per_launch = dom["model_flops"] / dom["launches"]
     # HBM bytes per launch of every kernel from the committed rocprofv3 counter summary
     # (FETCH_SIZE and WRITE_SIZE runs of this same command, scaled by a plain copy)
-    per_kernel = {}
-    tpath = os.path.join(ROOT, "profiles", "hbm_traffic_%s%s%s.txt"
-                         % (TRAFFIC_TAGS.get(wl, "none"), "_backward" if args.backward else "",
-                            "_pass_kernels" if args.pass_kernels else ""))
-    if os.path.exists(tpath):
-        with open(tpath) as f:
-            for line in f:
-                cols = line.rstrip("\n").split("\t")
-                if not line.startswith("#") and len(cols) == 5:
-                    per_kernel[cols[0]] = float(cols[4])
+    per_kernel = measured_traffic(
+        os.path.join(ROOT, "profiles", "hbm_traffic_%s%s%s.txt"
+                     % (TRAFFIC_TAGS.get(wl, "none"), "_backward" if args.backward else "",
+                        "_pass_kernels" if args.pass_kernels else "")),
+        {k: v["launches"] for k, v in table.items()})
     traffic = per_kernel.get(dominant)
     measured_step_bytes = None
-    if per_kernel and all(k in per_kernel for k in table):
+    if per_kernel:
         measured_step_bytes = sum(per_kernel[k] * table[k]["launches"] for k in table)
 
     # ---- the dominant kernel against the roofline that binds it.  Its work: the model flops
