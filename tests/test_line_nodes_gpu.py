@@ -68,6 +68,7 @@ def test_line_nodes(n, J, Q, max_order, padded, o, batch):
         # (order 2 of a random walk is 1e-4 of the signal and carries its rounding, in either schedule)
         errs_old = per_order_errors(old, want, order_of_channels(rows), x)
         print("passes", errs_old, flush=True)
+        assert max(errs_old.values()) <= TOL, errs_old
         assert all(errs[k] <= max(3e-6, 1.5 * errs_old[k]) for k in errs), (errs, errs_old)
     else:
         errs = per_order_errors(got, old, order_of_channels(rows), x)
@@ -84,6 +85,8 @@ def test_line_nodes(n, J, Q, max_order, padded, o, batch):
     for p in range(batch):
         new, before = rel(grad[p], want[p]), rel(grad_old[p], want[p])
         print("gradient", p, new, before, flush=True)
+        # (a random walk's 1e-5, see above, with a factor of ten: the passes have a bar of their own)
+        assert before <= 1e-4, (p, before)
         assert new <= max(1e-6, 2 * before), (p, new, before)
 
 

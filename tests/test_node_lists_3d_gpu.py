@@ -46,6 +46,36 @@ def test_lists_forward_and_backward(shape, J, L, mo, o, batch):
     assert emax <= TOL, emax
 
 
+def test_special_values():
+    """A volume of zeros, a constant, large values and an infinity, each beside the others in one call."""
+    import torch
+    shape, J, L = (16, 32, 16), 2, 2
+    rng = np.random.default_rng(11)
+    x = np.zeros((4,) + shape, dtype=np.float32)
+    x[1] = 2.5
+    x[2] = (0.2 + rng.random(shape)) * 1e4
+    x[3, 0, 0, 0] = np.inf
+    plan = scat.Scattering(shape, J, L)
+    try:
+        xd = torch.from_numpy(x).cuda()
+        y = plan.forward(xd)
+        g = rng.standard_normal(tuple(y.shape)).astype(np.float32)
+        gx = plan.backward(xd, torch.from_numpy(g).cuda())
+        torch.cuda.synchronize()
+        got, ggot = y.cpu().numpy(), gx.cpu().numpy().astype(np.float64)
+        rows = plan.coeff_index()
+    finally:
+        plan.close()
+    errs = per_order_errors(got[:3], o3.harmonic_scattering3d(x[:3], J, L), order_of_channels(rows), x[:3])
+    assert max(errs.values()) <= TOL, errs
+    assert (got[0] == 0).all() and np.isnan(got[3]).all()
+    want = o3.harmonic_scattering3d_backward(x[:3], g[:3], J, L)
+    for p in (0, 2):  # zeros: the lowpass of x alone
+        assert np.abs(ggot[p] - want[p]).max() / np.abs(want[p]).max() <= TOL, p
+    assert np.isfinite(ggot[1]).all()  # (moduli that vanish up to rounding, which decides their signs)
+    assert np.isnan(ggot[3]).all()
+
+
 def test_lists_cut_by_the_static_buffer():
     """64^3 at J = 3, L = 3 asks for more scratch than the library's static buffer has: the call
     takes fewer nodes at a time there and gives the same coefficients (bit for bit: a node's

@@ -13,6 +13,8 @@ import oracle
 import paper_1812_11214_amd as scat
 from oracle.scattering import pad_index, padded_size
 
+from parity import TOL, order_of_channels, per_order_errors
+
 
 @pytest.mark.parametrize("n,J", [(28, 2), (5, 3), (100, 4), (32, 2), (1, 2), (3, 1), (1000, 6)])
 def test_extension_matches_numpy_symmetric_pad(n, J):
@@ -194,6 +196,42 @@ def test_padded_backward_parity_gpu_1d(n, J, Q, batch):
     want = oracle.scattering1d_padded_backward(x.astype(np.float64), g.astype(np.float64), J, Q)
     for p in range(batch):
         err = np.abs(got[p] - want[p]).max() / np.abs(want[p]).max()
+        assert err <= 1e-4, (p, err)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,J,Q,mo,batch", [(9001, 4, 2, 2, 3), (20000, 5, 4, 2, 2), (8190, 6, 1, 2, 2),
+                                            (16385, 3, 3, 1, 2)])
+def test_padded_long_signals_gpu_1d(n, J, Q, mo, batch):
+    """Grids of more than 8192 samples: the pass kernels, with the extension, the crop and their
+    adjoints as kernels of their own."""
+    import torch
+    rng = np.random.default_rng(n + J)
+    # Noise with an offset.  (Not a random walk: the rounding of its spectrum, 1e-7 of a norm a hundred
+    # to a thousand times the octave-0 moduli, is 1e-5 to 1e-4 of their phases, which the gradient passes
+    # on sample by sample; noise has 1e-7 there and 1e-5 at its smallest moduli.)
+    x = (rng.standard_normal((batch, n)) + 1.0).astype(np.float32)
+    plan = scat.Scattering((n,), J, Q, mo, padded=True)
+    try:
+        assert plan.grid_shape[0] > 8192
+        xd = torch.from_numpy(x).cuda()
+        g = rng.standard_normal((batch, plan.K) + plan.out_shape).astype(np.float32)
+        plan.timing_begin(None)
+        y = plan.forward(xd)
+        gi = plan.backward(xd, torch.from_numpy(g).cuda())
+        torch.cuda.synchronize()
+        assert not any(s.startswith("k_line_") for s in plan.timing_end())
+        rows = plan.coeff_index()
+        got, grad = y.cpu().numpy(), gi.cpu().numpy().astype(np.float64)
+    finally:
+        plan.close()
+    errs = per_order_errors(got, oracle.scattering1d_padded(x.astype(np.float64), J, Q, mo),
+                            order_of_channels(rows), x)
+    assert max(errs.values()) <= TOL, errs
+    want = oracle.scattering1d_padded_backward(x.astype(np.float64), g.astype(np.float64), J, Q, mo)
+    for p in range(batch):
+        err = np.abs(grad[p] - want[p]).max() / np.abs(want[p]).max()
+        print(n, p, errs, err, flush=True)
         assert err <= 1e-4, (p, err)
 
 

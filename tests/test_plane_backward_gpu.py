@@ -67,7 +67,7 @@ def test_plane_backward(shape, J, L, max_order, padded, o, batch):
         # alone moves the gradient by 3e-6 in relative L2 (in either schedule, by its own rounding: no
         # bound on their ratio).  So the L2 bar is 1e-5, and the median over the pixels, which such a
         # sample does not reach, is held to the rounding of nine chained transforms.
-        assert new <= 1e-5, (p, new, before)
+        assert new <= 1e-5 and before <= 1e-5, (p, new, before)
         assert mid <= max(3e-7, 1.5 * mid_before), (p, mid, mid_before)
 
 
@@ -99,6 +99,23 @@ def test_few_nodes_of_one_angle_keep_the_passes(shape, J, few, many):
         assert torch.cuda.mem_get_info()[0] == free
     finally:
         plan.close()
+
+
+def test_special_values():
+    """A plane of zeros (no gradient through any modulus), a constant, large noise and an infinity."""
+    shape, J, L = (64, 32), 2, 3
+    rng = np.random.default_rng(3)
+    x = np.zeros((4,) + shape, dtype=np.float32)
+    x[1] = -2.5
+    x[2] = rng.standard_normal(shape) * 1e4
+    x[3, 0, 0] = np.inf
+    got, names, g = run(shape, J, L, 2, x, lambda per: rng.standard_normal((4,) + per).astype(np.float32), False, 0)
+    assert any(s.startswith("k_plane_nodes<") for s in names), names
+    want = oracle.scattering2d_backward(x[:3].astype(np.float64), g[:3].astype(np.float64), J, L)
+    assert rel(got[0], want[0]) <= 1e-6          # the lowpass of x alone: two transforms of 2048 points
+    assert np.isfinite(got[1]).all()             # (its moduli vanish up to rounding, which decides their phases)
+    assert rel(got[2], want[2]) <= 1e-5          # (the bar of test_plane_backward)
+    assert np.isnan(got[3]).all()
 
 
 def test_grids_out_of_range_keep_the_passes():
