@@ -1,5 +1,5 @@
-"""Whole-node kernel for grids of any shape (k_node_rect): every node shape and subsampling it is
-built for, source counts that do not fill a workgroup or the last group of eight, padded and
+"""Whole-node kernel for grids of any shape (k_node_rect): every node shape and subsampling that a plan
+reaches, source counts that do not fill a workgroup or the last group of eight, padded and
 first-order plans, against the oracle and against the pass kernels of the same plan."""
 import numpy as np
 import pytest
@@ -51,6 +51,43 @@ def test_rect_nodes(shape, J, L, max_order, padded, batch):
     # five chained transforms and two sums in fp32 on either side: 2 * 3e-6 of the order's maximum
     errs = per_order_errors(got, old, order_of_channels(rows), x)
     assert max(errs.values()) <= 6e-6, errs
+
+
+# (rows, columns, subsampling) of the variants that each plan's octaves take: together all that a plan reaches
+VARIANTS = [
+    ((32, 32), 1, 4, 1, [(32, 32, 2)]),
+    ((32, 64), 1, 3, 2, [(32, 64, 2)]),
+    ((32, 64), 2, 5, 2, [(32, 64, 4), (16, 32, 2)]),
+    ((32, 64), 3, 2, 1, [(32, 64, 8), (16, 32, 4)]),   # (8 x 16 nodes on the passes)
+    ((64, 32), 1, 2, 2, [(64, 32, 2)]),
+    ((64, 32), 2, 3, 2, [(64, 32, 4), (32, 16, 2)]),
+    ((64, 64), 1, 7, 2, [(64, 64, 2)]),
+    ((64, 64), 2, 3, 2, [(64, 64, 4), (32, 32, 2)]),
+    ((64, 64), 3, 2, 2, [(64, 64, 8), (32, 32, 4), (16, 16, 2)]),
+    ((64, 128), 1, 3, 1, [(64, 128, 2)]),
+    ((64, 128), 2, 2, 2, [(64, 128, 4), (32, 64, 2)]),
+    ((64, 128), 3, 2, 2, [(64, 128, 8), (32, 64, 4), (16, 32, 2)]),
+    ((128, 64), 1, 2, 2, [(128, 64, 2)]),
+    ((128, 64), 2, 1, 2, [(128, 64, 4), (64, 32, 2)]),
+    ((128, 64), 3, 2, 2, [(128, 64, 8), (64, 32, 4), (32, 16, 2)]),
+]
+
+
+@pytest.mark.parametrize("shape,J,L,max_order,variants", VARIANTS)
+def test_rect_node_variants(shape, J, L, max_order, variants):
+    rng = np.random.default_rng(shape[0] * 100 + shape[1] + J)
+    x = rng.standard_normal((3,) + shape).astype(np.float32)
+    x[0] = np.cumsum(x[0], axis=0) * 0.1 + 3
+    got, names, rows = run(shape, J, L, max_order, False, x)
+    assert {n for n in names if n.startswith("k_node_rect<")} == {"k_node_rect<%d, %d, %d>" % v for v in variants}
+    errs = per_order_errors(got, oracle.scattering2d(x, J, L, max_order), order_of_channels(rows), x)
+    print("rect", shape, J, L, errs, flush=True)
+    # what the fp32 chain of transforms shows elsewhere in this file: 3e-6 of an order's maximum
+    assert max(errs.values()) <= 3e-6, errs
+
+
+def test_all_variants_are_tested():
+    assert len({v for case in VARIANTS for v in case[4]}) == 20
 
 
 @pytest.mark.parametrize("shape,J,L,max_order,few,many", [
