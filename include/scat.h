@@ -128,15 +128,21 @@ scat_status scat_plan_create_padded_host(scat_plan **out_plan, int dims, const i
  */
 #define SCAT_PLAN_PADDED 1
 #define SCAT_PLAN_HOST_ONLY 2
-/* 2-D plans of 256 x 256 at J = 3 or 128 x 128 at J = 2 (without oversampling): scat_forward
- * walks the tree with one workgroup per node (the "Implementation" paragraph's depth-first
- * walk: a node's inverse transform, modulus, lowpass and, for parents, spectrum never leave
- * the compute unit; only the spectra of the input and of first-order moduli with children are
- * kept in scratch).  This is what these plans do by default; SCAT_PLAN_NODE_KERNELS is kept
- * for callers that ask for it by name and changes nothing.  SCAT_PLAN_PASS_KERNELS selects
- * the row and column passes over the whole batch instead (the schedule of every other 2-D
- * shape), for comparison: same results to rounding.  Both are ignored by other shapes and by
- * scat_backward. */
+/* By default nodes of the tree are computed whole, one workgroup or wavefront each (the
+ * "Implementation" paragraph's walk: a node's inverse transform, modulus, lowpass and, for
+ * parents, spectrum never leave the compute unit), where the library has a kernel for them and
+ * that is the faster way:
+ *   scat_forward, 2-D without oversampling: every node of 256 x 256 plans at J = 3 and 128 x 128
+ *     plans at J = 2; of other plans with J <= 4 whose rows have 32 ... 256 points, 16 or more at
+ *     octave J - 1, the nodes of at most 8192 points (sides 16 ... 128, square or 2 : 1);
+ *   scat_forward and scat_backward, 1-D: periodic grids of at most 8192 samples;
+ *   scat_backward, 2-D: grids of at most 128 x 128 whose smallest nodes have sides of at least 16.
+ * SCAT_PLAN_PASS_KERNELS selects the row and column passes over the whole batch for all of
+ * these instead, in both directions, for comparison: same results to rounding, other scratch
+ * sizes.  Calls with few nodes take the passes by themselves where those are faster, so the
+ * rounding of a plane's result may depend on the batch it is in.  The flag changes nothing for
+ * other plans (32 x 32 at J = 2 forward, 3-D plans, larger grids).  SCAT_PLAN_NODE_KERNELS is
+ * kept for callers that ask for the default by name and changes nothing. */
 #define SCAT_PLAN_NODE_KERNELS 4
 #define SCAT_PLAN_PASS_KERNELS 8
 scat_status scat_plan_create_ex(scat_plan **out_plan, int dims, const int *shape, int J, int LQ,
@@ -171,7 +177,8 @@ scat_status scat_forward(scat_plan *plan, const float *in, float *out, long batc
  * allocate nor synchronise (paper, section 2 "Implementation": the transform is meant to sit
  * inside a training or serving loop).  Synchronises the device if the buffer has to grow;
  * must run on the plan's device with no call of this plan in flight.  The buffer never
- * shrinks.  Errors: SCAT_ERR_NULL, SCAT_ERR_ARG (batch < 1), SCAT_ERR_DEVICE (host-only plan
+ * shrinks.  3-D plans keep up to 1 GiB for the signals of the nodes in flight besides what
+ * scales with the batch (scat_plan_workspace_bytes).  Errors: SCAT_ERR_NULL, SCAT_ERR_ARG (batch < 1), SCAT_ERR_DEVICE (host-only plan
  * or wrong device), SCAT_ERR_ALLOC.
  */
 scat_status scat_plan_reserve(scat_plan *plan, long batch, int with_backward);

@@ -282,8 +282,9 @@ class Scattering:
         """padded=True: signals of any size, extended symmetrically to a periodic grid of
         power-of-two sides (scat_plan_create_padded); else `shape` is that periodic grid.
         oversampling=o: every signal 2^o times finer than the default schedule.
-        node_kernels=False: 256x256/J=3 and 128x128/J=2 plans, which by default walk the tree one
-        workgroup per node, use the row and column passes instead (SCAT_PLAN_PASS_KERNELS)."""
+        node_kernels=False: row and column passes over the whole batch, forward and backward,
+        for the plans that by default compute nodes of the tree whole, one workgroup each: 2-D
+        up to 256 a side, 1-D up to 8192 samples (SCAT_PLAN_PASS_KERNELS in scat.h lists them)."""
         self.shape = tuple(int(s) for s in shape)
         self.dims = len(self.shape)
         self.J, self.LQ, self.max_order = int(J), int(LQ), int(max_order)

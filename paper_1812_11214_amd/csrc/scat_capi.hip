@@ -587,7 +587,7 @@ scat_status upload_rect(scat_plan *p, std::vector<float> &pool, PeakCache &cache
 // Does scat_line.hip serve a 1-D plan?  A node of 8192 samples takes 66 KB of LDS (two workgroups on
 // a compute unit) and twice that has no room; nodes of fewer than 32 samples and output grids of
 // fewer than 16 have no shape, more than 64 alias blocks no mask.  Where it can, it always does: 1.7
-// to 7 times as fast as the passes at 64 ... 8192 samples, batches of 1 ... 8000.
+// to 7.4 times as fast as the passes at 64 ... 8192 samples, batches of 1 ... 8000, Q = 8.
 bool line_fits(const scat::HostPlan &h, int n, int J) {
   if (h.dims != 1 || J > scat::kLineMaxOctaves || n > 8192) return false;
   const int fine = h.res(J - 1);
@@ -2487,10 +2487,12 @@ Work3 work_3d(const scat_plan &p, bool backward) {
 }
 
 // Bytes for the nodes in flight of a chunk of `pc` volumes: all of a layer's where that is below
-// kArea3, else as many as that holds.  (Smaller areas, whose contents the last-level cache would
-// hold from one launch to the next, measured slower: 16 volumes of 64^3, forward, 766 us with
-// 64 to 192 MB, 720 us from 384 MB up; forward and backward 2.52 ms, 2.41 ms with 384 MB, 2.30 ms
-// with 1 GB.)  Never less than one node needs; never decreasing in pc (scat_plan_reserve).
+// kArea3, else as many as that holds.  Smaller areas, whose contents the last-level cache would hold
+// from one launch to the next, are never the faster ones by more than 3 % and mostly slower, us with 256
+// MB, 384 MB, 1 GB: 16 volumes of 64^3 (J = 2, L = 3) forward 705, 694, 703, backward 1754, 1699, 1592; 8
+// of them 405, 396, 378 and 943, 900, 816; 25 of them 1087, 1077, 1048 and 2655, 2655, 2485; 40 at J = 1
+// 709, 708, 667 and 1372, 1377, 1327; 80 of 16 x 64 x 64 817, 822, 846 and 1953, 1952, 1817.
+// Never less than one node needs; never decreasing in pc (scat_plan_reserve).
 constexpr size_t kArea3 = size_t(1) << 30;
 size_t area_bytes_3d(const Work3 &w, long pc, size_t budget) {
   const size_t c8 = sizeof(float2), n = static_cast<size_t>(pc);

@@ -12,9 +12,11 @@
 // and column pass by itself; at 32 signals of 8192 a launch has 32 ... 512 workgroups and takes the
 // latency of its own load-transform-store chain (5 ... 30 us, 85 launches in a training step), and at
 // large batches every pass goes through memory.  Measured, passes -> here: training step of 32
-// signals of 5000 samples (J 5, Q 8) 853 -> 206 us; forward / backward of 600 x 8192 (J 5, Q 8) 1609 ->
-// 684 / 2878 -> 1736 us, 2048 x 2048 (J 4, Q 8) 1554 -> 482 / 2701 -> 1203 us, one signal of 2048 193 ->
-// 28 / 346 -> 54 us: no size, batch or oversampling was found where the passes are the better ones.
+// signals of 5000 samples (J 5, Q 8) 827 -> 207 us; forward / backward of 600 x 8192 (J 5, Q 8) 1609 ->
+// 610 / 2874 -> 1724 us, 2048 x 2048 (J 4, Q 8) 1548 -> 408 / 2693 -> 1175 us, one signal of 2048 190 ->
+// 27 / 345 -> 56 us: no size, batch or oversampling was found where the passes are the better ones.
+// Error against 64 bits (40 shapes, 4 inputs each): 0.93 of the passes' forward (0.83 ... 1.07 by shape),
+// 0.97 backward (0.86 ... 1.10; 1.7e-7 ... 4.6e-7).
 // What bounds it at large batches is the LDS exchanges (two a transform) and the source and filter reads
 // through L2; at small ones the chain of eleven launches.
 #include <hip/hip_runtime.h>

@@ -7,9 +7,10 @@
 // its N1 N2 / 16 threads.  The passes that serve these plans otherwise (taped row and column passes,
 // k_rows2d_adj, k_node_modback) write and read a complex value per point four times more, and at a
 // small batch are launches of a few dozen workgroups.  Backward pass, passes -> here (L = 8): 128
-// planes of 32 x 32, J = 2, 207 -> 88 us, 2048 of them 1175 -> 649 us; 512 of 64 x 64, J = 3, 1467 -> 998 us;
-// 100 of 128 x 128, J = 3, 1014 -> 915 us, J = 2, 665 -> 646 us (one workgroup a compute unit at octave 0:
-// the smallest gain); one of 64 x 64 253 -> 155 us.  Error against 64 bits the same (2.4e-7 ... 5e-7).
+// planes of 32 x 32, J = 2, 204 -> 84 us, 2048 of them 1160 -> 604 us; 512 of 64 x 64, J = 3, 1457 -> 938 us;
+// 100 of 128 x 128, J = 3, 994 -> 881 us, J = 2, 619 -> 614 us (one workgroup a compute unit at octave 0:
+// the smallest gain; plane_pays in scat_capi.hip has the line); one of 64 x 64 254 -> 152 us.  Error
+// against 64 bits the same (20 shapes, 4 inputs each: 0.99 of the passes' on average).
 // What bounds it is the children's spectra and wavelets, read through L2 by every parent.
 #include <hip/hip_runtime.h>
 

@@ -7,8 +7,9 @@
 // transform of the modulus.  Against the passes that serve these nodes otherwise (k_rows_fused,
 // k_col_fast, k_row_lowpass_fast) the node never goes to memory, between the row and the column
 // transform as little as after the modulus: 8 + 8 + 4 bytes per point saved.  The nodes that fit
-// always take it: 96 planes of 128 x 128, J = 3, 613 -> 299 us (their 6144 + 6144 second-order nodes
-// of octave 0: 331 -> 128 us); 48 planes of 200 x 120, 555 -> 345 us.  What bounds it now is the
+// take it, but for small calls of few angles (rect_pays in scat_capi.hip): 96 planes of 128 x 128, J = 3,
+// L = 8, 600 -> 297 us (their 6144 + 6144 second-order nodes of octave 0: 331 -> 128 us); 48 planes of
+// 200 x 120 543 -> 334 us.  What bounds it now is the
 // source spectrum and filter reads through L2 (130 KB per 64 x 64 child of a 128 x 128 node, 9 TB/s)
 // together with the transforms' LDS exchanges.
 #include <hip/hip_runtime.h>
