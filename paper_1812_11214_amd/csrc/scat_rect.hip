@@ -266,9 +266,11 @@ bool pow2i(int n) { return n > 0 && (n & (n - 1)) == 0; }
 
 int rect_reach(int dec) { return kRectReach * dec; }
 
+// (8 dec <= N2: plans on the fused row pass keep 16 points a row at their last octave, where dec is 2)
 bool node_rect_supported(int N1, int N2, int A, int dec) {
   return pow2i(N1) && pow2i(N2) && N1 >= 16 && N2 >= 16 && N1 * N2 <= 8192 &&
-         (N1 == N2 || N1 == 2 * N2 || N2 == 2 * N1) && (dec == 2 || dec == 4 || dec == 8) && pow2i(A) && A <= 8;
+         (N1 == N2 || N1 == 2 * N2 || N2 == 2 * N1) && (dec == 2 || dec == 4 || dec == 8) && 8 * dec <= N2 && pow2i(A) &&
+         A <= 8;
 }
 
 hipError_t launch_node_rect(const RectNode &n, hipStream_t st) {
@@ -295,25 +297,24 @@ hipError_t launch_node_rect(const RectNode &n, hipStream_t st) {
   a.K = n.K;
   a.tw = n.tw;
   a.tw_n = n.tw_n;
-#define SCAT_RECT(N1_, N2_)                                          \
-  case (N1_ << 12) | N2_:                                            \
-    switch (n.dec) {                                                 \
-      case 2: return launch_rect_t<N1_, N2_, 2>(a, st);              \
-      case 4: return launch_rect_t<N1_, N2_, 4>(a, st);              \
-      default: return launch_rect_t<N1_, N2_, 8>(a, st);             \
-    }
-  switch ((n.N1 << 12) | n.N2) {
-    SCAT_RECT(16, 16)
-    SCAT_RECT(16, 32)
-    SCAT_RECT(32, 16)
-    SCAT_RECT(32, 32)
-    SCAT_RECT(32, 64)
-    SCAT_RECT(64, 32)
-    SCAT_RECT(64, 64)
-    SCAT_RECT(64, 128)
-    SCAT_RECT(128, 64)
+#define SCAT_RECT(N1_, N2_, DEC_) \
+  case (N1_ << 16) | (N2_ << 4) | DEC_: return launch_rect_t<N1_, N2_, DEC_>(a, st);
+#define SCAT_RECT4(N1_, N2_) SCAT_RECT(N1_, N2_, 2) SCAT_RECT(N1_, N2_, 4)
+#define SCAT_RECT8(N1_, N2_) SCAT_RECT4(N1_, N2_) SCAT_RECT(N1_, N2_, 8)
+  switch ((n.N1 << 16) | (n.N2 << 4) | n.dec) {
+    SCAT_RECT(16, 16, 2)
+    SCAT_RECT4(16, 32)
+    SCAT_RECT(32, 16, 2)
+    SCAT_RECT4(32, 32)
+    SCAT_RECT8(32, 64)
+    SCAT_RECT4(64, 32)
+    SCAT_RECT8(64, 64)
+    SCAT_RECT8(64, 128)
+    SCAT_RECT8(128, 64)
     default: return hipErrorInvalidValue;
   }
+#undef SCAT_RECT8
+#undef SCAT_RECT4
 #undef SCAT_RECT
 }
 
