@@ -178,8 +178,8 @@ scat_status scat_forward(scat_plan *plan, const float *in, float *out, long batc
  * inside a training or serving loop).  Synchronises the device if the buffer has to grow;
  * must run on the plan's device with no call of this plan in flight.  The buffer never
  * shrinks.  3-D plans keep up to 1 GiB for the signals of the nodes in flight besides what
- * scales with the batch (scat_plan_workspace_bytes).  Errors: SCAT_ERR_NULL, SCAT_ERR_ARG (batch < 1), SCAT_ERR_DEVICE (host-only plan
- * or wrong device), SCAT_ERR_ALLOC.
+ * scales with the batch (scat_plan_workspace_bytes).  Errors: SCAT_ERR_NULL, SCAT_ERR_ARG
+ * (batch < 1), SCAT_ERR_DEVICE (host-only plan or wrong device), SCAT_ERR_ALLOC.
  */
 scat_status scat_plan_reserve(scat_plan *plan, long batch, int with_backward);
 
