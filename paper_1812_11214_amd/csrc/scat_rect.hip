@@ -110,9 +110,11 @@ __global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectAr
     if (TS >= 64) block = __builtin_amdgcn_readfirstlane(block);
     struct Unit {
       float xr[4], xi[4], w[4], sign;
+      bool own;
     };
-    // rows N1 / 4 g + t1 + T1 i of alias block `bit`
-    auto load = [&](Unit &un, int g, int bit) {
+    // rows N1 / 4 g + t1 + T1 i of alias block `bit`; own: the blocks that this node's filter uses
+    auto load = [&](Unit &un, int g, int bit, unsigned long long own) {
+      un.own = TS >= 64 || (own >> bit & 1ull) != 0ull;
       const int ar = bit >> a.lgA, ac = bit & (A - 1), kr = N1 / 4 * g + N1 * ar;
       const bool mir = kr >= Sr / 2;
       // mirrored: row Sr - kr, column -(c + N2 ac); the columns -c but 0 lie one block of N2 before
@@ -129,7 +131,11 @@ __global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectAr
         un.w[i] = at(pw + i * T1 * Sc, x_w);
       }
     };
+    // (a node takes its own filter's blocks and no others, whatever nodes it shares a wavefront with: its bits
+    // do not depend on its place in the batch, and an infinity in a block that it leaves out does not reach it.
+    // 16 planes of 64 x 64, J = 3, L = 8 74.6 -> 76.2 us, 200 planes 154.1 -> 156.2)
     auto add = [&](const Unit &un, int g) {
+      if (!un.own) return;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         float2 &z = v[4 * g + i];
@@ -140,13 +146,14 @@ __global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectAr
     if (A == 1) {  // one block each: all of them at once
       Unit un[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) load(un[g], g, 0);
+      for (int g = 0; g < 4; ++g) load(un[g], g, 0, 1ull);
 #pragma unroll
       for (int g = 0; g < 4; ++g) add(un[g], g);
     } else
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      unsigned long long rem = a.mask[block + g * (N2 / S::CW)];
+      const unsigned long long own = a.mask[block + g * (N2 / S::CW)];
+      unsigned long long rem = own;
       if (TS < 64) {  // slabs that share a wavefront: what any of them uses
         rem |= __shfl_xor(rem, 32);
         if (TS < 32) rem |= __shfl_xor(rem, 16);
@@ -162,20 +169,20 @@ __global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectAr
       for (; n >= 4; n -= 4) {
         Unit un[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) load(un[e], g, next());
+        for (int e = 0; e < 4; ++e) load(un[e], g, next(), own);
 #pragma unroll
         for (int e = 0; e < 4; ++e) add(un[e], g);
       }
       if (n & 2) {
         Unit un[2];
-        load(un[0], g, next());
-        load(un[1], g, next());
+        load(un[0], g, next(), own);
+        load(un[1], g, next(), own);
         add(un[0], g);
         add(un[1], g);
       }
       if (n & 1) {
         Unit un;
-        load(un, g, next());
+        load(un, g, next(), own);
         add(un, g);
       }
     }

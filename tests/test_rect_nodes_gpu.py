@@ -116,6 +116,25 @@ def test_few_nodes_of_few_angles_keep_the_passes(shape, J, L, max_order, few, ma
     assert max(errs.values()) <= TOL, errs
 
 
+@pytest.mark.parametrize("shape,J,L", [
+    ((64, 64), 3, 5),     # 16 x 16 leaves, four nodes to a wavefront
+    ((64, 64), 3, 6),
+    ((128, 64), 3, 3),    # 32 x 16 leaves, two to a wavefront
+    ((64, 128), 3, 5),    # 16 x 32 leaves
+])
+def test_a_plane_has_the_same_bits_wherever_it_stands(shape, J, L):
+    """Nodes of fewer than 64 threads share a wavefront with other planes' nodes, with other filters at
+    another place in the batch."""
+    x = torch.from_numpy(np.random.default_rng(J + L).standard_normal((7,) + shape).astype(np.float32)).cuda()
+    plan = scat.Scattering(shape, J, L)
+    try:
+        y = plan.forward(x)
+        for k in range(len(x)):
+            assert torch.equal(plan.forward(x[k:k + 1].contiguous())[0], y[k]), k
+    finally:
+        plan.close()
+
+
 def test_oversampled_plans_keep_the_passes():
     x = np.random.default_rng(1).standard_normal((1, 64, 64)).astype(np.float32)
     got, names, rows = run((64, 64), 3, 3, 2, False, x, oversampling=1)
