@@ -208,12 +208,10 @@ __global__ void k_mulfold_invrow(const float2 *__restrict__ src, const float *__
 }
 
 // ------------------------------------------------------------------------------------
-// Forward row FFT in place, transform in registers (rows of E*T points, T lanes per row).
-template <int E, int T>
-__global__ __launch_bounds__(E == 32 ? 128 : 256) void k_row_fwd_reg(float2 *__restrict__ data,
-                                                                     long rows, int planar,
-                                                                     const float2 *__restrict__ tw,
-                                                                     int tw_n) {
+// Forward row FFT in place, transform in registers (rows of E*T points, T lanes per row).  PLANAR: rows are
+// left as real and imaginary parts, in pieces of T floats (1) or in runs through LDS (2).
+template <int E, int T, int PLANAR>
+__device__ __forceinline__ void row_fwd(float2 *__restrict__ data, long rows, const float2 *__restrict__ tw, int tw_n) {
   constexpr int NT = E == 32 ? 128 : 256;
   constexpr int RPB = NT / T, M = E * T;
   extern __shared__ float2 lds[];
@@ -227,7 +225,7 @@ __global__ __launch_bounds__(E == 32 ? 128 : 256) void k_row_fwd_reg(float2 *__r
   float2 wt[E];
   load_twiddles<E, T>(wt, t, tw, tw_n);
   fft_core<E, T, false, true>(v, t, lds + rl * (E * (T + 1)), T + 1, 1, wt);
-  if (planar == 1 && valid) {  // (the row's lanes have all read it)
+  if (PLANAR == 1 && valid) {  // (the row's lanes have all read it)
     float *q = reinterpret_cast<float *>(p - t) + t;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
@@ -235,7 +233,7 @@ __global__ __launch_bounds__(E == 32 ? 128 : 256) void k_row_fwd_reg(float2 *__r
       q[M + T * i] = v[i].y;
     }
   }
-  if (planar == 2) {
+  if constexpr (PLANAR == 2) {
     // through LDS, so that a wavefront (whole rows, which its lanes have all read) writes its 64 / T rows as
     // one run; rows 2 M + T floats apart there: no bank conflicts
     constexpr int PITCH = 2 * M + T;
@@ -266,10 +264,25 @@ __global__ __launch_bounds__(E == 32 ? 128 : 256) void k_row_fwd_reg(float2 *__r
         if (lane + 64 * j < left) q[64 * j] = o[j];
     }
   }
-  if (!valid || planar) return;
+  if (PLANAR == 0 && valid) {
 #pragma unroll
-  for (int i = 0; i < E; ++i) p[T * i] = v[i];
+    for (int i = 0; i < E; ++i) p[T * i] = v[i];
+  }
 }
+
+// (kernels of their own: in one kernel with the layout as an argument all took 91 ... 110 registers, five or four waves
+// a SIMD; the plain transform of up to 128 points takes 58 ... 70, eight or seven)
+template <int E, int T>
+__global__ __launch_bounds__(E == 32 ? 128 : 256) void k_row_fwd_reg(float2 *__restrict__ data, long rows,
+                                                                     const float2 *__restrict__ tw, int tw_n) {
+  row_fwd<E, T, 0>(data, rows, tw, tw_n);
+}
+template <int E, int T, bool RUNS>
+__global__ __launch_bounds__(256) void k_row_fwd_planar(float2 *__restrict__ data, long rows,
+                                                        const float2 *__restrict__ tw, int tw_n) {
+  row_fwd<E, T, RUNS ? 2 : 1>(data, rows, tw, tw_n);
+}
+
 
 // ------------------------------------------------------------------------------------
 // k_mulfold_invrow with the transform in registers (output rows of E*T points, T lanes per
@@ -2255,13 +2268,23 @@ hipError_t launch_row_fwd_reg_t(float2 *data, long rows, bool planar, const floa
   if (rows <= 0 || blocks > 0x7fffffffL || tw_n % (E * T) != 0) return hipErrorInvalidValue;
   // planar rows: writes of T floats at a time where the launch is a matter of latency and T is not too
   // short for that (T = 2, 16 planes of 64 x 32: 10.8 us, in runs 8.6), else whole runs
-  const int mode = !planar ? 0 : blocks < (T < 4 ? 2 : 256) ? 1 : 2;
-  const size_t lds = T == 1 && mode != 2 ? 0 : static_cast<size_t>(RPB) * E * (T + 1) * sizeof(float2);
-  const std::string name = "k_row_fwd_reg<" + std::to_string(E) + ", " + std::to_string(T) + ">";
+  const bool runs = planar && blocks >= (T < 4 ? 2 : 256);
+  const size_t lds = T == 1 && !runs ? 0 : static_cast<size_t>(RPB) * E * (T + 1) * sizeof(float2);
+  const std::string name = std::string(planar ? "k_row_fwd_planar<" : "k_row_fwd_reg<") + std::to_string(E) + ", " +
+                           std::to_string(T) + (!planar ? ">" : runs ? ", true>" : ", false>");
   Observe ob(name.c_str(), static_cast<double>(rows) * E * T * 16,
              static_cast<double>(rows) * fft_flops(E * T), st);
-  hipLaunchKernelGGL((k_row_fwd_reg<E, T>), dim3(static_cast<unsigned>(blocks)), dim3(NT), lds, st,
-                     data, rows, mode, tw, tw_n);
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (!planar) {
+    hipLaunchKernelGGL((k_row_fwd_reg<E, T>), grid, dim3(NT), lds, st, data, rows, tw, tw_n);
+  } else if constexpr (E == 16) {
+    if (runs)
+      hipLaunchKernelGGL((k_row_fwd_planar<E, T, true>), grid, dim3(NT), lds, st, data, rows, tw, tw_n);
+    else
+      hipLaunchKernelGGL((k_row_fwd_planar<E, T, false>), grid, dim3(NT), lds, st, data, rows, tw, tw_n);
+  } else {
+    return hipErrorInvalidValue;  // (the fused schedule's rows have at most 256 points)
+  }
   return hipGetLastError();
 }
 

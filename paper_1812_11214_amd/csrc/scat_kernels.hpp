@@ -158,7 +158,7 @@ hipError_t launch_rows2d_adj(float2 *dst, long nodes, int Sr, int Sc, const Rows
                              const float2 *tw, int tw_n, hipStream_t st);
 
 // planar: every row is left as its Mc real parts followed by its Mc imaginary parts (what k_node_rect
-// reads; rows of 16 ... 512 points)
+// reads; rows of 16 ... 256 points)
 hipError_t launch_row_fwd(float2 *data, long rows, int Mc, const float2 *tw, int tw_n,
                           hipStream_t st, bool planar = false);
 
