@@ -133,7 +133,7 @@ __global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectAr
     };
     // (a node takes its own filter's blocks and no others, whatever nodes it shares a wavefront with: its bits
     // do not depend on its place in the batch, and an infinity in a block that it leaves out does not reach it.
-    // 16 planes of 64 x 64, J = 3, L = 8 74.6 -> 76.2 us, 200 planes 154.1 -> 156.2)
+    // 16 planes of 64 x 64, J = 3, L = 8 74.7 -> 75.3 us, of 64 x 32, J = 2, 46.4 -> 47.2)
     auto add = [&](const Unit &un, int g) {
       if (!un.own) return;
 #pragma unroll
@@ -149,41 +149,45 @@ __global__ __launch_bounds__((RectShape<N1, N2>::NT), 4) void k_node_rect(RectAr
       for (int g = 0; g < 4; ++g) load(un[g], g, 0, 1ull);
 #pragma unroll
       for (int g = 0; g < 4; ++g) add(un[g], g);
-    } else
+    } else {
+      unsigned long long owns[4];  // (all before the first use of any: 16 planes of 64 x 64 75.9 -> 75.3 us)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const unsigned long long own = a.mask[block + g * (N2 / S::CW)];
-      unsigned long long rem = own;
-      if (TS < 64) {  // slabs that share a wavefront: what any of them uses
-        rem |= __shfl_xor(rem, 32);
-        if (TS < 32) rem |= __shfl_xor(rem, 16);
-        rem = (static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<int>(rem >> 32))) << 32) |
-              static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(rem)));
-      }
-      auto next = [&] {
-        const int bit = __ffsll(static_cast<long long>(rem)) - 1;
-        rem &= rem - 1ull;
-        return bit;
-      };
-      int n = __popcll(rem);
-      for (; n >= 4; n -= 4) {
-        Unit un[4];
+      for (int g = 0; g < 4; ++g) owns[g] = a.mask[block + g * (N2 / S::CW)];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) load(un[e], g, next(), own);
+      for (int g = 0; g < 4; ++g) {
+        const unsigned long long own = owns[g];
+        unsigned long long rem = own;
+        if (TS < 64) {  // slabs that share a wavefront: what any of them uses
+          rem |= __shfl_xor(rem, 32);
+          if (TS < 32) rem |= __shfl_xor(rem, 16);
+          rem = (static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<int>(rem >> 32))) << 32) |
+                static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(rem)));
+        }
+        auto next = [&] {
+          const int bit = __ffsll(static_cast<long long>(rem)) - 1;
+          rem &= rem - 1ull;
+          return bit;
+        };
+        int n = __popcll(rem);
+        for (; n >= 4; n -= 4) {
+          Unit un[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) add(un[e], g);
-      }
-      if (n & 2) {
-        Unit un[2];
-        load(un[0], g, next(), own);
-        load(un[1], g, next(), own);
-        add(un[0], g);
-        add(un[1], g);
-      }
-      if (n & 1) {
-        Unit un;
-        load(un, g, next(), own);
-        add(un, g);
+          for (int e = 0; e < 4; ++e) load(un[e], g, next(), own);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) add(un[e], g);
+        }
+        if (n & 2) {
+          Unit un[2];
+          load(un[0], g, next(), own);
+          load(un[1], g, next(), own);
+          add(un[0], g);
+          add(un[1], g);
+        }
+        if (n & 1) {
+          Unit un;
+          load(un, g, next(), own);
+          add(un, g);
+        }
       }
     }
   }
