@@ -324,9 +324,7 @@ void fused_scratch(const scat_plan &p, bool whole, Layout &L) {
   const size_t n = static_cast<size_t>(p.n1) * p.n2, l = h.LQ, m_r = p.n1 >> h.res(h.J);
   size_t t = 0, v = 0, w = m_r * p.n2;
   for (int j1 = 0; j1 < h.J; ++j1) {
-    // (nodes of 128 x 128 count as the passes': the size that callers are told, and with it their
-    // chunks, is the one from before k_node_half took them)
-    if (!(whole && rect_first_fits(p, j1)) || (p.n1 >> h.res(j1) == 128 && p.n2 >> h.res(j1) == 128)) {
+    if (!(whole && rect_first_fits(p, j1))) {
       t += l * (n >> (2 * h.res(j1)));
       w = std::max(w, l * m_r * (p.n2 >> h.res(j1)));
     }

@@ -162,7 +162,7 @@ def test_reserve_argument_errors_need_no_gpu():
 
 
 @pytest.mark.parametrize("shape,J,L,max_order,on_passes", [
-    ((128, 128), 3, 8, 2, (0,)),      # octave 0 on the passes, its children whole
+    ((128, 128), 3, 8, 2, ()),        # every node whole, octave 0 by k_node_half
     ((256, 128), 3, 5, 1, (0,)),
     ((256, 256), 4, 8, 2, (0, 1)),    # and the 128 x 128 children of octave 0
     ((64, 64), 3, 8, 2, ()),          # every node whole

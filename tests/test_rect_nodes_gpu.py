@@ -25,7 +25,7 @@ def run(shape, J, L, max_order, padded, x, **kw):
 
 
 @pytest.mark.parametrize("shape,J,L,max_order,padded,batch", [
-    ((128, 128), 3, 8, 2, False, 2),   # 64 x 64 and 32 x 32 nodes, octave 0 on the passes
+    ((128, 128), 3, 8, 2, False, 2),   # 64 x 64 and 32 x 32 nodes, octave 0 by k_node_half
     ((128, 128), 4, 3, 2, False, 1),   # 64, 32 and 16 a side, subsampling 8, 4 and 2
     ((64, 64), 2, 5, 2, False, 3),     # 15 first-order nodes: a last workgroup that is not full
     ((64, 64), 3, 1, 2, False, 9),     # one angle; more sources than a group of eight
