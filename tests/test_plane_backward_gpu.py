@@ -28,7 +28,8 @@ def rel(a, b):
 
 
 @pytest.mark.parametrize("shape,J,L,max_order,padded,o,batch", [
-    ((32, 32), 2, 8, 2, False, 0, 3),    # a last workgroup that is not full
+    ((32, 32), 1, 8, 2, False, 0, 3),    # a last workgroup that is not full (at J = 2 it is a tree's)
+    ((32, 32), 2, 3, 2, False, 1, 5),    # oversampled, so no tree: octaves of one size
     ((64, 64), 3, 3, 2, False, 0, 2),    # 64, 32 and 16 a side
     ((64, 128), 3, 2, 2, False, 0, 1),   # wide
     ((128, 64), 2, 1, 2, False, 0, 5),   # tall; one angle
@@ -37,7 +38,7 @@ def rel(a, b):
     ((64, 32), 2, 5, 1, False, 0, 2),    # first order only
     ((32, 64), 1, 4, 2, False, 0, 2),    # no children
     ((64, 64), 3, 2, 2, False, 2, 2),    # oversampled: octaves of one size
-    ((28, 27), 2, 8, 2, True, 0, 3),
+    ((28, 27), 1, 8, 2, True, 0, 3),     # padded to 32 x 32
     ((50, 33), 2, 3, 2, True, 0, 2),
 ])
 def test_plane_backward(shape, J, L, max_order, padded, o, batch):
@@ -50,7 +51,11 @@ def test_plane_backward(shape, J, L, max_order, padded, o, batch):
 
     print("plane", shape, J, L, max_order, padded, o, flush=True)
     got, names, gg = run(shape, J, L, max_order, x, g, padded, o)
-    assert any(s.startswith("k_plane_nodes<") for s in names), names
+    n1, n2 = ((1 << (n + 2 ** J - 1).bit_length()) for n in shape) if padded else shape
+    sides = {(n1 >> max(j - o, 0), n2 >> max(j - o, 0)) for j in range(J)}
+    assert {s for s in names if s.startswith("k_plane_nodes<") and s.endswith(", true>")} == {
+        "k_plane_nodes<%d, %d, true>" % s for s in sides}, names
+    assert {"k_plane_end<%d, %d, true>" % (n1, n2), "k_plane_end<%d, %d, false>" % (n1, n2), "k_plane_sum"} <= names
     old, names, _ = run(shape, J, L, max_order, x, g, padded, o, node_kernels=False)
     assert not any(s.startswith("k_plane_") for s in names), names
     if padded:
