@@ -182,15 +182,20 @@ def test_backward_1d(n, J, Q, max_order, o, batch):
     assert worst_max <= TOL_MAX and worst_l2 <= TOL_L2, (worst_max, worst_l2)
 
 
-@pytest.mark.parametrize("shape,J,LQ,batch", [((64, 64), 3, 4, 7), ((4096,), 5, 4, 5)])
-def test_backward_in_chunks_matches_one_pass(shape, J, LQ, batch):
-    """A scratch budget that forces one plane per chunk (read once per process, hence the child
+@pytest.mark.parametrize("shape,J,LQ,batch,padded", [
+    ((64, 64), 3, 4, 7, False),
+    ((4096,), 5, 4, 5, False),
+    ((32, 32), 2, 8, 40, False),   # a tree: 13 planes a chunk, the last one not full
+    ((28, 21), 2, 5, 45, True),
+])
+def test_backward_in_chunks_matches_one_pass(shape, J, LQ, batch, padded):
+    """A scratch budget that forces one plane (32 x 32: a few) per chunk (read once per process, hence the child
     process) gives bit for bit the gradient of the single-chunk pass."""
     import torch
     import subprocess, sys, os, tempfile
     rng = np.random.default_rng(5 + len(shape))
     x = rng.standard_normal((batch,) + shape).astype(np.float32)
-    plan = scat.Scattering(shape, J, LQ)
+    plan = scat.Scattering(shape, J, LQ, padded=padded)
     try:
         g = rng.standard_normal((batch, plan.K) + plan.out_shape).astype(np.float32)
         a = plan.backward(torch.from_numpy(x).cuda(), torch.from_numpy(g).cuda())
@@ -203,11 +208,12 @@ def test_backward_in_chunks_matches_one_pass(shape, J, LQ, batch):
         "sys.path.insert(0, %r)\n"
         "import paper_1812_11214_amd as scat\n"
         "d = np.load(sys.argv[1])\n"
-        "p = scat.Scattering(%r, %d, %d)\n"
+        "p = scat.Scattering(%r, %d, %d, padded=%r)\n"
+        "assert p.backward_workspace_bytes(len(d['x'])) < len(d['x']) * p.backward_workspace_bytes(1)\n"
         "y = p.backward(torch.from_numpy(d['x']).cuda(), torch.from_numpy(d['g']).cuda())\n"
         "torch.cuda.synchronize()\n"
         "np.save(sys.argv[2], y.cpu().numpy()); p.close()\n"
-    ) % (os.path.dirname(os.path.dirname(os.path.abspath(__file__))), shape, J, LQ)
+    ) % (os.path.dirname(os.path.dirname(os.path.abspath(__file__))), shape, J, LQ, padded)
     with tempfile.TemporaryDirectory() as d:
         inp, out = os.path.join(d, "in.npz"), os.path.join(d, "y.npy")
         np.savez(inp, x=x, g=g)
