@@ -304,8 +304,9 @@ int rect_mask_columns(int N2) { return rect_mask_width(N2); }
 bool node_rect_supported(int N1, int N2, int A, int dec) {
   // 128 x 128 in octave 0 only: from larger sources k_node_half wants their filters in a layout of its own,
   // and the passes take 128 + 42 us there for the 1536 + 192 nodes of 24 planes of 256 x 256, which it would
-  // not do in less.  On every batch and number of angles tried (1 ... 400 planes, 1 ... 12) it is the faster
-  // way: 1 plane, L = 8 107 -> 93 us, 400 planes 983 -> 807, first order only 357 -> 237.
+  // not do in less.  Passes -> k_node_half, us: J = 3 on every batch and number of angles tried (1 ... 400 planes,
+  // 1 ... 12): 1 plane, L = 8 107 -> 93, 400 planes 983 -> 807, first order only 357 -> 237; J = 4 for all but few nodes of
+  // one or two angles (rect_pays): 1 plane, L = 8 155 -> 134, 256 planes 712 -> 574, first order only, L = 5, 172 -> 132.
   if (N1 == 128 && N2 == 128) return A == 1 && (dec == 8 || dec == 16);
   return pow2i(N1) && pow2i(N2) && N1 >= 16 && N2 >= 16 && N1 * N2 <= 8192 &&
          (N1 == N2 || N1 == 2 * N2 || N2 == 2 * N1) && (dec == 2 || dec == 4 || dec == 8) && 8 * dec <= N2 && pow2i(A) &&

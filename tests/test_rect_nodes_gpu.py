@@ -93,13 +93,15 @@ def test_all_variants_are_tested():
 @pytest.mark.parametrize("shape,J,L,max_order,few,many", [
     ((128, 128), 4, 1, 1, 2, 300),
     ((128, 128), 4, 1, 2, 1, 150),
+    ((128, 128), 4, 2, 2, 2, 8),      # two angles and second-order nodes: the passes up to four planes
+    ((128, 128), 4, 3, 1, None, 1),   # three: whole nodes at any batch
     ((256, 128), 4, 2, 1, 1, 80),
     ((128, 256), 3, 1, 1, 3, 520),
     ((128, 128), 4, 5, 1, None, 1),   # more angles: whole nodes at any batch
 ])
 def test_few_nodes_of_few_angles_keep_the_passes(shape, J, L, max_order, few, many):
-    """Calls that k_node_rect makes slower (few first-order nodes beside an octave 0 on the passes)
-    run on the passes, larger ones of the same plan do not; the coefficients are the same."""
+    """Calls that k_node_rect makes slower (few first-order nodes of few angles) run on the passes, larger
+    ones of the same plan do not; the coefficients are the same."""
     rng = np.random.default_rng(shape[1] + 7 * J + L)
     x = rng.standard_normal((many,) + shape).astype(np.float32)
     got, names, rows = run(shape, J, L, max_order, False, x)
