@@ -811,7 +811,7 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k_node_modback(
 // 2-D transform of the node, a third of its LDS exchanges.  6144 leaves of 128 x 128 under 96 planes of
 // 256 x 256 643 -> 498 us, and seven small transforms of 18 us became three of 10; training step 3575 -> 3340 us;
 // error against 64 bits 0.98 of the other's.  128 x 128: bound by the loads and stores of the one workgroup a
-// compute unit that its 128 registers allow (3.2 TB/s).  Smaller nodes exchange real and imaginary parts in
+// compute unit that its 158 KB of LDS allow (3.2 TB/s).  Smaller nodes exchange real and imaginary parts in
 // turn, through a plane of floats: four and more workgroups a compute unit.
 template <int N1, int N2, int MR>
 struct LeafShape {

@@ -284,8 +284,9 @@ __device__ __forceinline__ void line_node(const NodeArgs &a, const NodeSeg &g, u
 // threads; two workgroups of eight waves fit a compute unit (70 KB of LDS each).  With 256 threads of 32
 // samples it was eight waves: 32 x 8192, J = 5, Q = 8 forward 58.1 -> 56.6 us, backward 138 -> 133; 200 x 7000, first
 // order, 123 -> 118, 243 -> 222; 600 x 8192 611 -> 604, 1722 -> 1717.  The adjoint holds a node's signal beside
-// its gradient: without BIG four waves a SIMD would spill and be slower than three; BIG has to have them (two
-// waves, one workgroup a compute unit: 32 x 8192 145 us, 600 x 8192 1913).
+// its gradient: without BIG four waves a SIMD would spill and be slower than three; BIG has to have them, and
+// with them 20 bytes of scratch a lane, in the times above (two waves, no scratch, one workgroup a compute unit: 32 x 8192
+// 145 us, 600 x 8192 1913).
 constexpr int line_threads(bool big) { return big ? 512 : 256; }
 template <bool BACK, bool BIG>
 __global__ __launch_bounds__(line_threads(BIG), BACK && !BIG ? 3 : 4) void k_line_nodes(NodeArgs a) {

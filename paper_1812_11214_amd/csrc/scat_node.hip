@@ -646,8 +646,10 @@ __global__ __launch_bounds__(512, 4) void k_node_pair(NodeArgs a) { node_body<64
 // DEC: 4 for 32 outputs a side (4 output steps of taps each side); 8 and 16 with the filter of k_node_rect
 // (5 steps, summed from the tails to the centre): octave 0 of 128 x 128 grids at J = 3 and 4, whose row
 // pass, column pass, row half of the lowpass and row transform (27 + 42 + 7 + 23 us for 768 nodes) it
-// replaces: 96 planes, J = 3, L = 8: 48 us for the nodes, 300 -> 242 us for the call; error against 64 bits
-// 0.96 ... 1.0 of the passes'.
+// replaces: 96 planes, J = 3, L = 8: 53 us for the nodes, 300 -> 242 us for the call; J = 4, L = 8, 256 planes 712 ->
+// 574 us, one plane 155 -> 134; error against 64 bits 0.96 ... 1.0 of the passes'.  At 128 registers the FIR stages do not
+// all fit: 32 bytes of scratch a lane at DEC = 8, 216 at DEC = 16 (its 161 taps are unrolled), in the times above; and
+// 56 in the variants that read a full spectrum (512 x 512).
 template <int A, int P, bool POLY, bool FULL, int DEC = 4>
 __global__ __launch_bounds__(512, 4) void k_node_half(NodeArgs a) {
   static_assert(!FULL || P == 1, "a full spectrum is one source");

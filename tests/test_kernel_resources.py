@@ -59,3 +59,28 @@ def test_plain_row_transforms_keep_their_waves(kernels):
     for name, most in (("<16, 1>", 64), ("<16, 2>", 72), ("<16, 4>", 72), ("<16, 8>", 72), ("<16, 16>", 88),
                        ("<32, 16>", 144)):
         assert kernels["k_row_fwd_reg" + name][".vgpr_count"] <= most, name
+
+
+# Kernels that keep part of a lane's state in scratch memory, and the bytes a lane.  Each says so at its launch
+# bounds or is measured as the faster one with it.
+SCRATCH = {
+    "k_node_half<1, 1, false, false, 8>": 32,
+    "k_node_half<1, 1, false, false, 16>": 216,
+    "k_node_half<2, 1, false, true, 4>": 56,
+    "k_node_half<4, 1, false, true, 4>": 56,
+    "k_line_nodes<true, true>": 20,
+    "k_plane_nodes<128, 128, true>": 56,
+    "k_node_modback<128, 128, false, true>": 40,
+    "k_node_modback<128, 128, true, true>": 44,
+    "k_rows1d_reg<16, 16, false>": 12,
+    "k_rows1d_reg<16, 16, true>": 8,
+    "k_rows1d_adj<16, 4>": 12,
+    "k3_slab_fwd_mulacc<128, 128>": 16,
+    "k3_slab_fwd_mulacc<64, 256>": 8,
+}
+
+
+def test_no_other_kernel_uses_scratch(kernels):
+    used = {name: k[".private_segment_fixed_size"] for name, k in kernels.items() if k[".private_segment_fixed_size"]}
+    assert set(used) <= set(SCRATCH), used
+    assert all(size <= SCRATCH[name] for name, size in used.items()), used
