@@ -293,15 +293,15 @@ bool rect_node_fits(const scat_plan &p, int r, int j) {
 // one after another: 25 us for one 16 x 16 node under a 128 x 128 plane).  Few nodes of few angles do not hide that.
 // Passes -> whole nodes, us, J = 4.  128 x 128 (octave 0 whole too): one angle, first order only, one plane 64 -> 77, 128
 // planes 89 -> 92, 256 117 -> 99; two angles, 64 planes 80 -> 88, 128 98 -> 94; three, one plane 71 -> 69; with second-order
-// nodes, one angle, 64 planes 177 -> 184, 128 203 -> 191; two, one plane 154 -> 168, 8 planes 179 -> 177; three, one plane
-// 170 -> 150.  Larger grids, octave 0 on the passes, first order only: 256 x 128, one angle, one plane 65 -> 81, 200 planes
+// nodes, one angle, 64 planes 177 -> 184, 128 203 -> 191; two, one plane 154 -> 168, 30 planes 184 -> 186, 60 201 -> 191; three,
+// one plane 170 -> 150.  Larger grids, octave 0 on the passes, first order only: 256 x 128, one angle, one plane 65 -> 81, 200 planes
 // 182 -> 150, two angles, 60 planes 109 -> 118; 256 x 256, two angles, 32 planes 113 -> 120, three, 42 planes, 159 -> 142 (the
 // line there is on the safe side: with second-order nodes of one angle up to 9 % of a call are left).  At J = 3 only rows
 // of 256 lose (128 x 256, one angle, first order, 64 planes 71 -> 82, 400 planes even).
 bool rect_pays(const scat_plan &p, long batch) {
   const scat::HostPlan &h = p.host;
   const double angles = static_cast<double>(h.LQ) * h.max_order, nodes = static_cast<double>(batch) * angles;
-  if (h.J == 4 && p.n1 == 128 && p.n2 == 128) return h.LQ > 2 || nodes > (angles > 2 ? 16 : 160);
+  if (h.J == 4 && p.n1 == 128 && p.n2 == 128) return h.LQ > 2 || nodes > 160;
   if (h.J == 4)
     return angles > 4 || angles * angles * p.n1 * p.n2 > 4 * 4 * 128 * 128 || nodes * std::max(p.n1, 128) > 256 * 128;
   if (h.J == 3 && p.n2 == 256) return angles * h.max_order > 4 || nodes * h.max_order > 512;

@@ -93,7 +93,7 @@ def test_all_variants_are_tested():
 @pytest.mark.parametrize("shape,J,L,max_order,few,many", [
     ((128, 128), 4, 1, 1, 2, 300),
     ((128, 128), 4, 1, 2, 1, 150),
-    ((128, 128), 4, 2, 2, 2, 8),      # two angles and second-order nodes: the passes up to four planes
+    ((128, 128), 4, 2, 2, 40, 41),    # two angles and second-order nodes: the passes up to 160 nodes
     ((128, 128), 4, 3, 1, None, 1),   # three: whole nodes at any batch
     ((256, 128), 4, 2, 1, 1, 80),
     ((128, 256), 3, 1, 1, 3, 520),
