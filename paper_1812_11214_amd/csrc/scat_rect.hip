@@ -10,11 +10,12 @@
 // transform as little as after the modulus: 8 + 8 + 4 bytes per point saved.  The nodes that fit
 // take it, but for small calls of few angles (rect_pays in scat_capi.hip): 96 planes of 128 x 128, J = 3,
 // L = 8, 600 -> 297 us (their 6144 + 6144 second-order nodes of octave 0: 331 -> 128 us); 48 planes of
-// 200 x 120 543 -> 334 us.  With spectra as real and imaginary rows (below) 315 us for the latter; with
-// octave 0 whole too (k_node_half) 224 us for the former.
-// What bounds it: 6144 nodes of 64 x 64 under 128 x 128 take 80 us; without their loads 49, loads alone 47,
-// and the two hardly overlap, with more waves (5 and 7 a SIMD) or more loads in flight (12 ... 48 a lane) as
-// little.
+// 200 x 120 543 -> 343 us.  With spectra as real and imaginary rows (below) 325 us for the latter; with
+// octave 0 whole too (k_node_half) 227 us for the former.
+// What bounds it: vector issue, with the loads' address path close behind.  6144 nodes of 64 x 64 under 128 x 128 take
+// 83 us under the counters: 0.69 of the issue slots at 2.4 GHz, which is about 0.8 at the 2 GHz that the busy cycles show,
+// and 0.57 (about 0.7) of the address path's cycles.  Without their loads they take 49, loads alone 47; more waves (5 and
+// 7 a SIMD) or more loads in flight (12 ... 48 a lane) changed little.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
