@@ -245,7 +245,9 @@ __global__ __launch_bounds__((Slab<N1, N2>::NT)) void k3_slab_fwd_low(Nodes3 nod
   const bool live = slab < slabs;
   const long sl = live ? slab : slabs - 1;
   float2 *area = lds + s * N1 * S::RS;
-  // (twiddles from LDS tables, fetched while the slab is: 39.7 -> 36.2 us a launch of 16 x 64^3)
+  // (twiddles from LDS tables, fetched while the slab is: 39.7 -> 36.2 us a launch of 16 x 64^3; with them slabs of
+  // 16 x 256 fit a compute unit three instead of four times, which costs nothing: J = 2, L = 2, 24 volumes of
+  // 16 x 16 x 256 169.4 -> 168.7 us, gradient 360.9 -> 357.3; of 64 x 16 x 256 648.8 -> 645.5, 1478 -> 1476)
   float2 *wtab = lds + S::SPW * N1 * S::RS;
   S::fill_twiddles(wtab, tw, tw_n, false);
   const int r = q / S::T2, t = q % S::T2;
